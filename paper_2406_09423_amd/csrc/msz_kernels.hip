@@ -709,16 +709,62 @@ __host__ __device__ __forceinline__ int label_tiles_of(const Grid& gr) {
     return ((gr.nx + T::X - 1) / T::X) * ((gr.ny + T::Y - 1) / T::Y) * ((gr.nz + T::Z - 1) / T::Z);
 }
 
-// The stored pointer of a tile-pass terminal a (tile origin X0, Y0, Z0): an
-// exit code -e-1 as it is, an extremum's local code as its global id.  (A
-// non-negative a, a local index, cannot remain after the jumping; it would
-// name an in-tile ancestor.)
+// Pointer codes of the tile pass while it runs: an id (an extremum of the
+// grid, >= 0 and below kLocalCode), an exit -e-1 (negative), or the in-tile
+// vertex with local index l as kLocalCode + 4 l (its byte offset in the LDS
+// arrays).  Ids stay below 2^31 - 2^16, so the codes never meet, and a
+// finished pointer is stored as it is.
+constexpr int kLocalCode = 0x7FFFC000;
+
+// What a slot means inside a label tile: the step in the packed coordinates
+// of tile_pos, in local codes, and the code of a target outside the tile,
+// (i ^ flip) + step_id for a vertex i.  One 16-byte LDS read per pointer
+// replaces decoding the slot's three components and testing each against the
+// tile's box.
+struct __align__(16) SlotStep {
+    int pos, local, flip, id;
+};
+
+// Local coordinates packed so that a step out of the tile shows in one mask:
+// a coordinate c of extent E (a power of two) is stored as c + E in a field
+// of log2(E) + 2 bits, so bits E and 2E of the field read 01 inside the tile
+// and 00 or 10 one step outside it.
+constexpr int log2_of(int e) { return e <= 1 ? 0 : 1 + log2_of(e / 2); }
 template <int NDIM>
-__device__ __forceinline__ int tile_term_global(const Grid& gr, int X0, int Y0, int Z0, int a) {
+struct TilePos {
     using T = LabelTile<NDIM>;
-    if (a < 0 && a >= -gr.n) return a;
-    const int l = a < 0 ? -a - 1 - gr.n : a;
-    return X0 + l % T::X + gr.nx * (Y0 + (l / T::X) % T::Y) + gr.nxy * (Z0 + l / (T::X * T::Y));
+    static constexpr int SY = log2_of(T::X) + 2, SZ = SY + log2_of(T::Y) + 2;
+    static constexpr int kIn = T::X | (T::Y << SY) | (NDIM == 3 ? T::Z << SZ : 0);
+    static constexpr int kMask = 3 * kIn;
+    __device__ __forceinline__ static int of(int lx, int ly, int lz) {
+        return kIn + lx + (ly << SY) + (NDIM == 3 ? lz << SZ : 0);
+    }
+    __device__ __forceinline__ static bool inside(int pos) { return (pos & kMask) == kIn; }
+};
+
+// Fills the 16 entries of a block's slot table; the caller puts a barrier
+// between this and the first label_tile_body.
+template <int NDIM>
+__device__ __forceinline__ void fill_slot_steps(const Grid& gr, SlotStep* tab) {
+    using T = LabelTile<NDIM>;
+    using P = TilePos<NDIM>;
+    if (threadIdx.x < 16) {
+        int dx, dy, dz;
+        slot_delta(threadIdx.x, dx, dy, dz);
+        SlotStep s;
+        if (threadIdx.x < 14) {
+            s.pos = dx + dy * (1 << P::SY) + (NDIM == 3 ? dz * (1 << P::SZ) : 0);
+            s.local = 4 * (dx + T::X * (dy + T::Y * dz));
+            s.flip = -1;  // -(i + off) - 1 = ~i - off
+            s.id = -(dx + gr.nx * dy + gr.nxy * dz);
+        } else {  // the vertex itself: never inside (a step of X reads 10), its id
+            s.pos = T::X;
+            s.local = 0;
+            s.flip = 0;
+            s.id = 0;
+        }
+        tab[threadIdx.x] = s;
+    }
 }
 
 // Follows K chains of exits from stored pointers y[k] to their roots, one
@@ -758,17 +804,24 @@ __device__ __forceinline__ void follow_roots(const int* q_up, const int* q_dn, i
     }
 }
 
-// One label tile; su, sd: LDS arrays of the tile's vertex count.  The caller
-// separates consecutive tiles of one block with a barrier.
+// One label tile; su, sd: LDS arrays of the tile's vertex count; tab: the
+// block's slot table (fill_slot_steps).  The caller separates consecutive
+// tiles of one block with a barrier.
 //
 // Thread t owns the 4-vertex row groups starting at l = 4 t + 1024 k and
 // keeps their pointers in registers; the LDS copy is what other threads read.
-// Terminal pointers are negative: an exit e as -e-1 (in -n .. -1), an in-tile
-// extremum with local index l as -(n + l) - 1 (below -n; n + 4096 < 2^31).
+//
+// The pass streams 1 byte in and 8 out per vertex, but was bound by
+// instruction issue (building the two first pointers of a vertex and turning
+// the terminals into ids took most of its instructions).  With the slot table
+// and codes that need no conversion at the end the pass over 256^3 takes
+// 40.6 us where it took 74.2 (3.7 TB/s, was 2.0; a large copy reaches 5.1).
 template <int NDIM>
 __device__ __forceinline__ void label_tile_body(const uint8_t* __restrict__ dirs, const Grid& gr, int tile,
-                                                int* __restrict__ q_up, int* __restrict__ q_dn, int* su, int* sd) {
+                                                int* __restrict__ q_up, int* __restrict__ q_dn, int* su, int* sd,
+                                                const SlotStep* tab) {
     using T = LabelTile<NDIM>;
+    using P = TilePos<NDIM>;
     constexpr int NT = T::X * T::Y * T::Z;
     constexpr int G = NT / 1024;  // row groups per thread
 
@@ -803,33 +856,18 @@ __device__ __forceinline__ void label_tile_body(const uint8_t* __restrict__ dirs
         const int lx0 = l0 % T::X, ly = (l0 / T::X) % T::Y, lz = l0 / (T::X * T::Y);
         const int xa = X0 + lx0, y = Y0 + ly, z = Z0 + lz;
         const bool row_in = y < gr.ny && z < gr.nz;
-        const int i0 = xa + gr.nx * y + gr.nxy * z;
+        // a group outside the grid counts from 0: its codes are ids that
+        // nothing points at and nothing stores
+        const int i0 = row_in && xa < gr.nx ? xa + gr.nx * y + gr.nxy * z : 0;
+        const int pos0 = P::of(lx0, ly, lz);
+        const unsigned du = d4[k], dd = d4[k] << 4;  // a slot's table offset: its nibble times 16
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int lx = lx0 + j;
-            int p[2] = {-1, -1};
-            if (row_in && xa + j < gr.nx) {
-                const int i = i0 + j;
-                const unsigned d = (d4[k] >> (8 * j)) & 0xFFu;
-                const unsigned s2[2] = {d >> 4, d & 15u};
-#pragma unroll
-                for (int w = 0; w < 2; ++w) {
-                    const unsigned s = s2[w];
-                    if (s == kSelf) {
-                        p[w] = -(gr.n + lx + T::X * (ly + T::Y * lz)) - 1;
-                    } else {
-                        int dx, dy, dz;
-                        slot_delta(s, dx, dy, dz);
-                        const int ax = lx + dx, ay = ly + dy, az = lz + dz;
-                        if (ax >= 0 && ax < T::X && ay >= 0 && ay < T::Y && az >= 0 && az < T::Z)
-                            p[w] = ax + T::X * (ay + T::Y * az);
-                        else
-                            p[w] = -(i + slot_offset(gr, s)) - 1;
-                    }
-                }
-            }
-            pu[k][j] = p[0];
-            pd[k][j] = p[1];
+            const SlotStep tu = *reinterpret_cast<const SlotStep*>(reinterpret_cast<const char*>(tab) + ((du >> (8 * j)) & 0xF0u));
+            const SlotStep td = *reinterpret_cast<const SlotStep*>(reinterpret_cast<const char*>(tab) + ((dd >> (8 * j)) & 0xF0u));
+            const int i = i0 + j, local = kLocalCode + 4 * (l0 + j);
+            pu[k][j] = P::inside(pos0 + j + tu.pos) ? local + tu.local : (i ^ tu.flip) + tu.id;
+            pd[k][j] = P::inside(pos0 + j + td.pos) ? local + td.local : (i ^ td.flip) + td.id;
         }
         *reinterpret_cast<int4*>(su + l0) = make_int4(pu[k][0], pu[k][1], pu[k][2], pu[k][3]);
         *reinterpret_cast<int4*>(sd + l0) = make_int4(pd[k][0], pd[k][1], pd[k][2], pd[k][3]);
@@ -844,35 +882,36 @@ __device__ __forceinline__ void label_tile_body(const uint8_t* __restrict__ dirs
     // path.  A group is skipped once the whole wave's copies of it are
     // terminal; otherwise its eight reads are issued together, branch-free
     // (a terminal pointer reads entry 0 and keeps its value).
+    const char* bu = reinterpret_cast<const char*>(su);
+    const char* bd = reinterpret_cast<const char*>(sd);
+    auto max8 = [](const int (&a)[4], const int (&b)[4]) {
+        return max(max(max(a[0], a[1]), max(a[2], a[3])), max(max(b[0], b[1]), max(b[2], b[3])));
+    };
     for (int iter = 0; iter < NT; ++iter) {
-        bool pending = false;
+        int top = 0;
 #pragma unroll
         for (int k = 0; k < G; ++k) {
-            bool live = false;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) live |= (pu[k][j] & pd[k][j]) >= 0;  // either is non-terminal
-            if (!__any(live)) continue;
+            if (!__any(max8(pu[k], pd[k]) >= kLocalCode)) continue;
             int nu[4], nd[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                nu[j] = su[max(pu[k][j], 0)];
-                nd[j] = sd[max(pd[k][j], 0)];
+                nu[j] = *reinterpret_cast<const int*>(bu + (max(pu[k][j], kLocalCode) & 0x3FFC));
+                nd[j] = *reinterpret_cast<const int*>(bd + (max(pd[k][j], kLocalCode) & 0x3FFC));
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                pu[k][j] = pu[k][j] >= 0 ? nu[j] : pu[k][j];
-                pd[k][j] = pd[k][j] >= 0 ? nd[j] : pd[k][j];
-                pending |= (pu[k][j] & pd[k][j]) >= 0;
+                pu[k][j] = pu[k][j] >= kLocalCode ? nu[j] : pu[k][j];
+                pd[k][j] = pd[k][j] >= kLocalCode ? nd[j] : pd[k][j];
             }
+            top = max(top, max8(pu[k], pd[k]));
             const int l0 = 4 * threadIdx.x + 1024 * k;
             *reinterpret_cast<int4*>(su + l0) = make_int4(pu[k][0], pu[k][1], pu[k][2], pu[k][3]);
             *reinterpret_cast<int4*>(sd + l0) = make_int4(pd[k][0], pd[k][1], pd[k][2], pd[k][3]);
         }
-        if (!pending) break;
+        if (top < kLocalCode) break;
     }
-    // Every in-tile path is shorter than the tile, so all pointers are terminal
-    // here: an exit keeps its code, an extremum becomes its id.
-    auto global_of = [&](int a) { return tile_term_global<NDIM>(gr, X0, Y0, Z0, a); };
+    // Every in-tile path is shorter than the tile, so all pointers are
+    // terminal here: ids and exit codes.
 #pragma unroll
     for (int k = 0; k < G; ++k) {
         const int l0 = 4 * threadIdx.x + 1024 * k;
@@ -882,15 +921,15 @@ __device__ __forceinline__ void label_tile_body(const uint8_t* __restrict__ dirs
         const int i0 = xa + gr.nx * y + gr.nxy * z;
         if (vec4 && xa + 3 < gr.nx) {
             *reinterpret_cast<int4*>(q_up + i0) =
-                make_int4(global_of(pu[k][0]), global_of(pu[k][1]), global_of(pu[k][2]), global_of(pu[k][3]));
+                make_int4(pu[k][0], pu[k][1], pu[k][2], pu[k][3]);
             *reinterpret_cast<int4*>(q_dn + i0) =
-                make_int4(global_of(pd[k][0]), global_of(pd[k][1]), global_of(pd[k][2]), global_of(pd[k][3]));
+                make_int4(pd[k][0], pd[k][1], pd[k][2], pd[k][3]);
         } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 if (xa + j < gr.nx) {
-                    q_up[i0 + j] = global_of(pu[k][j]);
-                    q_dn[i0 + j] = global_of(pd[k][j]);
+                    q_up[i0 + j] = pu[k][j];
+                    q_dn[i0 + j] = pd[k][j];
                 }
         }
     }
@@ -903,7 +942,10 @@ __global__ void __launch_bounds__(256) k_label_tile(const uint8_t* __restrict__ 
     constexpr int NT = LabelTile<NDIM>::X * LabelTile<NDIM>::Y * LabelTile<NDIM>::Z;
     __shared__ __align__(16) int su[NT];
     __shared__ __align__(16) int sd[NT];
-    label_tile_body<NDIM>(dirs, gr, xcd_logical_block(blockIdx.x, gridDim.x), q_up, q_dn, su, sd);
+    __shared__ __align__(16) SlotStep tab[16];
+    fill_slot_steps<NDIM>(gr, tab);
+    __syncthreads();
+    label_tile_body<NDIM>(dirs, gr, xcd_logical_block(blockIdx.x, gridDim.x), q_up, q_dn, su, sd, tab);
 }
 
 // Number of face-layer vertices of a full label tile.
@@ -1946,6 +1988,7 @@ __device__ __forceinline__ void eng_run_range(const EngField& F, const EngState&
     int* sd = su + 4096;
     float* sm = reinterpret_cast<float*>(smem);
     const int cidx[4] = {kCntCase + 0, kCntCase + 1, kCntCase + 2, kCntCase + 3};
+    __shared__ __align__(16) SlotStep s_tab[16];  // label tile passes
     switch (st.op) {
         case kOpPreA: {
             unsigned bad = 0;
@@ -1966,8 +2009,10 @@ __device__ __forceinline__ void eng_run_range(const EngField& F, const EngState&
             break;
         }
         case kOpPreB:  // the pointers of f's forests, kept for the troublemaker passes
+            fill_slot_steps<NDIM>(gr, s_tab);
+            __syncthreads();
             for (int item = lo; item < hi; ++item) {
-                label_tile_body<NDIM>(F.dirs_f, gr, item, F.Mf, F.mf, su, sd);
+                label_tile_body<NDIM>(F.dirs_f, gr, item, F.Mf, F.mf, su, sd, s_tab);
                 __syncthreads();
                 if (lead) acct += 9 * tile_vertices<NDIM>(gr, item);
             }
@@ -1975,9 +2020,11 @@ __device__ __forceinline__ void eng_run_range(const EngField& F, const EngState&
         case kOpRTile:
             // only tiles with a changed direction are redone: the others'
             // pointers are still those of their last pass
+            fill_slot_steps<NDIM>(gr, s_tab);
+            __syncthreads();
             for (int item = lo; item < hi; ++item) {
                 if (!F.tile_dirty[item]) continue;
-                label_tile_body<NDIM>(F.dirs_g, gr, item, F.qu, F.qd, su, sd);
+                label_tile_body<NDIM>(F.dirs_g, gr, item, F.qu, F.qd, su, sd, s_tab);
                 __syncthreads();
                 if (threadIdx.x == 0) {
                     F.tile_dirty[item] = 0;
