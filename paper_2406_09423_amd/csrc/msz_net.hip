@@ -26,7 +26,6 @@ namespace msz {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kNetC = 16;
 constexpr int kOffW0 = 0, kOffB0 = kOffW0 + 27 * 16 * 16, kOffW1 = kOffB0 + 16, kOffB1 = kOffW1 + 27 * 16 * 16,
               kOffW2 = kOffB1 + 16, kOffB2 = kOffW2 + 27 * 16, kNetParams = kOffB2 + 1;
 static_assert(kNetParams == MSZ_NET_PARAMS, "parameter layout");
@@ -66,65 +65,92 @@ __device__ __forceinline__ float weight_at(const WeightView& wv, int tap, int in
     return wv.W[t * wv.s_tap + in * wv.s_in + out * wv.s_out];
 }
 
-// Loads the input tile t (16 x TY x TZ vertices plus a one-vertex halo, CH16
-// 16-byte chunks per vertex, zeros outside the grid) into registers.
-template <int TY, int TZ, int CH16, int PER>
+// Input tile t of a convolution: 16 x TY x TZ vertices plus a one-vertex halo,
+// two 16-byte chunks (eight channels each) per vertex, zeros outside the grid.
+// Chunk e of the tile is chunk e % 2 of halo vertex e / 2.
+struct TileOrigin {
+    int X0, Y0, Z0;
+};
+template <int TY, int TZ>
+__device__ __forceinline__ TileOrigin conv_origin(int t, int tx_n, int ty_n) {
+    using T = ConvTile<TY, TZ>;
+    return {(t % tx_n) * T::X, ((t / tx_n) % ty_n) * T::Y, (t / (tx_n * ty_n)) * T::Z};
+}
+
+template <int TY, int TZ>
+__device__ __forceinline__ uint4 conv_chunk(const uint16_t* __restrict__ in, const Grid& gr, const TileOrigin& o,
+                                            int e) {
+    using T = ConvTile<TY, TZ>;
+    const int hv = e >> 1, ch = e & 1;
+    const int hx = hv % T::HX, hy = (hv / T::HX) % T::HY, hz = hv / (T::HX * T::HY);
+    const int x = o.X0 + hx - 1, y = o.Y0 + hy - 1, z = o.Z0 + hz - 1;
+    // an unconditional load (vertex 0 outside the grid), so that a thread's
+    // loads are all issued before the first one is waited for
+    const bool ok = x >= 0 && x < gr.nx && y >= 0 && y < gr.ny && z >= 0 && z < gr.nz;
+    const long vid = ok ? x + static_cast<long>(gr.nx) * y + static_cast<long>(gr.nxy) * z : 0;
+    const uint4 v = reinterpret_cast<const uint4*>(in)[2 * vid + ch];
+    return make_uint4(ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u);
+}
+
+template <int TY, int TZ, int PER>
 __device__ __forceinline__ void conv_tile_load(const uint16_t* __restrict__ in, const Grid& gr, int t, int tx_n,
                                                int ty_n, uint4 (&buf)[PER]) {
-    using T = ConvTile<TY, TZ>;
-    constexpr int NCH = T::HALO * CH16;
-    const int X0 = (t % tx_n) * T::X, Y0 = ((t / tx_n) % ty_n) * T::Y, Z0 = (t / (tx_n * ty_n)) * T::Z;
+    const TileOrigin o = conv_origin<TY, TZ>(t, tx_n, ty_n);
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int e = threadIdx.x + 256 * k;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (e < NCH) {
-            const int hv = e / CH16, ch = e - hv * CH16;
-            const int hx = hv % T::HX, hy = (hv / T::HX) % T::HY, hz = hv / (T::HX * T::HY);
-            const int x = X0 + hx - 1, y = Y0 + hy - 1, z = Z0 + hz - 1;
-            if (x >= 0 && x < gr.nx && y >= 0 && y < gr.ny && z >= 0 && z < gr.nz) {
-                const long vid = x + static_cast<long>(gr.nx) * y + static_cast<long>(gr.nxy) * z;
-                v = reinterpret_cast<const uint4*>(in)[vid * CH16 + ch];
-            }
-        }
-        buf[k] = v;
+        buf[k] = conv_chunk<TY, TZ>(in, gr, o, min(e, 2 * ConvTile<TY, TZ>::HALO - 1));
     }
 }
 
-enum : int { kConvHidden = 0, kConvFinal = 1, kConvBackData = 2 };
+enum : int { kConvHidden = 0, kConvBackData = 1 };
 
-// out = conv(in) for CIN input channels stored per vertex.
+// out = conv(in) for 16 input and 16 output channels.
 //  kConvHidden:   out16[v][16] = bf16(relu(conv + bias))
-//  kConvFinal:    out1[v]      = (conv + bias)[channel 0] (fp32, linear output)
 //  kConvBackData: out16[v][16] = bf16(conv * (mask[v][c] > 0))  (gradient through ReLU)
-template <int CIN, int TY, int TZ, int MODE>
+//
+// A row of 16 vertices takes 14 MFMAs in one chain, each with one 16-byte LDS
+// read per lane.  Four y-consecutive rows run side by side, so the chains
+// overlap, and a lane's LDS offset is one of 14 registers plus a row constant.
+// Bound by the LDS reads (8 cycles of the compute unit per MFMA, which takes
+// 4) and the 64 bytes per vertex it moves, about 210 us each for 256^3: 338 us
+// there, where one chain at a time with its address arithmetic took 468; for
+// 128^3, where loading the weights weighed more, 54 against 139.
+template <int TY, int TZ, int MODE>
 __global__ void __launch_bounds__(256) k_conv(const uint16_t* __restrict__ in, Grid gr, WeightView wv,
-                                              const uint16_t* __restrict__ mask, uint16_t* __restrict__ out16,
-                                              float* __restrict__ out1) {
+                                              const uint16_t* __restrict__ mask, uint16_t* __restrict__ out16) {
     using T = ConvTile<TY, TZ>;
-    constexpr int KSTEPS = CIN == 16 ? 14 : 7;   // 27 taps (+1 zero tap) x CIN / 32
-    constexpr int CH16 = CIN * 2 / 16;            // 16-byte chunks per vertex
-    __shared__ uint4 tile[T::HALO * CH16];
+    constexpr int KSTEPS = 14;  // 27 taps and one zero tap, two per MFMA
+    constexpr int R = 4;        // rows computed side by side
+    static_assert(T::Y % R == 0 && T::ROWS % (4 * R) == 0, "whole row groups per wave");
+    __shared__ uint4 tile[T::HALO * 2];
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m = lane & 15, g = lane >> 4;
 
-    // A operand (weights) of every K step, in registers for the whole kernel
+    // the weights as BF16 [out][tap][in] in the tile's LDS first: one strided
+    // global load per thread and tap, where a lane picking its own 112 values
+    // from memory cost each block some 35 us
+    static_assert(16 * 28 * 2 <= T::HALO * 2, "the weights fit the tile's LDS");
+    uint16_t* wl = reinterpret_cast<uint16_t*>(tile);
+#pragma unroll
+    for (int tap = 0; tap < 28; ++tap) {
+        const int ci = threadIdx.x >> 4, co = threadIdx.x & 15;
+        wl[(co * 28 + tap) * 16 + ci] = bf16_bits(weight_at(wv, tap, ci, co));
+    }
+    __syncthreads();
+
+    // A operand (weights) and the lane's tile offset (in chunks) of every K
+    // step, in registers for the whole kernel
     bf16x8 wa[KSTEPS];
+    int off[KSTEPS];
 #pragma unroll
     for (int s = 0; s < KSTEPS; ++s) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            int tap, ci;
-            if (CIN == 16) {
-                tap = 2 * s + (g >> 1);
-                ci = 8 * (g & 1) + j;
-            } else {
-                tap = 4 * s + g;
-                ci = j;
-            }
-            wa[s][j] = static_cast<__bf16>(weight_at(wv, tap, ci, m));
-        }
+        const int tap = 2 * s + (g >> 1);
+        wa[s] = __builtin_bit_cast(bf16x8, tile[(m * 28 + tap) * 2 + (g & 1)]);
+        int dx, dy, dz;
+        tap_delta(tap > 26 ? 26 : tap, dx, dy, dz);  // the zero-weight padding tap reads a valid address
+        off[s] = 2 * ((m + dx + 1) + T::HX * ((dy + 1) + T::HY * (dz + 1))) + (g & 1);
     }
     float bias[4];
 #pragma unroll
@@ -138,12 +164,12 @@ __global__ void __launch_bounds__(256) k_conv(const uint16_t* __restrict__ in, G
     const ItemRange range = xcd_items(ntiles);
     // the input tile (with halo) of the next tile is loaded into registers
     // while the current one is computed from LDS
-    constexpr int NCH = T::HALO * CH16;
+    constexpr int NCH = T::HALO * 2;
     constexpr int PER = (NCH + 255) / 256;
     uint4 buf[PER];
-    if (range.first < range.hi) conv_tile_load<TY, TZ, CH16, PER>(in, gr, range.first, tx_n, ty_n, buf);
+    if (range.first < range.hi) conv_tile_load<TY, TZ, PER>(in, gr, range.first, tx_n, ty_n, buf);
     for (int t = range.first; t < range.hi; t += range.stride) {
-        const int X0 = (t % tx_n) * T::X, Y0 = ((t / tx_n) % ty_n) * T::Y, Z0 = (t / (tx_n * ty_n)) * T::Z;
+        const TileOrigin o = conv_origin<TY, TZ>(t, tx_n, ty_n);
         __syncthreads();  // the previous tile's reads are done
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
@@ -151,48 +177,45 @@ __global__ void __launch_bounds__(256) k_conv(const uint16_t* __restrict__ in, G
             if (e < NCH) tile[e] = buf[k];
         }
         __syncthreads();
-        if (t + range.stride < range.hi) conv_tile_load<TY, TZ, CH16, PER>(in, gr, t + range.stride, tx_n, ty_n, buf);
+        if (t + range.stride < range.hi) conv_tile_load<TY, TZ, PER>(in, gr, t + range.stride, tx_n, ty_n, buf);
 
-        for (int row = wave; row < T::ROWS; row += 4) {
+#pragma unroll 1
+        for (int q = 0; q < T::ROWS / (4 * R); ++q) {
+            const int row = wave * (T::ROWS / 4) + q * R;  // the first of R rows
             const int ly = row % T::Y, lz = row / T::Y;
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            const uint4* src = tile + 2 * T::HX * (ly + T::HY * lz);
+            f32x4 acc[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int s = 0; s < KSTEPS; ++s) {
-                int tap, chunk;
-                if (CIN == 16) {
-                    tap = 2 * s + (g >> 1);
-                    chunk = g & 1;
-                } else {
-                    tap = 4 * s + g;
-                    chunk = 0;
-                }
-                if (tap > 26) tap = 26;  // the zero-weight padding tap reads a valid address
-                int dx, dy, dz;
-                tap_delta(tap, dx, dy, dz);
-                const int hv = (m + dx + 1) + T::HX * ((ly + dy + 1) + T::HY * (lz + dz + 1));
-                const uint4 bv = tile[hv * CH16 + chunk];
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[s], __builtin_bit_cast(bf16x8, bv), acc, 0, 0, 0);
+                const uint4* b = src + off[s];
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        wa[s], __builtin_bit_cast(bf16x8, b[2 * T::HX * r]), acc[r], 0, 0, 0);
             }
-            const int x = X0 + m, y = Y0 + ly, z = Z0 + lz;
-            if (x >= gr.nx || y >= gr.ny || z >= gr.nz) continue;
-            const long vid = x + static_cast<long>(gr.nx) * y + static_cast<long>(gr.nxy) * z;
-            if constexpr (MODE == kConvFinal) {
-                if (g == 0) out1[vid] = acc[0] + bias[0];
-            } else {
-                uint16_t o[4];
+            const int x = o.X0 + m, z = o.Z0 + lz;
+            if (x >= gr.nx || z >= gr.nz) continue;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int y = o.Y0 + ly + r;
+                if (y >= gr.ny) break;
+                const long vid = x + static_cast<long>(gr.nx) * y + static_cast<long>(gr.nxy) * z;
+                uint16_t ov[4];
                 if constexpr (MODE == kConvHidden) {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) o[i] = bf16_bits(fmaxf(acc[i] + bias[i], 0.0f));
+                    for (int i = 0; i < 4; ++i) ov[i] = bf16_bits(fmaxf(acc[r][i] + bias[i], 0.0f));
                 } else {
                     const uint2 mk = reinterpret_cast<const uint2*>(mask)[vid * 4 + g];
                     const uint16_t mv[4] = {static_cast<uint16_t>(mk.x & 0xFFFFu), static_cast<uint16_t>(mk.x >> 16),
                                             static_cast<uint16_t>(mk.y & 0xFFFFu), static_cast<uint16_t>(mk.y >> 16)};
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) o[i] = bf16_float(mv[i]) > 0.0f ? bf16_bits(acc[i]) : 0;
+                    for (int i = 0; i < 4; ++i) ov[i] = bf16_float(mv[i]) > 0.0f ? bf16_bits(acc[r][i]) : 0;
                 }
                 uint2 pk;
-                pk.x = static_cast<unsigned>(o[0]) | (static_cast<unsigned>(o[1]) << 16);
-                pk.y = static_cast<unsigned>(o[2]) | (static_cast<unsigned>(o[3]) << 16);
+                pk.x = static_cast<unsigned>(ov[0]) | (static_cast<unsigned>(ov[1]) << 16);
+                pk.y = static_cast<unsigned>(ov[2]) | (static_cast<unsigned>(ov[3]) << 16);
                 reinterpret_cast<uint2*>(out16)[vid * 4 + g] = pk;
             }
         }
@@ -203,170 +226,229 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // The output layer (16 -> 1 channels) with packed BF16 dot products on the
 // VALU (v_dot2 accumulates two products into an FP32 sum): on the 16x16 MFMA
-// tile it would use one of 16 output rows.  Same tile and halo staging as
-// k_conv; a thread computes OPT x-consecutive outputs of one row, reading the
-// OPT + 2 input columns of each (dy, dz) once.
+// tile it would use one of 16 output rows.  A thread computes OPT
+// y-consecutive outputs of one x, so the 16 lanes of a row read 16
+// consecutive vertices; the two chunks of a vertex lie in two LDS arrays,
+// which makes such a read contiguous (threads that owned x-consecutive
+// outputs read 128 bytes apart, and bank conflicts bound the kernel:
+// 256^3 took 713 us and takes 285).  An output adds its taps in increasing order.
 template <int TY, int TZ>
 __global__ void __launch_bounds__(256) k_conv_out(const uint16_t* __restrict__ in, Grid gr,
                                                   const float* __restrict__ W2, const float* __restrict__ b2,
                                                   float* __restrict__ out1) {
     using T = ConvTile<TY, TZ>;
-    constexpr int CH16 = 2;
     constexpr int OPT = 16 * T::ROWS / 256;  // outputs per thread: 4 for 8 x 8 rows, 2 for 32 x 1
-    constexpr int GX = 16 / OPT;             // threads per row
-    static_assert(OPT * 256 == 16 * T::ROWS, "every output has one thread");
-    __shared__ uint4 tile[T::HALO * CH16];
-    __shared__ unsigned wpk[27 * 8];  // BF16 weight pairs (channels 2p, 2p + 1) of every tap
-    for (int e = threadIdx.x; e < 27 * 8; e += 256) {
-        const int tap = e / 8, q = e % 8;
-        wpk[e] = static_cast<unsigned>(bf16_bits(W2[tap * 16 + 2 * q])) |
-                 (static_cast<unsigned>(bf16_bits(W2[tap * 16 + 2 * q + 1])) << 16);
-    }
+    static_assert(OPT * 256 == 16 * T::ROWS && T::Y % OPT == 0, "every output has one thread");
+    __shared__ uint4 tile[2][T::HALO];
+    __shared__ uint4 wq[27 * 2];  // BF16 weights of every tap, channels 0..7 and 8..15
+    for (int e = threadIdx.x; e < 27 * 8; e += 256)
+        reinterpret_cast<unsigned*>(wq)[e] = static_cast<unsigned>(bf16_bits(W2[2 * e])) |
+                                             (static_cast<unsigned>(bf16_bits(W2[2 * e + 1])) << 16);
     const float bias = b2[0];
-    const int xg = threadIdx.x % GX, row = threadIdx.x / GX;
-    const int ly = row % T::Y, lz = row / T::Y;
+    const int lx = threadIdx.x & 15, ly = OPT * ((threadIdx.x >> 4) % (T::Y / OPT)),
+              lz = (threadIdx.x >> 4) / (T::Y / OPT);
 
     const int tx_n = (gr.nx + T::X - 1) / T::X, ty_n = (gr.ny + T::Y - 1) / T::Y, tz_n = (gr.nz + T::Z - 1) / T::Z;
     const ItemRange range = xcd_items(tx_n * ty_n * tz_n);
-    constexpr int NCH = T::HALO * CH16;
+    constexpr int NCH = T::HALO * 2;
     constexpr int PER = (NCH + 255) / 256;
     uint4 buf[PER];
-    if (range.first < range.hi) conv_tile_load<TY, TZ, CH16, PER>(in, gr, range.first, tx_n, ty_n, buf);
+    if (range.first < range.hi) conv_tile_load<TY, TZ, PER>(in, gr, range.first, tx_n, ty_n, buf);
     for (int t = range.first; t < range.hi; t += range.stride) {
-        const int X0 = (t % tx_n) * T::X, Y0 = ((t / tx_n) % ty_n) * T::Y, Z0 = (t / (tx_n * ty_n)) * T::Z;
+        const TileOrigin o = conv_origin<TY, TZ>(t, tx_n, ty_n);
         __syncthreads();  // the previous tile's reads (and the weight packing) are done
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             const int e = threadIdx.x + 256 * k;
-            if (e < NCH) tile[e] = buf[k];
+            if (e < NCH) tile[e & 1][e >> 1] = buf[k];
         }
         __syncthreads();
-        if (t + range.stride < range.hi) conv_tile_load<TY, TZ, CH16, PER>(in, gr, t + range.stride, tx_n, ty_n, buf);
+        if (t + range.stride < range.hi) conv_tile_load<TY, TZ, PER>(in, gr, t + range.stride, tx_n, ty_n, buf);
         float acc[OPT];
 #pragma unroll
         for (int i = 0; i < OPT; ++i) acc[i] = bias;
-        // one (dy, dz) row group at a time keeps OPT + 2 columns live
 #pragma unroll 1
-        for (int dz = -1; dz <= 1; ++dz)
-#pragma unroll 1
-            for (int dy = -1; dy <= 1; ++dy) {
-                unsigned col[OPT + 2][8];
+        for (int dz = 0; dz < 3; ++dz) {
+            unsigned w[9][8];  // the plane's nine taps
 #pragma unroll
-                for (int c = 0; c < OPT + 2; ++c) {
-                    const int hv = (xg * OPT + c) + T::HX * ((ly + dy + 1) + T::HY * (lz + dz + 1));
-                    const uint4 u0 = tile[hv * CH16], u1 = tile[hv * CH16 + 1];
-                    col[c][0] = u0.x, col[c][1] = u0.y, col[c][2] = u0.z, col[c][3] = u0.w;
-                    col[c][4] = u1.x, col[c][5] = u1.y, col[c][6] = u1.z, col[c][7] = u1.w;
-                }
+            for (int k = 0; k < 9; ++k) {
+                const uint4 a = wq[18 * dz + 2 * k], b = wq[18 * dz + 2 * k + 1];
+                w[k][0] = a.x, w[k][1] = a.y, w[k][2] = a.z, w[k][3] = a.w;
+                w[k][4] = b.x, w[k][5] = b.y, w[k][6] = b.z, w[k][7] = b.w;
+            }
+            // input row r is the row dy = r - i (0..2) of output i
 #pragma unroll
-                for (int dx = -1; dx <= 1; ++dx) {
-                    const int tap = (dz + 1) * 9 + (dy + 1) * 3 + (dx + 1);
-                    unsigned w[8];
+            for (int r = 0; r < OPT + 2; ++r)
 #pragma unroll
-                    for (int q = 0; q < 8; ++q) w[q] = wpk[tap * 8 + q];
+                for (int dx = 0; dx < 3; ++dx) {
+                    const int hv = lx + dx + T::HX * (ly + r + T::HY * (lz + dz));
+                    const uint4 u0 = tile[0][hv], u1 = tile[1][hv];
+                    const unsigned col[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
 #pragma unroll
-                    for (int i = 0; i < OPT; ++i)
+                    for (int i = 0; i < OPT; ++i) {
+                        const int dy = r - i;
+                        if (dy < 0 || dy > 2) continue;
 #pragma unroll
                         for (int q = 0; q < 8; ++q)
-                            acc[i] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, col[i + dx + 1][q]),
-                                                                     __builtin_bit_cast(bf16x2, w[q]), acc[i], false);
+                            acc[i] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, col[q]),
+                                                                     __builtin_bit_cast(bf16x2, w[3 * dy + dx][q]),
+                                                                     acc[i], false);
+                    }
                 }
-            }
-        const int y = Y0 + ly, z = Z0 + lz;
-        if (y < gr.ny && z < gr.nz) {
+        }
+        const int x = o.X0 + lx, z = o.Z0 + lz;
+        if (x < gr.nx && z < gr.nz) {
 #pragma unroll
             for (int i = 0; i < OPT; ++i) {
-                const int x = X0 + xg * OPT + i;
-                if (x < gr.nx) out1[x + static_cast<long>(gr.nx) * y + static_cast<long>(gr.nxy) * z] = acc[i];
+                const int y = o.Y0 + ly + i;
+                if (y < gr.ny) out1[x + static_cast<long>(gr.nx) * y + static_cast<long>(gr.nxy) * z] = acc[i];
             }
         }
     }
 }
 
-// Weight gradient of one layer, one partial sum per tile:
-//   part[tile][tap][ci][co] = sum over the tile's vertices v of in[v + tap][ci] * dz[v][co]
-//   part_b[tile][co]        = sum over the tile's vertices v of dz[v][co]
-// M = 16 input channels, N = 16 output channels, K = 32 vertices per MFMA.
-template <int CIN, int TY, int TZ>
-__global__ void __launch_bounds__(256) k_conv_dw(const uint16_t* __restrict__ in, const uint16_t* __restrict__ dz,
-                                                 Grid gr, float* __restrict__ part, float* __restrict__ part_b) {
+// Weight gradient of one layer, one partial sum per block:
+//   part[block][tap][ci][co]     = sum over the block's vertices v of in[v + tap][ci] * dz[v][co]
+//   part[block][27 * 256 + co]   = sum over the block's vertices v of dz[v][co]
+// M = 16 input channels, N = 16 output channels, K = 32 vertices (two rows of
+// 16) per MFMA.  Both operands need eight vertices of one channel per lane,
+// while a vertex's channels are contiguous: ds_read_b64_tr_b16 hands each of
+// 16 lanes its channel of four consecutive vertices (128 contiguous bytes),
+// for any tap at a constant offset from the lane's address, so the inner loop
+// is two LDS reads and one MFMA per tap.  A wave keeps the sums of all 27
+// taps (and of dz, against a row of ones) in registers over all tiles of its
+// block; the waves' sums are added at the end.  Bound by the LDS reads (8
+// cycles of the compute unit per MFMA) and the staging of the tiles:
+// 128^3 takes 61 us where one pass per tap with 2-byte reads took 464.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+constexpr int kDwSums = 27 * 256 + 16;  // sums of one partial
+constexpr int kDwBlocks = 768;          // three per compute unit (51 KB of LDS each)
+
+// Eight vertices of the lane's channel: the four at p (a group of 16 lanes
+// passes 128 contiguous bytes, 8 per lane) and the four after them.
+__device__ __forceinline__ bf16x8 read_vertices8(const uint16_t* p) {
+    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 64));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+template <int TY, int TZ>
+__global__ void __launch_bounds__(256, 3) k_conv_dw(const uint16_t* __restrict__ in, const uint16_t* __restrict__ dz,
+                                                 Grid gr, float* __restrict__ part) {
     using T = ConvTile<TY, TZ>;
     constexpr int NV = T::X * T::ROWS;
-    __shared__ uint16_t sin[T::HALO * CIN];
-    __shared__ uint16_t sdz[NV * kNetC];
+    static_assert(T::Y % 2 == 0 && T::ROWS % 8 == 0, "row pairs split evenly over four waves");
+    union Smem {
+        uint4 stage[T::HALO * 2 + NV * 2];
+        float sums[kDwSums];
+    };
+    __shared__ Smem sm;
+    uint4* sin = sm.stage;
+    uint4* sdz = sm.stage + T::HALO * 2;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m = lane & 15, g = lane >> 4;
-    const int tx_n = (gr.nx + T::X - 1) / T::X, ty_n = (gr.ny + T::Y - 1) / T::Y;
-    const int tile = blockIdx.x;
-    const int X0 = (tile % tx_n) * T::X, Y0 = ((tile / tx_n) % ty_n) * T::Y, Z0 = (tile / (tx_n * ty_n)) * T::Z;
-    constexpr int CH16 = CIN * 2 / 16;
-    for (int e = threadIdx.x; e < T::HALO * CH16; e += 256) {
-        const int hv = e / CH16, ch = e - hv * CH16;
-        const int hx = hv % T::HX, hy = (hv / T::HX) % T::HY, hz = hv / (T::HX * T::HY);
-        const int x = X0 + hx - 1, y = Y0 + hy - 1, z = Z0 + hz - 1;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (x >= 0 && x < gr.nx && y >= 0 && y < gr.ny && z >= 0 && z < gr.nz)
-            v = reinterpret_cast<const uint4*>(in)[(x + static_cast<long>(gr.nx) * y + static_cast<long>(gr.nxy) * z) * CH16 + ch];
-        reinterpret_cast<uint4*>(sin)[e] = v;
+    const int tx_n = (gr.nx + T::X - 1) / T::X, ty_n = (gr.ny + T::Y - 1) / T::Y, tz_n = (gr.nz + T::Z - 1) / T::Z;
+    const ItemRange range = xcd_items(tx_n * ty_n * tz_n);
+    f32x4 acc[27], acc_b = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int tap = 0; tap < 27; ++tap) acc[tap] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 ones;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) ones[j] = static_cast<__bf16>(1.0f);
+    for (int t = range.first; t < range.hi; t += range.stride) {
+        const TileOrigin o = conv_origin<TY, TZ>(t, tx_n, ty_n);
+        __syncthreads();  // the previous tile's reads are done
+        // in two batches of loads (the sums leave few registers)
+        constexpr int NCH = T::HALO * 2, PER = (NCH + 255) / 256, HALF = (PER + 1) / 2;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            uint4 buf[HALF];
+#pragma unroll
+            for (int k = 0; k < HALF; ++k)
+                if (h * HALF + k < PER)
+                    buf[k] = conv_chunk<TY, TZ>(in, gr, o, min(static_cast<int>(threadIdx.x) + 256 * (h * HALF + k), NCH - 1));
+#pragma unroll
+            for (int k = 0; k < HALF; ++k) {
+                const int e = threadIdx.x + 256 * (h * HALF + k);
+                if (h * HALF + k < PER && e < NCH) sin[e] = buf[k];
+            }
+        }
+        uint4 db[NV * 2 / 256];
+#pragma unroll
+        for (int k = 0; k < NV * 2 / 256; ++k) {
+            const int e = threadIdx.x + 256 * k, lv = e >> 1, r = lv / T::X;
+            const int x = o.X0 + lv % T::X, y = o.Y0 + r % T::Y, z = o.Z0 + r / T::Y;
+            const bool ok = x < gr.nx && y < gr.ny && z < gr.nz;  // the others contribute nothing
+            const uint4 v = reinterpret_cast<const uint4*>(
+                dz)[ok ? 2 * (x + static_cast<long>(gr.nx) * y + static_cast<long>(gr.nxy) * z) + (e & 1) : 0];
+            db[k] = make_uint4(ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u);
+        }
+#pragma unroll
+        for (int k = 0; k < NV * 2 / 256; ++k) sdz[threadIdx.x + 256 * k] = db[k];
+        __syncthreads();
+#pragma unroll 1
+        for (int q = wave; q < T::ROWS / 2; q += 4) {
+            // lanes 16 g ..: vertices 8 (g & 1) .. + 7 of row 2 q + (g >> 1)
+            const int row = 2 * q + (g >> 1), x = 8 * (g & 1), ly = row % T::Y, lz = row / T::Y;
+            const uint16_t* pd = reinterpret_cast<const uint16_t*>(sdz) + 16 * (x + T::X * row) + 4 * m;
+            // the lane's vertices displaced by tap (-1, -1, -1)
+            const uint16_t* pi = reinterpret_cast<const uint16_t*>(sin) + 16 * (x + T::HX * (ly + T::HY * lz)) + 4 * m;
+            const bf16x8 b = read_vertices8(pd);
+#pragma unroll
+            for (int tap = 0; tap < 27; ++tap) {
+                int dx, dy, dzz;
+                tap_delta(tap, dx, dy, dzz);
+                const bf16x8 a = read_vertices8(pi + 16 * ((dx + 1) + T::HX * ((dy + 1) + T::HY * (dzz + 1))));
+                acc[tap] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[tap], 0, 0, 0);
+            }
+            acc_b = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, b, acc_b, 0, 0, 0);
+        }
     }
-    for (int e = threadIdx.x; e < NV * 2; e += 256) {
-        const int lv = e >> 1, ch = e & 1;
-        const int x = X0 + lv % T::X, r = lv / T::X, y = Y0 + r % T::Y, z = Z0 + r / T::Y;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);  // vertices outside the grid contribute nothing
-        if (x < gr.nx && y < gr.ny && z < gr.nz)
-            v = reinterpret_cast<const uint4*>(dz)[(x + static_cast<long>(gr.nx) * y + static_cast<long>(gr.nxy) * z) * 2 + ch];
-        reinterpret_cast<uint4*>(sdz)[e] = v;
+    // acc[tap][i] = D[ci = 4g + i][co = m]; the waves in turn
+    for (int w = 0; w < 4; ++w) {
+        __syncthreads();
+        if (wave != w) continue;
+#pragma unroll
+        for (int tap = 0; tap < 27; ++tap)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float* d = sm.sums + tap * 256 + (4 * g + i) * 16 + m;
+                *d = w == 0 ? acc[tap][i] : *d + acc[tap][i];
+            }
+        if (g == 0) {  // every row of acc_b is the sum of dz
+            float* d = sm.sums + 27 * 256 + m;
+            *d = w == 0 ? acc_b[0] : *d + acc_b[0];
+        }
     }
     __syncthreads();
-    for (int tap = wave; tap < 27; tap += 4) {
-        int dx, dy, dzz;
-        tap_delta(tap, dx, dy, dzz);
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        for (int ks = 0; ks < NV / 32; ++ks) {
-            bf16x8 a, b;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int lv = 32 * ks + 8 * g + j;  // output vertex of the tile
-                const int lx = lv % T::X, r = lv / T::X, ly = r % T::Y, lz = r / T::Y;
-                const int hv = (lx + dx + 1) + T::HX * ((ly + dy + 1) + T::HY * (lz + dzz + 1));
-                a[j] = m < CIN ? __builtin_bit_cast(__bf16, sin[hv * CIN + (m < CIN ? m : 0)]) : static_cast<__bf16>(0.0f);
-                b[j] = __builtin_bit_cast(__bf16, sdz[lv * kNetC + m]);
-            }
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
-        }
-        // acc[i] = D[ci = 4g + i][co = m]
-        float* dst = part + (static_cast<long>(tile) * 27 + tap) * 16 * 16;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) dst[(4 * g + i) * 16 + m] = acc[i];
-    }
-    if (threadIdx.x < 16) {
-        float sb = 0.0f;
-        for (int lv = 0; lv < NV; ++lv) sb += bf16_float(sdz[lv * kNetC + threadIdx.x]);
-        part_b[static_cast<long>(tile) * 16 + threadIdx.x] = sb;
-    }
+    for (int e = threadIdx.x; e < kDwSums; e += 256) part[static_cast<long>(blockIdx.x) * kDwSums + e] = sm.sums[e];
 }
 
-// Sums the per-tile partials into the gradient of one layer's weights and bias,
-// in the parameter layout (out channels beyond n_out and in channels beyond
-// n_in are dropped).
-__global__ void __launch_bounds__(256) k_reduce_dw(const float* __restrict__ part, const float* __restrict__ part_b,
-                                                   int ntiles, int n_in, int n_out, int s_in, float* __restrict__ gW,
-                                                   float* __restrict__ gb) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < 27 * 16 * 16) {
-        const int tap = e / 256, ci = (e / 16) % 16, co = e % 16;
-        if (ci < n_in && co < n_out) {
-            float s = 0.0f;
-            for (int t = 0; t < ntiles; ++t) s += part[static_cast<long>(t) * 27 * 256 + e];
-            gW[tap * n_in * s_in + ci * s_in + co] = s;
-        }
-    } else if (e < 27 * 256 + 16) {
-        const int co = e - 27 * 256;
-        if (co < n_out) {
-            float s = 0.0f;
-            for (int t = 0; t < ntiles; ++t) s += part_b[static_cast<long>(t) * 16 + co];
-            gb[co] = s;
-        }
+// Sums the blocks' partials into the gradient of one layer's weights and bias,
+// in the parameter layout (out channels beyond n_out are dropped).  A block
+// sums 64 entries: its 16 waves take every 16th partial each, so that one
+// entry is not a serial chain of loads over all partials (6 us for 768
+// partials; one thread per entry over 2048 partials took 480).
+__global__ void __launch_bounds__(1024) k_reduce_dw(const float* __restrict__ part, int nparts, int n_out,
+                                                    float* __restrict__ gW, float* __restrict__ gb) {
+    __shared__ float red[16][64];
+    const int lane = threadIdx.x & 63, seg = threadIdx.x >> 6, e = blockIdx.x * 64 + lane;
+    float s = 0.0f;
+    if (e < kDwSums) {
+#pragma unroll 8
+        for (int b = seg; b < nparts; b += 16) s += part[static_cast<long>(b) * kDwSums + e];
+    }
+    red[seg][lane] = s;
+    __syncthreads();
+    if (seg != 0 || e >= kDwSums) return;
+    for (int k = 1; k < 16; ++k) s += red[k][lane];
+    if (e < 27 * 256) {
+        const int co = e % 16;
+        if (co < n_out) gW[(e / 16) * n_out + co] = s;
+    } else if (e - 27 * 256 < n_out) {
+        gb[e - 27 * 256] = s;
     }
 }
 
@@ -567,34 +649,43 @@ __global__ void __launch_bounds__(256) k_halvings(const float* __restrict__ L, c
 // ------------------------------------------------------------- launchers ---
 
 constexpr int kConvBlocks = 2048;
+// Blocks of the convolutions: as many as run at once (two per compute unit by
+// LDS), each walking its tiles, so that a block loads its weights once.
+constexpr int kTileBlocks = 512;
 
-template <int CIN, int MODE>
+static int tiles_of(const Grid& gr, int ty, int tz) {
+    return ((gr.nx + 15) / 16) * ((gr.ny + ty - 1) / ty) * ((gr.nz + tz - 1) / tz);
+}
+
+template <int MODE>
 static void launch_conv_t(const uint16_t* in, const Grid& gr, const WeightView& wv, const uint16_t* mask,
-                          uint16_t* out16, float* out1, hipStream_t s) {
+                          uint16_t* out16, hipStream_t s) {
     if (gr.nz == 1) {
-        using T = ConvTile<32, 1>;
-        const int nt = ((gr.nx + 15) / 16) * ((gr.ny + T::Y - 1) / T::Y) * gr.nz;
-        hipLaunchKernelGGL((k_conv<CIN, 32, 1, MODE>), dim3(nt < kConvBlocks ? nt : kConvBlocks), dim3(256), 0, s, in, gr, wv,
-                           mask, out16, out1);
+        const int nt = tiles_of(gr, 32, 1);
+        hipLaunchKernelGGL((k_conv<32, 1, MODE>), dim3(nt < kTileBlocks ? nt : kTileBlocks), dim3(256), 0, s, in, gr, wv,
+                           mask, out16);
     } else {
-        using T = ConvTile<8, 8>;
-        const int nt = ((gr.nx + 15) / 16) * ((gr.ny + T::Y - 1) / T::Y) * ((gr.nz + T::Z - 1) / T::Z);
-        hipLaunchKernelGGL((k_conv<CIN, 8, 8, MODE>), dim3(nt < kConvBlocks ? nt : kConvBlocks), dim3(256), 0, s, in, gr, wv,
-                           mask, out16, out1);
+        const int nt = tiles_of(gr, 8, 8);
+        hipLaunchKernelGGL((k_conv<8, 8, MODE>), dim3(nt < kTileBlocks ? nt : kTileBlocks), dim3(256), 0, s, in, gr, wv,
+                           mask, out16);
     }
 }
 
-static int conv_tiles(const Grid& gr) {
-    if (gr.nz == 1) return ((gr.nx + 15) / 16) * ((gr.ny + 31) / 32);
-    return ((gr.nx + 15) / 16) * ((gr.ny + 7) / 8) * ((gr.nz + 7) / 8);
+// Blocks (and partial sums) of a weight gradient: tiles of 16 x 8 x 4 vertices
+// (2D: 16 x 16), so that three blocks' tiles with their halos share a
+// compute unit's LDS and one block stages while another computes.
+static int dw_blocks(const Grid& gr) {
+    const int nt = gr.nz == 1 ? tiles_of(gr, 16, 1) : tiles_of(gr, 8, 4);
+    return nt < kDwBlocks ? nt : kDwBlocks;
 }
 
-template <int CIN>
-static void launch_dw_t(const uint16_t* in, const uint16_t* dz, const Grid& gr, float* part, float* part_b,
-                        hipStream_t s) {
-    const int nt = conv_tiles(gr);
-    if (gr.nz == 1) hipLaunchKernelGGL((k_conv_dw<CIN, 32, 1>), dim3(nt), dim3(256), 0, s, in, dz, gr, part, part_b);
-    else hipLaunchKernelGGL((k_conv_dw<CIN, 8, 8>), dim3(nt), dim3(256), 0, s, in, dz, gr, part, part_b);
+// The gradient of one layer's weights (n_out output channels stored) and bias.
+static void launch_dw(const uint16_t* in, const uint16_t* dz, const Grid& gr, float* part, int n_out, float* gW,
+                      float* gb, hipStream_t s) {
+    const int nb = dw_blocks(gr);
+    if (gr.nz == 1) hipLaunchKernelGGL((k_conv_dw<16, 1>), dim3(nb), dim3(256), 0, s, in, dz, gr, part);
+    else hipLaunchKernelGGL((k_conv_dw<8, 4>), dim3(nb), dim3(256), 0, s, in, dz, gr, part);
+    hipLaunchKernelGGL(k_reduce_dw, dim3((kDwSums + 63) / 64), dim3(1024), 0, s, part, nb, n_out, gW, gb);
 }
 
 }  // namespace msz
@@ -609,14 +700,11 @@ bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // Net workspace of one field.
 struct NetLayout {
-    size_t dirs_f, dirs_h, feat, a1, a2, p, dz_a, dz_b, part, part_b, minmax, L, g0, total;
+    size_t dirs_f, dirs_h, feat, a1, a2, p, dz_a, dz_b, part, minmax, L, g0, total;
 };
-
-int conv_tile_count(const Grid& gr) { return conv_tiles(gr); }
 
 NetLayout net_layout(const Grid& gr) {
     const size_t n = static_cast<size_t>(gr.n);
-    const size_t nt = static_cast<size_t>(conv_tile_count(gr));
     NetLayout l{};
     size_t o = 0;
     auto take = [&](size_t b) {
@@ -632,8 +720,7 @@ NetLayout net_layout(const Grid& gr) {
     l.p = take(n * 4);
     l.dz_a = take(n * 32);
     l.dz_b = take(n * 32);
-    l.part = take(nt * 27 * 256 * 4);
-    l.part_b = take(nt * 16 * 4);
+    l.part = take(static_cast<size_t>(dw_blocks(gr)) * kDwSums * 4);
     l.minmax = take(kConvBlocks * 2 * 4);
     l.L = take(n * 4);
     l.g0 = take(n * 4);
@@ -680,17 +767,15 @@ WeightView layer_back_view(const float* P, int layer) {
 
 void net_forward(const float* P, const uint16_t* feat, const Grid& gr, uint16_t* a1, uint16_t* a2, float* p,
                  hipStream_t s) {
-    launch_conv_t<16, kConvHidden>(feat, gr, layer_view(P, 0), nullptr, a1, nullptr, s);
-    launch_conv_t<16, kConvHidden>(a1, gr, layer_view(P, 1), nullptr, a2, nullptr, s);
+    launch_conv_t<kConvHidden>(feat, gr, layer_view(P, 0), nullptr, a1, s);
+    launch_conv_t<kConvHidden>(a1, gr, layer_view(P, 1), nullptr, a2, s);
     if (gr.nz == 1) {
-        using T = ConvTile<32, 1>;
-        const int nt = ((gr.nx + 15) / 16) * ((gr.ny + T::Y - 1) / T::Y);
-        hipLaunchKernelGGL((k_conv_out<32, 1>), dim3(nt < kConvBlocks ? nt : kConvBlocks), dim3(256), 0, s, a2, gr,
+        const int nt = tiles_of(gr, 32, 1);
+        hipLaunchKernelGGL((k_conv_out<32, 1>), dim3(nt < kTileBlocks ? nt : kTileBlocks), dim3(256), 0, s, a2, gr,
                            P + kOffW2, P + kOffB2, p);
     } else {
-        using T = ConvTile<8, 8>;
-        const int nt = ((gr.nx + 15) / 16) * ((gr.ny + T::Y - 1) / T::Y) * ((gr.nz + T::Z - 1) / T::Z);
-        hipLaunchKernelGGL((k_conv_out<8, 8>), dim3(nt < kConvBlocks ? nt : kConvBlocks), dim3(256), 0, s, a2, gr,
+        const int nt = tiles_of(gr, 8, 8);
+        hipLaunchKernelGGL((k_conv_out<8, 8>), dim3(nt < kTileBlocks ? nt : kTileBlocks), dim3(256), 0, s, a2, gr,
                            P + kOffW2, P + kOffB2, p);
     }
 }
@@ -824,27 +909,18 @@ int msz_net_gradients(const float* params, const uint16_t* feat, const float* ta
     uint16_t* dza = reinterpret_cast<uint16_t*>(w + l.dz_a);
     uint16_t* dzb = reinterpret_cast<uint16_t*>(w + l.dz_b);
     float* part = reinterpret_cast<float*>(w + l.part);
-    float* part_b = reinterpret_cast<float*>(w + l.part_b);
     float* lp = reinterpret_cast<float*>(w + l.minmax);
-    const int nt = conv_tile_count(gr);
     net_forward(params, feat, gr, a1, a2, p, s);
     const int nb = blocks_n(gr.n);
     hipLaunchKernelGGL(k_mse, dim3(nb), dim3(256), 0, s, p, target, gr.n, edit_weight, dza, lp);
-    const int rb = (27 * 256 + 16 + 255) / 256;
     // layer 2
-    launch_dw_t<16>(a2, dza, gr, part, part_b, s);
-    hipLaunchKernelGGL(k_reduce_dw, dim3(rb), dim3(256), 0, s, part, part_b, nt, 16, 1, 1, grad_out + kOffW2,
-                       grad_out + kOffB2);
-    launch_conv_t<16, kConvBackData>(dza, gr, layer_back_view(params, 2), a2, dzb, nullptr, s);
+    launch_dw(a2, dza, gr, part, 1, grad_out + kOffW2, grad_out + kOffB2, s);
+    launch_conv_t<kConvBackData>(dza, gr, layer_back_view(params, 2), a2, dzb, s);
     // layer 1
-    launch_dw_t<16>(a1, dzb, gr, part, part_b, s);
-    hipLaunchKernelGGL(k_reduce_dw, dim3(rb), dim3(256), 0, s, part, part_b, nt, 16, 16, 16, grad_out + kOffW1,
-                       grad_out + kOffB1);
-    launch_conv_t<16, kConvBackData>(dzb, gr, layer_back_view(params, 1), a1, dza, nullptr, s);
+    launch_dw(a1, dzb, gr, part, 16, grad_out + kOffW1, grad_out + kOffB1, s);
+    launch_conv_t<kConvBackData>(dzb, gr, layer_back_view(params, 1), a1, dza, s);
     // layer 0
-    launch_dw_t<16>(feat, dza, gr, part, part_b, s);
-    hipLaunchKernelGGL(k_reduce_dw, dim3(rb), dim3(256), 0, s, part, part_b, nt, 16, 16, 16, grad_out + kOffW0,
-                       grad_out + kOffB0);
+    launch_dw(feat, dza, gr, part, 16, grad_out + kOffW0, grad_out + kOffB0, s);
     if (hipGetLastError() != hipSuccess) return MSZ_EDEVICE;
     std::vector<float> host(nb);
     if (hipMemcpyAsync(host.data(), lp, nb * sizeof(float), hipMemcpyDeviceToHost, s) != hipSuccess ||
