@@ -462,104 +462,160 @@ __global__ void __launch_bounds__(1024) k_reduce_dw(const float* __restrict__ pa
 //   11 up_fhat(u) = i for a neighbour u with up_fhat(u) != up_f(u)
 // Channels 8..11 gather over the neighbour slots: neighbour j = i + off[s]
 // points back at i through the opposite slot s ^ 1.
-// One thread per (x, y) column walks z, keeping the 3x3 in-plane sums of f
-// and fhat and the 3x3 direction bytes of planes z - 1, z, z + 1, so every
-// plane is read once per column (36 loads per vertex instead of 82).  A
-// direction byte of 0 stands for "outside the grid": no in-grid vertex has
-// its ascent and its descent in the same slot 0.
-struct PlaneBox {
-    double sf, sh;         // sums over the in-grid part of the 3x3 block
-    int cnt;               // its in-grid vertices
-    unsigned wf[3], wh[3];  // row dy + 1: direction bytes of dx = -1, 0, 1 in bytes 0..2
-    __device__ __forceinline__ unsigned df(int dx, int dy) const { return (wf[dy + 1] >> (8 * (dx + 1))) & 0xFFu; }
-    __device__ __forceinline__ unsigned dh(int dx, int dy) const { return (wh[dy + 1] >> (8 * (dx + 1))) & 0xFFu; }
-};
+//
+// A block owns 32 x 8 columns and walks kFeatZ planes of z.  Each plane, with
+// a one-vertex halo, is staged in LDS once: (f, fhat) and the target masks of
+// every vertex, both zero outside the grid (a zero adds nothing to a box sum
+// and targets nothing).  A thread reads its 3 x 3 neighbourhood and carries
+// what the planes above and below need of it in registers: the box sums of
+// planes z - 1 and z, and the target bits it hands to each side.  Quotients
+// by the box count and by xi use a reciprocal, one residual and one
+// correction (correctly rounded, as the division is: the reciprocals are
+// correctly rounded and no divisor's significand is all ones).
+// Moves 42 bytes per vertex: 213 us for 256^3 (3.3 TB/s), where one thread
+// per column, loading its 36 values per vertex itself, took 788.
+constexpr int kFeatX = 32, kFeatY = 8, kFeatZ = 16, kFeatHX = kFeatX + 2, kFeatHY = kFeatY + 2;
 
-__device__ __forceinline__ PlaneBox load_plane_box(const float* __restrict__ f, const float* __restrict__ fhat,
-                                                   const uint8_t* __restrict__ dirs_f,
-                                                   const uint8_t* __restrict__ dirs_h, const Grid& gr, int x, int y,
-                                                   int z) {
-    PlaneBox P;
-    P.sf = 0.0;
-    P.sh = 0.0;
-    P.cnt = 0;
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        P.wf[r] = 0u;
-        P.wh[r] = 0u;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const int xx = x + q - 1, yy = y + r - 1;
-            if (z >= 0 && z < gr.nz && xx >= 0 && xx < gr.nx && yy >= 0 && yy < gr.ny) {
-                const long j = xx + static_cast<long>(gr.nx) * yy + static_cast<long>(gr.nxy) * z;
-                P.sf += f[j];
-                P.sh += fhat[j];
-                P.cnt += 1;
-                P.wf[r] |= static_cast<unsigned>(dirs_f[j]) << (8 * q);
-                P.wh[r] |= static_cast<unsigned>(dirs_h[j]) << (8 * q);
-            }
-        }
-    }
-    return P;
+// Target masks of vertex j from its directions in f and fhat: bit d of a is
+// set when j's descents differ and f's is slot d, bit d of b when its ascents
+// differ and fhat's is slot d (bit 15: the self slot); the high halves repeat
+// a where fhat's descent is the self slot and b where f's ascent is.
+struct TargetMask {
+    unsigned a, b;
+};
+__device__ __forceinline__ TargetMask target_mask(unsigned fj, unsigned hj) {
+    const unsigned uf = fj >> 4, nf = fj & 15u, uh = hj >> 4, nh = hj & 15u;
+    const unsigned a = nh != nf ? 1u << nf : 0u, b = uh != uf ? 1u << uh : 0u;
+    return {nh == kSelf ? a | (a << 16) : a, uf == kSelf ? b | (b << 16) : b};
 }
 
-// Channels 8..11 of vertex i from the neighbour j in slot sl (plane Q).
-__device__ __forceinline__ unsigned target_bits(const PlaneBox& Q, int sl, int dx, int dy) {
-    const unsigned back = static_cast<unsigned>(sl ^ 1);
-    const unsigned fj = Q.df(dx, dy), hj = Q.dh(dx, dy);
-    const unsigned ufj = fj >> 4, nfj = fj & 15u, uhj = hj >> 4, nhj = hj & 15u;
-    unsigned tg = 0;
-    if (nhj == kSelf && nfj == back) tg |= 1u;  // FPmin at j targets dn_f(j)
-    if (ufj == kSelf && uhj == back) tg |= 2u;  // FNmax at j targets up_fhat(j)
-    if (nhj != nfj && nfj == back) tg |= 4u;
-    if (uhj != ufj && uhj == back) tg |= 8u;
-    return tg;
+// Bits 0 and 16 of each word: the vertex with mask w, in slot s of the
+// reader, targets the reader.
+__device__ __forceinline__ void add_target(uint2& t, const uint2& w, int s) {
+    t.x |= (w.x >> (s ^ 1)) & 0x00010001u;
+    t.y |= (w.y >> (s ^ 1)) & 0x00010001u;
+}
+
+__device__ __forceinline__ double quotient(double x, double d, double r) {  // x / d, r = 1 / d
+    const double q = __dmul_rn(x, r);
+    return __fma_rn(__fma_rn(-q, d, x), r, q);
 }
 
 __global__ void __launch_bounds__(256) k_features(const float* __restrict__ f, const float* __restrict__ fhat,
                                                   const uint8_t* __restrict__ dirs_f,
                                                   const uint8_t* __restrict__ dirs_h, Grid gr, float xi, float xi_ch,
                                                   uint16_t* __restrict__ feat) {
+    constexpr int NP = kFeatHX * kFeatHY, PER = (NP + 255) / 256;
+    __shared__ float2 sv[2][NP];
+    __shared__ uint2 st[2][NP];
+    const int tx_n = (gr.nx + kFeatX - 1) / kFeatX, ty_n = (gr.ny + kFeatY - 1) / kFeatY;
+    const int t = blockIdx.x;
+    const int X0 = (t % tx_n) * kFeatX, Y0 = ((t / tx_n) % ty_n) * kFeatY, Z0 = (t / (tx_n * ty_n)) * kFeatZ;
+    const int lx = threadIdx.x % kFeatX, ly = threadIdx.x / kFeatX;
+    const int x = X0 + lx, y = Y0 + ly;
+    const bool in_xy = x < gr.nx && y < gr.ny;
+    const int z_end = min(Z0 + kFeatZ, gr.nz);  // planes [Z0, z_end) are written
+    const int n_xy = (1 + (x > 0) + (x + 1 < gr.nx)) * (1 + (y > 0) + (y + 1 < gr.ny));
+    const double xid = xi, rxi = 1.0 / xid;
     const unsigned one = bf16_bits(1.0f);
-    for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < gr.nxy; c += gridDim.x * blockDim.x) {
-        const int x = c % gr.nx, y = c / gr.nx;
-        PlaneBox pm = load_plane_box(f, fhat, dirs_f, dirs_h, gr, x, y, -1);  // plane z - 1
-        PlaneBox p0 = load_plane_box(f, fhat, dirs_f, dirs_h, gr, x, y, 0);   // plane z
-        for (int z = 0; z < gr.nz; ++z) {
-            const PlaneBox pp = load_plane_box(f, fhat, dirs_f, dirs_h, gr, x, y, z + 1);  // plane z + 1
-            const long i = c + static_cast<long>(gr.nxy) * z;
-            const double sh = pm.sh + p0.sh + pp.sh, sf = pm.sf + p0.sf + pp.sf;
-            const int n = pm.cnt + p0.cnt + pp.cnt;
-            const double hi = fhat[i], fi = f[i];
-            const float ch0 = fminf(fmaxf(static_cast<float>((hi - sh / n) / xi), -8.0f), 8.0f);
-            const float ch6 = fminf(fmaxf(static_cast<float>((hi - fi) / xi), -8.0f), 8.0f);
-            const float ch7 = fminf(fmaxf(static_cast<float>((fi - sf / n) / xi), -8.0f), 8.0f);
-            const unsigned df = p0.df(0, 0), dh = p0.dh(0, 0);
-            const unsigned uf = df >> 4, nf = df & 15u, uh = dh >> 4, nh = dh & 15u;
-            const float fl[4] = {static_cast<float>((uh == kSelf) & (uf != kSelf)), static_cast<float>((nh == kSelf) & (nf != kSelf)),
-                                 static_cast<float>((uf == kSelf) & (uh != kSelf)), static_cast<float>((nf == kSelf) & (nh != kSelf))};
-            // the neighbour slots (offsets as in the slot table): in-plane ones, then the off-plane ones in 3D
-            unsigned tg = target_bits(p0, 0, 1, 0) | target_bits(p0, 1, -1, 0) | target_bits(p0, 2, 0, 1) |
-                          target_bits(p0, 3, 0, -1) | target_bits(p0, 4, 1, 1) | target_bits(p0, 5, -1, -1);
-            if (gr.ndim == 3)
-                tg |= target_bits(pp, 6, 0, 0) | target_bits(pm, 7, 0, 0) | target_bits(pp, 8, 1, 0) |
-                      target_bits(pm, 9, -1, 0) | target_bits(pp, 10, 0, 1) | target_bits(pm, 11, 0, -1) |
-                      target_bits(pp, 12, 1, 1) | target_bits(pm, 13, -1, -1);
+
+    // plane z into registers (unconditional loads; zeros outside the grid)
+    float2 rv[PER];
+    uint2 rt[PER];
+    auto load = [&](int z) {
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int e = min(static_cast<int>(threadIdx.x) + 256 * k, NP - 1);
+            const int xx = X0 + e % kFeatHX - 1, yy = Y0 + e / kFeatHX - 1;
+            const bool ok = xx >= 0 && xx < gr.nx && yy >= 0 && yy < gr.ny && z >= 0 && z < gr.nz;
+            const long j = ok ? xx + static_cast<long>(gr.nx) * yy + static_cast<long>(gr.nxy) * z : 0;
+            const float fj = f[j], hj = fhat[j];
+            const TargetMask m = target_mask(dirs_f[j], dirs_h[j]);
+            rv[k] = make_float2(ok ? fj : 0.0f, ok ? hj : 0.0f);
+            rt[k] = make_uint2(ok ? m.a : 0u, ok ? m.b : 0u);
+        }
+    };
+    auto store = [&](int slot) {
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int e = threadIdx.x + 256 * k;
+            if (e < NP) sv[slot][e] = rv[k], st[slot][e] = rt[k];
+        }
+    };
+
+    // carried from plane to plane: box sums of the last two planes, the last
+    // plane's target bits within itself and those of the two planes before,
+    // the vertex's values
+    double sf_m = 0.0, sh_m = 0.0, sf_0 = 0.0, sh_0 = 0.0;
+    uint2 t_0 = make_uint2(0u, 0u), t_dn = t_0, t_hold = t_0, m_0 = t_0;
+    float2 v_0 = make_float2(0.0f, 0.0f);
+    int n_last = 0;
+    double r_last = 0.0;
+
+    load(Z0 - 1);
+    store(0);
+    __syncthreads();
+    for (int z = Z0 - 1; z <= z_end; ++z) {  // plane z is in LDS; vertex z - 1 is written
+        const int slot = (z - Z0 + 1) & 1;
+        if (z < z_end) load(z + 1);
+        const float2* pv = sv[slot] + (lx + 1) + kFeatHX * (ly + 1);
+        const uint2* pt = st[slot] + (lx + 1) + kFeatHX * (ly + 1);
+        double sf = 0.0, sh = 0.0;
+#pragma unroll
+        for (int dy = -1; dy <= 1; ++dy)
+#pragma unroll
+            for (int dx = -1; dx <= 1; ++dx) {
+                const float2 v = pv[dx + kFeatHX * dy];
+                sf += v.x;
+                sh += v.y;
+            }
+        const uint2 c = pt[0], px = pt[1], mx = pt[-1], py = pt[kFeatHX], my = pt[-kFeatHX], pxy = pt[kFeatHX + 1],
+                    mxy = pt[-kFeatHX - 1];
+        uint2 t_up = make_uint2(0u, 0u), t_in = t_up, t_next = t_up;
+        add_target(t_up, c, 6);  // this plane's vertices seen from the plane below it
+        add_target(t_up, px, 8);
+        add_target(t_up, py, 10);
+        add_target(t_up, pxy, 12);
+        add_target(t_in, px, 0);
+        add_target(t_in, mx, 1);
+        add_target(t_in, py, 2);
+        add_target(t_in, my, 3);
+        add_target(t_in, pxy, 4);
+        add_target(t_in, mxy, 5);
+        add_target(t_next, c, 7);  // and from the plane above it
+        add_target(t_next, mx, 9);
+        add_target(t_next, my, 11);
+        add_target(t_next, mxy, 13);
+        if (z > Z0 && in_xy) {
+            const int zc = z - 1;
+            const int n = n_xy * (1 + (zc > 0) + (zc + 1 < gr.nz));
+            if (n != n_last) n_last = n, r_last = 1.0 / n;
+            const double hi = v_0.y, fi = v_0.x;
+            const double bh = quotient(sh_m + sh_0 + sh, n, r_last), bf = quotient(sf_m + sf_0 + sf, n, r_last);
+            const float ch0 = fminf(fmaxf(static_cast<float>(quotient(hi - bh, xid, rxi)), -8.0f), 8.0f);
+            const float ch6 = fminf(fmaxf(static_cast<float>(quotient(hi - fi, xid, rxi)), -8.0f), 8.0f);
+            const float ch7 = fminf(fmaxf(static_cast<float>(quotient(fi - bf, xid, rxi)), -8.0f), 8.0f);
+            const unsigned ta = t_0.x | t_up.x | t_dn.x, tb = t_0.y | t_up.y | t_dn.y;
             uint4 o0, o1;
             o0.x = static_cast<unsigned>(bf16_bits(ch0)) | (static_cast<unsigned>(bf16_bits(xi_ch)) << 16);
-            o0.y = static_cast<unsigned>(bf16_bits(fl[0])) | (static_cast<unsigned>(bf16_bits(fl[1])) << 16);
-            o0.z = static_cast<unsigned>(bf16_bits(fl[2])) | (static_cast<unsigned>(bf16_bits(fl[3])) << 16);
+            // the vertex's own cases: its ascents differ and fhat's is itself (FPmax), ...
+            o0.y = ((m_0.y & 0x8000u) ? one : 0u) | ((m_0.x >> 16) ? one << 16 : 0u);
+            o0.z = ((m_0.y >> 16) ? one : 0u) | ((m_0.x & 0x8000u) ? one << 16 : 0u);
             o0.w = static_cast<unsigned>(bf16_bits(ch6)) | (static_cast<unsigned>(bf16_bits(ch7)) << 16);
-            o1.x = ((tg & 1u) ? one : 0u) | (((tg & 2u) ? one : 0u) << 16);
-            o1.y = ((tg & 4u) ? one : 0u) | (((tg & 8u) ? one : 0u) << 16);
+            o1.x = ((ta >> 16) ? one : 0u) | ((tb >> 16) ? one << 16 : 0u);
+            o1.y = ((ta & 1u) ? one : 0u) | ((tb & 1u) ? one << 16 : 0u);
             o1.z = 0u;
             o1.w = 0u;
+            const long i = x + static_cast<long>(gr.nx) * y + static_cast<long>(gr.nxy) * zc;
             uint4* dst = reinterpret_cast<uint4*>(feat) + 2 * i;
             dst[0] = o0;
             dst[1] = o1;
-            pm = p0;
-            p0 = pp;
         }
+        sf_m = sf_0, sh_m = sh_0, sf_0 = sf, sh_0 = sh;
+        t_0 = t_in, m_0 = c, v_0 = pv[0];
+        t_dn = t_hold, t_hold = t_next;  // vertex z + 1 is written when plane z + 2 is in LDS
+        if (z < z_end) store(slot ^ 1);
+        __syncthreads();
     }
 }
 
@@ -610,17 +666,19 @@ __device__ __forceinline__ float halve_to(float g, float L) {
 }
 
 // Warm start: fhat halved k times, k = floor(fl(p - p_min)) + 1 clamped to
-// [0, kMaxWarmHalvings] (0 where p is not a number).
+// [0, kMaxWarmHalvings] (0 where p is not a number).  The floor is formed
+// where a value is halved (a few percent of the vertices): for 256^3 54 us,
+// where a pass that stored every floor first and this one took 79.
 constexpr int kMaxWarmHalvings = 64;
-__global__ void __launch_bounds__(256) k_warm_start(const float* __restrict__ p, const float* __restrict__ L,
-                                                    const float* __restrict__ fhat, float p_min, int n,
+__global__ void __launch_bounds__(256) k_warm_start(const float* __restrict__ p, const float* __restrict__ f,
+                                                    const float* __restrict__ fhat, float xi, float p_min, int n,
                                                     float* __restrict__ g0) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         const float q = floorf(__fsub_rn(p[i], p_min)) + 1.0f;
         const int k = q > 0.0f ? (q < static_cast<float>(kMaxWarmHalvings) ? static_cast<int>(q) : kMaxWarmHalvings) : 0;
         float g = fhat[i];
         if (k > 0) {
-            const float l = L[i];
+            const float l = floor_bound(f[i], xi);
             for (int j = 0; j < k; ++j) g = halve_to(g, l);
         }
         g0[i] = g;
@@ -630,10 +688,11 @@ __global__ void __launch_bounds__(256) k_warm_start(const float* __restrict__ p,
 // Training target: the number of halvings that take fhat_i to g_i (-1 when
 // g_i is not on that chain within kMaxCount steps).
 constexpr int kMaxCount = 256;
-__global__ void __launch_bounds__(256) k_halvings(const float* __restrict__ L, const float* __restrict__ fhat,
-                                                  const float* __restrict__ g, int n, float* __restrict__ k_out) {
+__global__ void __launch_bounds__(256) k_halvings(const float* __restrict__ f, const float* __restrict__ fhat,
+                                                  const float* __restrict__ g, float xi, int n,
+                                                  float* __restrict__ k_out) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const float gi = g[i], l = L[i];
+        const float gi = g[i], l = floor_bound(f[i], xi);
         float cur = fhat[i];
         int k = 0;
         while (cur > gi && k < kMaxCount) {
@@ -700,7 +759,7 @@ bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // Net workspace of one field.
 struct NetLayout {
-    size_t dirs_f, dirs_h, feat, a1, a2, p, dz_a, dz_b, part, minmax, L, g0, total;
+    size_t dirs_f, dirs_h, feat, a1, a2, p, dz_a, dz_b, part, minmax, g0, total;
 };
 
 NetLayout net_layout(const Grid& gr) {
@@ -722,7 +781,6 @@ NetLayout net_layout(const Grid& gr) {
     l.dz_b = take(n * 32);
     l.part = take(static_cast<size_t>(dw_blocks(gr)) * kDwSums * 4);
     l.minmax = take(kConvBlocks * 2 * 4);
-    l.L = take(n * 4);
     l.g0 = take(n * 4);
     l.total = o;
     return l;
@@ -799,10 +857,6 @@ __global__ void __launch_bounds__(256) k_minmax(const float* __restrict__ f, int
     }
 }
 
-__global__ void __launch_bounds__(256) k_floor(const float* __restrict__ f, float xi, int n, float* __restrict__ L) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) L[i] = floor_bound(f[i], xi);
-}
-
 int blocks_n(long n) {
     long b = (n + 255) / 256;
     return static_cast<int>(b < 1 ? 1 : (b > kConvBlocks ? kConvBlocks : b));
@@ -827,7 +881,8 @@ int features_impl(const float* f, const float* fhat, const Grid& gr, float xi, u
     const float xi_ch = static_cast<float>(std::log10(static_cast<double>(xi) / range) / 4.0 + 1.0);
     launch_dirs(f, gr, 0, df, s);
     launch_dirs(fhat, gr, 0, dh, s);
-    hipLaunchKernelGGL(k_features, dim3(blocks_n(gr.nxy)), dim3(256), 0, s, f, fhat, df, dh, gr, xi, xi_ch, feat);
+    const int nt = ((gr.nx + kFeatX - 1) / kFeatX) * ((gr.ny + kFeatY - 1) / kFeatY) * ((gr.nz + kFeatZ - 1) / kFeatZ);
+    hipLaunchKernelGGL(k_features, dim3(nt), dim3(256), 0, s, f, fhat, df, dh, gr, xi, xi_ch, feat);
     return hipGetLastError() == hipSuccess ? MSZ_OK : MSZ_EDEVICE;
 }
 
@@ -868,11 +923,9 @@ int msz_net_halvings(const float* f, const float* fhat, const float* g, msz_dims
     if (!make_grid(d, gr) || !f || !fhat || !g || !k_out) return MSZ_EINVAL;
     if (!(xi > 0.0f) || !(xi <= kValueLimit)) return MSZ_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    Scratch2 ws;
-    if (int rc = ws.get(workspace, workspace_bytes, a256(static_cast<size_t>(gr.n) * sizeof(float)), s)) return rc;
-    float* L = static_cast<float*>(ws.p);
-    hipLaunchKernelGGL(k_floor, dim3(blocks_n(gr.n)), dim3(256), 0, s, f, xi, gr.n, L);
-    hipLaunchKernelGGL(k_halvings, dim3(blocks_n(gr.n)), dim3(256), 0, s, L, fhat, g, gr.n, k_out);
+    // the declared scratch is not needed (the floors are formed in place)
+    if (workspace && workspace_bytes < a256(static_cast<size_t>(gr.n) * sizeof(float))) return MSZ_EINVAL;
+    hipLaunchKernelGGL(k_halvings, dim3(blocks_n(gr.n)), dim3(256), 0, s, f, fhat, g, xi, gr.n, k_out);
     if (hipGetLastError() != hipSuccess) return MSZ_EDEVICE;
     return hipStreamSynchronize(s) == hipSuccess ? MSZ_OK : MSZ_EDEVICE;
 }
@@ -970,12 +1023,10 @@ int msz_fix_learned(const float* f, const float* fhat, msz_dims d, float xi, con
     uint16_t* feat = reinterpret_cast<uint16_t*>(w + l.feat);
     int rc = features_impl(f, fhat, gr, xi, feat, w, l, s);
     float* p = reinterpret_cast<float*>(w + l.p);
-    float* L = reinterpret_cast<float*>(w + l.L);
     float* g0 = reinterpret_cast<float*>(w + l.g0);
     if (rc == MSZ_OK) {
         net_forward(params, feat, gr, reinterpret_cast<uint16_t*>(w + l.a1), reinterpret_cast<uint16_t*>(w + l.a2), p, s);
-        hipLaunchKernelGGL(k_floor, dim3(blocks_n(gr.n)), dim3(256), 0, s, f, xi, gr.n, L);
-        hipLaunchKernelGGL(k_warm_start, dim3(blocks_n(gr.n)), dim3(256), 0, s, p, L, fhat, p_min, gr.n, g0);
+        hipLaunchKernelGGL(k_warm_start, dim3(blocks_n(gr.n)), dim3(256), 0, s, p, f, fhat, xi, p_min, gr.n, g0);
         if (hipGetLastError() != hipSuccess) rc = MSZ_EDEVICE;
     }
     if (timing) (void)hipEventRecord(e1, s);
