@@ -111,6 +111,16 @@ namespace msz {
 // Validates dims (ndim 2 or 3, nz == 1 in 2D, positive sides, n <= 2^31 - 2^16) and fills gr.
 bool make_grid(const msz_dims& d, Grid& gr);
 
+// Device scratch of one call: the caller's, or taken from the library's pool
+// on the call's stream and given back to it at the end.
+struct Scratch {
+    void* p = nullptr;
+    hipStream_t s = nullptr;
+    bool owned = false;
+    ~Scratch();
+    int get(void* user, size_t user_bytes, size_t need, hipStream_t stream);
+};
+
 void launch_check_finite(const float* h, int n, unsigned* cnt, hipStream_t s);
 void launch_dirs(const float* h, const Grid& gr, int variant, uint8_t* dirs_out, hipStream_t s);
 void launch_label_tile(const uint8_t* dirs, const Grid& gr, int* q_up, int* q_dn, hipStream_t s);

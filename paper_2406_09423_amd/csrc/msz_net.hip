@@ -786,29 +786,6 @@ NetLayout net_layout(const Grid& gr) {
     return l;
 }
 
-struct Scratch2 {
-    void* p = nullptr;
-    hipStream_t s = nullptr;
-    bool owned = false;
-    ~Scratch2() {
-        if (owned && p) (void)hipFreeAsync(p, s);
-    }
-    int get(void* user, size_t user_bytes, size_t need, hipStream_t stream) {
-        s = stream;
-        if (user) {
-            if (user_bytes < need) return MSZ_EINVAL;
-            p = user;
-            return MSZ_OK;
-        }
-        if (hipMallocAsync(&p, need, stream) != hipSuccess) {
-            p = nullptr;
-            return MSZ_ENOMEM;
-        }
-        owned = true;
-        return MSZ_OK;
-    }
-};
-
 WeightView layer_view(const float* P, int layer) {
     switch (layer) {
         case 0: return {P + kOffW0, P + kOffB0, 256, 16, 1, 16, 16, 0};
@@ -910,7 +887,7 @@ int msz_net_features(const float* f, const float* fhat, msz_dims d, float xi, ui
     if (!make_grid(d, gr) || !f || !fhat || !feat || !al16(feat)) return MSZ_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const NetLayout l = net_layout(gr);
-    Scratch2 ws;
+    Scratch ws;
     if (int rc = ws.get(workspace, workspace_bytes, l.total, s)) return rc;
     const int rc = features_impl(f, fhat, gr, xi, feat, static_cast<char*>(ws.p), l, s);
     if (rc) return rc;
@@ -937,7 +914,7 @@ int msz_net_forward(const float* params, const uint16_t* feat, msz_dims d, float
         return MSZ_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const NetLayout l = net_layout(gr);
-    Scratch2 ws;
+    Scratch ws;
     if (int rc = ws.get(workspace, workspace_bytes, l.total, s)) return rc;
     char* w = static_cast<char*>(ws.p);
     uint16_t* a1 = act1_out ? act1_out : reinterpret_cast<uint16_t*>(w + l.a1);
@@ -953,7 +930,7 @@ int msz_net_gradients(const float* params, const uint16_t* feat, const float* ta
     if (!make_grid(d, gr) || !params || !feat || !target || !grad_out || !loss_out || !al16(feat)) return MSZ_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const NetLayout l = net_layout(gr);
-    Scratch2 ws;
+    Scratch ws;
     if (int rc = ws.get(workspace, workspace_bytes, l.total, s)) return rc;
     char* w = static_cast<char*>(ws.p);
     uint16_t* a1 = reinterpret_cast<uint16_t*>(w + l.a1);
@@ -1010,7 +987,7 @@ int msz_fix_learned(const float* f, const float* fhat, msz_dims d, float xi, con
     hipStream_t s = static_cast<hipStream_t>(stream);
     const NetLayout l = net_layout(gr);
     const size_t fix_bytes = msz_workspace_bytes(d);
-    Scratch2 ws;
+    Scratch ws;
     if (int rc = ws.get(o.workspace, o.workspace_bytes, a256(l.total) + fix_bytes, s)) {
         stats->status = rc;
         return rc;
