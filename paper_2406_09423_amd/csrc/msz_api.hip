@@ -41,6 +41,8 @@ bool make_grid(const msz_dims& d, Grid& gr) {
     gr.nz = d.nz;
     gr.nxy = d.nx * d.ny;
     gr.n = static_cast<int>(n);
+    gr.by_nx.set(gr.nx);
+    gr.by_nxy.set(gr.nxy);
     const int64_t X = 1, Y = d.nx, Z = static_cast<int64_t>(d.nx) * d.ny;
     const int64_t off[16] = {X,      -X,      Y,          -Y,          X + Y,          -X - Y,
                              Z,      -Z,      Z + X,      -Z - X,      Z + Y,          -Z - Y,
@@ -131,7 +133,7 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 
 // Workspace of one field.
 struct Layout {
-    size_t L, g, dirs_f, dirs_g, marks, cases, dirty, chunk_dirty, chunk_cnt, chunk_unk, tile_dirty, Mf, mf, qu, qd, total;
+    size_t L, g, dirs_f, dirs_g, marks, cases, dirty, chunk_dirty, chunk_cnt, chunk_unk, sparse, tile_dirty, Mf, mf, qu, qd, total;
 };
 
 Layout layout_for(const Grid& gr) {
@@ -153,6 +155,7 @@ Layout layout_for(const Grid& gr) {
     l.chunk_dirty = take(((n + kEngChunk - 1) / kEngChunk) * 4);
     l.chunk_cnt = take(((n + kEngChunk - 1) / kEngChunk) * 8);
     l.chunk_unk = take(((n + kEngChunk - 1) / kEngChunk) * 4);
+    l.sparse = take(sizeof(SparseBuf));
     l.tile_dirty = take(label_tile_count(gr));
     l.Mf = take(n * 4);
     l.mf = take(n * 4);
@@ -402,7 +405,7 @@ int phase_of_op(int op) {
         case kOpPreA2: return MSZ_PHASE_DIRS;
         case kOpPreB: case kOpRTile: return MSZ_PHASE_LABEL_TILE;
         case kOpPreD: return MSZ_PHASE_LABEL_FINAL;
-        case kOpApplyC: return MSZ_PHASE_APPLY;
+        case kOpApplyC: case kOpSparseC: return MSZ_PHASE_APPLY;
         case kOpPreE: case kOpFullC: case kOpFullR: return MSZ_PHASE_DIRS_DETECT;
         case kOpRefreshC: case kOpRefreshR: return MSZ_PHASE_REFRESH;
         case kOpRDetect: return MSZ_PHASE_DETECT_R;
@@ -726,6 +729,7 @@ void bind_field(EngField& F, char* w) {
     F.chunk_dirty = reinterpret_cast<unsigned*>(w + l.chunk_dirty);
     F.chunk_cnt = reinterpret_cast<unsigned*>(w + l.chunk_cnt);
     F.chunk_unk = reinterpret_cast<unsigned*>(w + l.chunk_unk);
+    F.sparse = reinterpret_cast<SparseBuf*>(w + l.sparse);
     F.tile_dirty = reinterpret_cast<uint8_t*>(w + l.tile_dirty);
     F.Mf = reinterpret_cast<int*>(w + l.Mf);
     F.mf = reinterpret_cast<int*>(w + l.mf);

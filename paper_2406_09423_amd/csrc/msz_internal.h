@@ -30,9 +30,28 @@ enum : int {
 };
 enum : unsigned { kErrNonFinite = 1u, kErrBound = 2u, kErrWarmNonFinite = 4u, kErrWarmBound = 8u, kErrWalk = 16u };
 
+// Exact quotients of ids (0 <= i < 2^31) by a fixed divisor d: with
+// l = ceil(log2 d) and m = floor(2^(31 + l) / d) + 1 <= 2^32 - 1,
+// i / d = i m / 2^(31 + l) rounded down (m exceeds 2^(31 + l) / d by at most
+// 1, so the product exceeds the quotient by less than 1 / d).
+struct FastDiv {
+    unsigned m;
+    int s;
+    void set(int d) {
+        int l = 0;
+        while ((1ll << l) < d) ++l;
+        s = 31 + l;
+        m = static_cast<unsigned>((1ull << s) / static_cast<unsigned>(d) + 1);
+    }
+    __device__ __forceinline__ int of(int i) const {
+        return static_cast<int>((static_cast<unsigned long long>(static_cast<unsigned>(i)) * m) >> s);
+    }
+};
+
 struct Grid {
     int ndim, nx, ny, nz, nxy, n;
     int off[16];  // linear id offset of each neighbour slot; off[15] = 0 (self)
+    FastDiv by_nx, by_nxy;
 };
 
 // Work items of a persistent grid, XCD-aware: blocks are dealt to the 8 XCDs
@@ -163,6 +182,7 @@ enum EngOp : int {
     kOpRDetect,    // troublemakers (labels by following the exit chains), and the edits of their targets
     kOpRefreshR,   // directions and cases of the vertices around the last R edits
     kOpFullR,      // the same for every vertex
+    kOpSparseC,    // C rounds while few cases are left: listed by all blocks, run by one
     kOpDelta,      // output
     kOpDone,
     kOpStart       // before the first step (its successor is kOpPreA)
@@ -171,6 +191,27 @@ enum EngOp : int {
 // EngState.type of a merged C round (all four case types at once); 0..3 are
 // the sub-loop types FPmax, FPmin, FNmax, FNmin.
 constexpr int kTypeMerged = 4;
+
+// Sparse C rounds (kOpSparseC): the most cases listed at their start, and a
+// flag added to EngState.type when the list holds the cases of every type.
+constexpr int kSparseCases = 256;
+constexpr int kTypeAll = 8;
+
+// What a run of sparse C rounds did, for the schedule.
+struct SparseResult {
+    int rounds[4];  // as EngStats.rounds counts them
+    int total;      // productive rounds
+    int cases[4];   // the number of cases of each type
+    int type;       // EngState.type after them
+    int stalled;    // 1: the last round changed nothing
+};
+
+// A field's cases as the blocks of a sparse step list them.
+struct SparseBuf {
+    int count, ticket;
+    SparseResult result[2];  // one-field runs, by step parity: for the next step's decision
+    int list[kSparseCases];
+};
 
 struct EngField {
     Grid gr;
@@ -192,6 +233,7 @@ struct EngField {
     unsigned* chunk_cnt;    // per kEngChunk vertices, 2 words: the number of cases of types 0, 1 (16-bit
                             // halves of word 0) and 2, 3 (word 1) in the chunk -- exact unless chunk_unk
     unsigned* chunk_unk;    // per kEngChunk vertices: 1 when the counts are not known (after a full pass)
+    SparseBuf* sparse;
     uint8_t *tile_dirty;  // per label tile: a direction of g in it changed since its last tile pass
     int *Mf, *mf, *qu, *qd;  // pointers of f's (Mf, mf) and g's (qu, qd) ascending / descending forests
     unsigned* cnt;  // kCntBlockWords words (kSlots slots), in the engine's control block

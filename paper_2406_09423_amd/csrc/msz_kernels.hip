@@ -572,6 +572,22 @@ __device__ __forceinline__ int slot_offset(const Grid& gr, unsigned s) {
     return dx + gr.nx * dy + gr.nxy * dz;
 }
 
+// Coordinates of vertex i.
+template <int NDIM>
+__device__ __forceinline__ void coords(const Grid& gr, int i, int& x, int& y, int& z) {
+    z = NDIM == 3 ? gr.by_nxy.of(i) : 0;
+    const int r = NDIM == 3 ? i - z * gr.nxy : i;
+    y = gr.by_nx.of(r);
+    x = r - y * gr.nx;
+}
+
+// Whether every neighbour of the vertex at (x, y, z) lies in the grid.
+template <int NDIM>
+__device__ __forceinline__ bool interior(const Grid& gr, int x, int y, int z) {
+    const bool in2 = x > 0 && x + 1 < gr.nx && y > 0 && y + 1 < gr.ny;
+    return NDIM == 2 ? in2 : in2 && z > 0 && z + 1 < gr.nz;
+}
+
 // Whether neighbour slot s of the vertex at (x, y, z) lies in the grid.
 template <int NDIM>
 __device__ __forceinline__ bool slot_in_grid(const Grid& gr, int x, int y, int z, int s) {
@@ -605,7 +621,8 @@ __device__ __forceinline__ void edit_value(float* __restrict__ g, const Dirty& d
     if (nv == old) return;
     g[t] = nv;
     ++changed;
-    const int x = t % gr.nx, y = (t / gr.nx) % gr.ny, z = NDIM == 3 ? t / gr.nxy : 0;
+    int x, y, z;
+    coords<NDIM>(gr, t, x, y, z);
     constexpr int NS = NDIM == 3 ? 14 : 6;
 #pragma unroll
     for (int s = 0; s < NS; ++s)
@@ -653,7 +670,8 @@ __device__ __forceinline__ void preempt_edit(float* __restrict__ g, const float*
     if (nv == old) return;
     __hip_atomic_store(g + t, nv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     ++changed;
-    const int x = t % gr.nx, y = (t / gr.nx) % gr.ny, z = NDIM == 3 ? t / gr.nxy : 0;
+    int x, y, z;
+    coords<NDIM>(gr, t, x, y, z);
     constexpr int NS = NDIM == 3 ? 14 : 6;
 #pragma unroll
     for (int s = 0; s < NS; ++s)
@@ -994,7 +1012,8 @@ template <int NDIM>
 __device__ __forceinline__ int tile_of_vertex(const Grid& gr, int i) {
     using T = LabelTile<NDIM>;
     const int tx_n = (gr.nx + T::X - 1) / T::X, ty_n = (gr.ny + T::Y - 1) / T::Y;
-    const int x = i % gr.nx, y = (i / gr.nx) % gr.ny, z = NDIM == 3 ? i / gr.nxy : 0;
+    int x, y, z;
+    coords<NDIM>(gr, i, x, y, z);
     return x / T::X + tx_n * (y / T::Y + ty_n * (z / T::Z));
 }
 
@@ -1656,7 +1675,7 @@ __host__ __device__ inline int eng_items(const EngField& F, int op) {
     const int tiles = label_tiles_of(F.gr);
     const int dirs = dirs_items_of(F.gr, F.variant);
     switch (op) {
-        case kOpPreA: case kOpApplyC: case kOpRefreshC: case kOpRefreshR: case kOpDelta:
+        case kOpPreA: case kOpApplyC: case kOpSparseC: case kOpRefreshC: case kOpRefreshR: case kOpDelta:
             return chunks;
         case kOpPreB: case kOpPreD: case kOpRTile: case kOpRDetect: return tiles;
         case kOpPreA2: case kOpPreE: case kOpFullC: case kOpFullR: return dirs;
@@ -1683,7 +1702,7 @@ __host__ __device__ inline int eng_weight(const EngField& F, int op) {
         case kOpPreD: return 22;
         case kOpRTile: return 13;  // the clean tiles of g are skipped
         case kOpRDetect: return 22;
-        case kOpApplyC: case kOpRefreshC: return 2;
+        case kOpApplyC: case kOpSparseC: case kOpRefreshC: return 2;
         case kOpRefreshR: return 3;
         case kOpDelta: return 5;
         default: return 1;
@@ -1711,31 +1730,41 @@ __device__ __forceinline__ void eng_dirs(const EngField& F, const float* h, uint
     }
 }
 
-// Steepest ascent and descent of vertex i in g, read straight from memory
-// (the refresh of a few vertices): the same neighbour order and comparisons
-// as the stencil (odd slots have the smaller ids, even slots the larger ones,
-// each nearest first), with neighbours outside the grid left out.
+// Vertex i and its neighbours in g, read straight from memory (the refresh of
+// a few vertices); neighbours outside the grid are NaN.
 template <int NDIM>
-__device__ __forceinline__ unsigned steepest_at(const float* __restrict__ g, const Grid& gr, int i) {
-    constexpr int NS = NDIM == 3 ? 14 : 6;
-    const int x = i % gr.nx, y = (i / gr.nx) % gr.ny, z = NDIM == 3 ? i / gr.nxy : 0;
-    const float nan = __builtin_nanf("");
-    float w[NS];
+struct Around {
+    static constexpr int NS = NDIM == 3 ? 14 : 6;
+    float v, w[NS];
+    __device__ __forceinline__ Around(const float* __restrict__ g, const Grid& gr, int i) {
+        int x, y, z;
+        coords<NDIM>(gr, i, x, y, z);
+        v = g[i];
+        if (interior<NDIM>(gr, x, y, z)) {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) w[s] = slot_in_grid<NDIM>(gr, x, y, z, s) ? g[i + gr.off[s]] : nan;
-    const float v = g[i];
-    Steepest b{v, v, kSelf, kSelf};
+            for (int s = 0; s < NS; ++s) w[s] = g[i + gr.off[s]];
+        } else {
 #pragma unroll
-    for (int s = 1; s < NS; s += 2) b.below(w[s], s);
+            for (int s = 0; s < NS; ++s) w[s] = slot_in_grid<NDIM>(gr, x, y, z, s) ? g[i + gr.off[s]] : __builtin_nanf("");
+        }
+    }
+    // steepest ascent and descent: the same neighbour order and comparisons as
+    // the stencil (odd slots have the smaller ids, even slots the larger ones,
+    // each nearest first)
+    __device__ __forceinline__ unsigned steepest() const {
+        Steepest b{v, v, kSelf, kSelf};
 #pragma unroll
-    for (int s = 0; s < NS; s += 2) b.above(w[s], s);
-    return (b.us << 4) | b.ds;
-}
+        for (int s = 1; s < NS; s += 2) b.below(w[s], s);
+#pragma unroll
+        for (int s = 0; s < NS; s += 2) b.above(w[s], s);
+        return (b.us << 4) | b.ds;
+    }
+};
 
-// Runs fn(v) for every flagged vertex v of the chunks [lo, hi) (kEngChunk
-// vertices each; thread t loads the 16 flag bytes t of a chunk, and a byte
-// flags its vertex when it has a bit of `mask` set; bytes past the grid are
-// never set).  With use_sel, a range of at least kSelectChunks chunks reads only the
+// Runs fn(list, np), by all threads of the block, on lists of the flagged
+// vertices of the chunks [lo, hi) (kEngChunk vertices each; thread t loads the
+// 16 flag bytes t of a chunk, and a byte flags its vertex when it has a bit of
+// `mask` set; bytes past the grid are never set).  With use_sel, a range of at least kSelectChunks chunks reads only the
 // chunks c with sel(c): the block evaluates sel for 256 chunks at once (one
 // per thread) and takes the selected ones from its ballots, so a range with
 // none costs one summary load per thread; after chunk c was read, thread 0
@@ -1849,8 +1878,7 @@ __device__ __forceinline__ int for_flagged(const uint8_t* flags, int n, int lo, 
                     }
             }
             __syncthreads();
-            const int np = min(kEngChunk, total - p0);
-            for (int e = threadIdx.x; e < np; e += blockDim.x) fn(list[e]);
+            fn(list, min(kEngChunk, total - p0));
             __syncthreads();  // the list is rewritten next
         }
     };
@@ -1888,6 +1916,14 @@ __device__ __forceinline__ int for_flagged(const uint8_t* flags, int n, int lo, 
     return read;
 }
 
+// fn(v) for every vertex v of a list, spread over the block's threads.
+template <typename Fn>
+__device__ __forceinline__ auto each(Fn fn) {
+    return [fn](const int* list, int np) {
+        for (int e = threadIdx.x; e < np; e += blockDim.x) fn(list[e]);
+    };
+}
+
 __device__ __forceinline__ Dirty dirty_of(const EngField& F, bool sum) { return Dirty{F.dirty, sum ? F.chunk_dirty : nullptr}; }
 
 // An apply's record of a chunk it read in full: its exact case counts.
@@ -1899,16 +1935,32 @@ __device__ __forceinline__ auto chunk_counted(const EngField& F) {
     };
 }
 
+// What the refresh of vertex j reads.
+template <int NDIM>
+struct RefreshIn {
+    int j;
+    unsigned df, dg, cases;
+    Around<NDIM> a;
+    __device__ __forceinline__ RefreshIn(const EngField& F, int vertex)
+        : j(vertex), df(F.dirs_f[vertex]), dg(F.dirs_g[vertex]), cases(F.cases[vertex]), a(F.g, F.gr, vertex) {}
+};
+
 // Directions and case byte of vertex j recomputed from g; c receives the
 // change of each case count (modulo 2^32), and j's label tile is flagged if
-// its direction changed.
+// its direction changed.  Returns the case bits, f's directions (bits 8..15)
+// and g's (16..23).
 template <int NDIM>
-__device__ __forceinline__ void refresh_vertex(const EngField& F, int j, bool sum, unsigned (&c)[4]) {
-    const unsigned dg = steepest_at<NDIM>(F.g, F.gr, j);
-    const unsigned now = case_bits(F.dirs_f[j], dg), was = F.cases[j];
-    if (dg != F.dirs_g[j]) F.tile_dirty[tile_of_vertex<NDIM>(F.gr, j)] = 1;
-    F.dirs_g[j] = static_cast<uint8_t>(dg);
-    F.cases[j] = static_cast<uint8_t>(now);
+__device__ __forceinline__ unsigned refresh_vertex(const EngField& F, const RefreshIn<NDIM>& in, bool sum,
+                                                   unsigned (&c)[4]) {
+    const int j = in.j;
+    const unsigned df = in.df, was_dg = in.dg, was = in.cases;
+    const unsigned dg = in.a.steepest();
+    const unsigned now = case_bits(df, dg);
+    if (dg != was_dg) {
+        F.tile_dirty[tile_of_vertex<NDIM>(F.gr, j)] = 1;
+        F.dirs_g[j] = static_cast<uint8_t>(dg);
+    }
+    if (now != was) F.cases[j] = static_cast<uint8_t>(now);
     if (sum && now != was) {  // the chunk's case counts: types 0, 1 in word 0, types 2, 3 in word 1 (16 bits each)
         const int d0 = static_cast<int>(now & 1u) - static_cast<int>(was & 1u);
         const int d1 = static_cast<int>((now >> 1) & 1u) - static_cast<int>((was >> 1) & 1u);
@@ -1920,6 +1972,275 @@ __device__ __forceinline__ void refresh_vertex(const EngField& F, int j, bool su
     }
 #pragma unroll
     for (int t = 0; t < 4; ++t) c[t] += ((now >> t) & 1u) - ((was >> t) & 1u);
+    return now | (df << 8) | (dg << 16);
+}
+
+// Refreshes the np vertices vertex(e); done(v, result) after each.  In 2D a
+// thread takes two at a time, so that the loads of both are in flight
+// together (in 3D the second one's fifteen values would cost the step kernels
+// a fourth of their occupancy).
+template <int NDIM, typename Get, typename Done>
+__device__ __forceinline__ void refresh_list(const EngField& F, int np, bool sum, unsigned (&c)[4], Get&& vertex,
+                                             Done&& done) {
+    const int nt = blockDim.x;
+    if constexpr (NDIM == 2) {
+        for (int e = threadIdx.x; e < np; e += 2 * nt) {
+            const bool two = e + nt < np;
+            const RefreshIn<NDIM> a(F, vertex(e)), b(F, vertex(two ? e + nt : e));
+            done(a.j, refresh_vertex<NDIM>(F, a, sum, c));
+            if (two) done(b.j, refresh_vertex<NDIM>(F, b, sum, c));
+        }
+    } else {
+        for (int e = threadIdx.x; e < np; e += nt) {
+            const RefreshIn<NDIM> a(F, vertex(e));
+            done(a.j, refresh_vertex<NDIM>(F, a, sum, c));
+        }
+    }
+}
+
+// Blocks of one kernel hand counters, lists, tickets and decided states to
+// each other through device-scope atomics only (every XCD sees one value of
+// each), and a block draws its ticket after its own memory operations have
+// completed: a device-scope fence, which on MI355X writes back the L2 of the
+// XCD, is never needed.  Everything else a step writes is read by later
+// steps, after the kernel boundary.
+__device__ __forceinline__ int ld_dev(const int* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned ld_dev(const unsigned* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_dev(int* p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// True in every thread of the block that draws ticket n - 1 of *ticket.
+__device__ __forceinline__ bool draw_last(int* ticket, int n, int* s_flag) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores and atomics have completed
+    __syncthreads();
+    if (threadIdx.x == 0)
+        *s_flag = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+    __syncthreads();
+    return *s_flag != 0;
+}
+
+// ------------------------------------------------------- sparse C rounds ---
+//
+// Most C rounds of a correction have few cases (of the 44 of a 3600x2400
+// field, 31 have fewer than 512), and such a round costs two step kernels whose
+// time is the launch, the decision and the scan for flags.  Once few enough
+// cases are left, one step lists them (all blocks scan the case bytes) and its
+// last block runs the rounds to their end by itself, from lists in LDS, with
+// barriers where the other schedule has kernel boundaries.
+//
+// A round: (A) the targets of the listed cases are edited, each once; (B) the
+// changed vertices and their neighbours are put into the set of vertices to
+// refresh; (C) these are refreshed, and those that are cases then are the
+// next list.  The list stays complete: a case of the round is refreshed itself
+// (also when its target did not change), and any new case comes from a
+// changed direction; listed cases of other types that were not refreshed are
+// carried over.  The set is a hash table in LDS, which also holds the claims,
+// so the flags and claims in memory are neither used nor left behind; the
+// number of cases of a round is bounded so that the set cannot overflow.
+// Everything a round reads or writes in memory is touched by this block
+// alone, whose plain loads and stores its barriers order.
+//
+// Bound by latency: a round of a few cases takes 3 to 5 us (one gather for
+// the targets, one for the refresh, the LDS atomics of the set and five
+// barriers) where two step kernels take 11 on a 128x128 field and 25 on a
+// 3600x2400 one; 256 more refreshes add about 2.5 us, so rounds beyond a few
+// hundred cases are left to all blocks.  128x128 bumps 0.68 -> 0.43 ms,
+// 3600x2400 1.99 -> 1.82 ms, the 96-field batch 24.9 -> 22.6 ms.  (Flags
+// and claims in memory, as the other rounds use, with a workgroup-scope atomic
+// per neighbour, took 7 us a round.)
+constexpr int kSparseList = 512;     // listed cases, and changed vertices of a round
+constexpr int kSparseSlots = 4096;   // hash table
+constexpr int kSparseDirty = 3328;   // vertices in it
+constexpr int kNoVertex = -1;
+struct SparseLds {
+    int v[2][kSparseList];          // listed cases; while a round edits, the other half holds its changed vertices
+    unsigned info[2][kSparseList];  // case bits, directions in f (bits 8..15) and g (16..23)
+    int key[kSparseSlots];
+    unsigned short slot[kSparseDirty];
+    unsigned claim[kSparseSlots / 32];
+};
+
+// The most cases a round may have: each refreshes itself and, per target
+// (three at most with merged rounds), the target and its neighbours.
+__host__ __device__ inline int sparse_limit(const EngField& F) {
+    const int ring = F.gr.ndim == 3 ? 15 : 7;
+    const int fit = kSparseDirty / (1 + (F.merged ? 3 : 1) * ring);
+    return fit < kSparseCases ? fit : kSparseCases;
+}
+
+// Lists the cases of the chunks [lo, hi) of F (type as in sparse_rounds).
+template <int NDIM>
+__device__ __forceinline__ int sparse_list(const EngField& F, int type, int lo, int hi, bool sum, int* list, int* wsum) {
+    const int t = type & ~kTypeAll;
+    const bool all = (type & kTypeAll) != 0;
+    return for_flagged<false>(
+        F.cases, F.gr.n, lo, hi, all ? 0x0F0F0F0Fu : 0x01010101u << t, sum, list, wsum,
+        [&](int c) {
+            const unsigned w0 = F.chunk_cnt[2 * c], w1 = F.chunk_cnt[2 * c + 1];
+            return F.chunk_unk[c] != 0u || (all ? (w0 | w1) != 0u : (((t >> 1) ? w1 : w0) >> (16 * (t & 1))) & 0xFFFFu);
+        },
+        [](int, unsigned, unsigned) {},
+        each([&](int i) {
+            const int k = __hip_atomic_fetch_add(&F.sparse->count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (k < kSparseCases) st_dev(F.sparse->list + k, i);
+        }),
+        [](int) {});
+}
+
+// The slot of vertex v in the set, put there if it is not (the table always
+// has free slots: see sparse_limit).
+__device__ __forceinline__ int sparse_put(SparseLds& S, int v, int* count) {
+    unsigned h = (static_cast<unsigned>(v) * 2654435761u) >> 20;
+    static_assert(kSparseSlots == 1 << 12, "12 hash bits");
+    for (;;) {
+        const int old = atomicCAS(&S.key[h], kNoVertex, v);
+        if (old == kNoVertex) S.slot[atomicAdd(count, 1)] = static_cast<unsigned short>(h);
+        if (old == kNoVertex || old == v) return static_cast<int>(h);
+        h = (h + 1) & (kSparseSlots - 1);
+    }
+}
+
+__device__ __forceinline__ bool sparse_has(const SparseLds& S, int v) {
+    unsigned h = (static_cast<unsigned>(v) * 2654435761u) >> 20;
+    while (S.key[h] != v) {
+        if (S.key[h] == kNoVertex) return false;
+        h = (h + 1) & (kSparseSlots - 1);
+    }
+    return true;
+}
+
+// Edits target t unless another case of the round already has.
+__device__ __forceinline__ void sparse_edit(const EngField& F, SparseLds& S, int t, int* count, int* changed,
+                                            int* list) {
+    const float old = F.g[t], lt = F.L[t];  // only the claim's winner writes it
+    const int h = sparse_put(S, t, count);
+    const unsigned bit = 1u << (h & 31);
+    if (atomicOr(&S.claim[h >> 5], bit) & bit) return;
+    const float nv = halve(old, lt);
+    if (nv == old) return;
+    F.g[t] = nv;
+    list[atomicAdd(changed, 1)] = t;
+}
+
+// The rounds, by all threads of one block, from the listed cases of F: of all
+// types when type has kTypeAll, else of type alone (then they end when that
+// sub-loop does).  cases: the current counts; at most max_rounds rounds.
+template <int NDIM>
+__device__ __forceinline__ SparseResult sparse_rounds(const EngField& F, int type, const int (&cases)[4],
+                                                      long long max_rounds, bool sum, char* smem,
+                                                      unsigned long long& acct) {
+    static_assert(sizeof(SparseLds) <= kEngSmemBytes, "the lists fit the step kernels' LDS");
+    constexpr int NS = NDIM == 3 ? 14 : 6;
+    SparseLds& S = *reinterpret_cast<SparseLds*>(smem);
+    __shared__ int s_nd, s_nl, s_changed;
+    __shared__ int s_cases[4];
+    const Grid& gr = F.gr;
+    const bool all = (type & kTypeAll) != 0;
+    const int limit = sparse_limit(F);
+    SparseResult R{};
+    R.type = type & ~kTypeAll;
+    for (int e = threadIdx.x; e < kSparseSlots; e += blockDim.x) S.key[e] = kNoVertex;
+    for (int e = threadIdx.x; e < kSparseSlots / 32; e += blockDim.x) S.claim[e] = 0u;
+    int n = min(ld_dev(&F.sparse->count), kSparseCases);
+    for (int e = threadIdx.x; e < n; e += blockDim.x) {
+        const int i = ld_dev(F.sparse->list + e);
+        S.v[0][e] = i;
+        S.info[0][e] = F.cases[i] | (static_cast<unsigned>(F.dirs_f[i]) << 8) | (static_cast<unsigned>(F.dirs_g[i]) << 16);
+    }
+    if (threadIdx.x < 4)
+        s_cases[threadIdx.x] = threadIdx.x == 0 ? cases[0] : threadIdx.x == 1 ? cases[1] : threadIdx.x == 2 ? cases[2] : cases[3];
+    if (threadIdx.x == 0) s_nd = 0, s_nl = 0, s_changed = 0;
+    __syncthreads();
+    int cur = 0;
+    for (;;) {
+        // block-uniform: the counts, the list's length, the type
+        const int c0 = s_cases[0], c1 = s_cases[1], c2 = s_cases[2], c3 = s_cases[3];
+        if (R.type == kTypeMerged) {
+            if (c0 + c1 + c2 + c3 == 0) break;
+        } else {  // the next type with cases, in the order of the sub-loops
+            bool found = false, ended = false;
+            for (int guard = 0; guard < 8 && !found && !ended; ++guard) {
+                const int ct = R.type == 0 ? c0 : R.type == 1 ? c1 : R.type == 2 ? c2 : c3;
+                if (ct > 0) found = true;
+                else if (!all) ended = true;
+                else if (R.type < 3) ++R.type;
+                else if (c0 + c1 + c2 > 0) R.type = 0;
+                else ended = true;
+            }
+            if (!found) break;
+        }
+        if (R.total >= max_rounds || n > limit) break;
+        // A: the edits
+        unsigned tries = 0;
+        for (int e = threadIdx.x; e < n; e += blockDim.x) {
+            const int i = S.v[cur][e];
+            const unsigned w = S.info[cur][e], b = w & (R.type == kTypeMerged ? 0xFu : 1u << R.type);
+            if (!b) continue;
+            tries += __popc(b);
+            sparse_put(S, i, &s_nd);
+            if (b & 9u) sparse_edit(F, S, i, &s_nd, &s_changed, S.v[cur ^ 1]);
+            if (b & 2u) sparse_edit(F, S, i + slot_offset(gr, (w >> 8) & 15u), &s_nd, &s_changed, S.v[cur ^ 1]);
+            if (b & 4u) sparse_edit(F, S, i + slot_offset(gr, (w >> 20) & 15u), &s_nd, &s_changed, S.v[cur ^ 1]);
+        }
+        __syncthreads();
+        const int nc = s_changed;
+        acct += 16ull * tries + (threadIdx.x == 0 ? static_cast<unsigned long long>(NS) * nc : 0ull);
+        if (nc == 0) {
+            R.stalled = 1;
+            break;
+        }
+        R.total += 1;
+        if (R.type == kTypeMerged) {
+            R.rounds[0] += c0 > 0, R.rounds[1] += c1 > 0, R.rounds[2] += c2 > 0, R.rounds[3] += c3 > 0;
+        } else {
+            R.rounds[0] += R.type == 0, R.rounds[1] += R.type == 1, R.rounds[2] += R.type == 2, R.rounds[3] += R.type == 3;
+        }
+        // B: the changed vertices' neighbours, one per thread and pass
+        for (int e = threadIdx.x; e < nc * 16; e += blockDim.x) {
+            const int t = S.v[cur ^ 1][e >> 4], s = e & 15;
+            if (s >= NS) continue;
+            int x, y, z;
+            coords<NDIM>(gr, t, x, y, z);
+            if (slot_in_grid<NDIM>(gr, x, y, z, s)) sparse_put(S, t + slot_offset(gr, s), &s_nd);
+        }
+        __syncthreads();
+        // C: the refresh and the next list
+        const int nd = s_nd;
+        const unsigned keep = all ? 0xFu : 1u << R.type;  // the cases the list holds
+        unsigned c[4] = {0u, 0u, 0u, 0u};
+        refresh_list<NDIM>(F, nd, sum, c, [&](int e) { return S.key[S.slot[e]]; }, [&](int j, unsigned w) {
+            if (w & keep) {
+                const int k = atomicAdd(&s_nl, 1);
+                if (k < kSparseList) S.v[cur ^ 1][k] = j, S.info[cur ^ 1][k] = w;
+            }
+        });
+        acct += 9ull * ((nd + blockDim.x - 1 - threadIdx.x) / blockDim.x);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            if (c[t]) atomicAdd(&s_cases[t], static_cast<int>(c[t]));
+        if (all)  // listed cases that were not refreshed
+            for (int e = threadIdx.x; e < n; e += blockDim.x) {
+                const int i = S.v[cur][e];
+                if (sparse_has(S, i)) continue;
+                const int k = atomicAdd(&s_nl, 1);
+                if (k < kSparseList) S.v[cur ^ 1][k] = i, S.info[cur ^ 1][k] = S.info[cur][e];
+            }
+        __syncthreads();
+        n = s_nl;
+        for (int e = threadIdx.x; e < nd; e += blockDim.x) S.key[S.slot[e]] = kNoVertex;
+        for (int e = threadIdx.x; e < kSparseSlots / 32; e += blockDim.x) S.claim[e] = 0u;
+        cur ^= 1;
+        __syncthreads();
+        if (threadIdx.x == 0) s_nd = 0, s_nl = 0, s_changed = 0;
+        __syncthreads();
+    }
+    R.cases[0] = s_cases[0], R.cases[1] = s_cases[1], R.cases[2] = s_cases[2], R.cases[3] = s_cases[3];
+    __syncthreads();
+    if (threadIdx.x == 0) st_dev(&F.sparse->count, 0);
+    return R;
 }
 
 // ----------------------------------------------------- byte accounting ---
@@ -2058,7 +2379,7 @@ __device__ __forceinline__ void eng_run_range(const EngField& F, const EngState&
                     F.cases, gr.n, lo, hi, 0x0F0F0F0Fu, sum, list, list + kEngChunk,
                     [&](int c) { return F.chunk_unk[c] != 0u || (F.chunk_cnt[2 * c] | F.chunk_cnt[2 * c + 1]) != 0u; },
                     chunk_counted(F),
-                    [&](int i) {
+                    each([&](int i) {
                         const unsigned b = F.cases[i];
                         tries += __popc(b & 0xFu);
                         if (b & 9u) target_edit<NDIM>(pre, F.marks, F.g, F.L, dirty, gr, i, changed);
@@ -2068,7 +2389,7 @@ __device__ __forceinline__ void eng_run_range(const EngField& F, const EngState&
                         if (b & 4u)
                             target_edit<NDIM>(pre, F.marks, F.g, F.L, dirty, gr, i + slot_offset(gr, F.dirs_g[i] >> 4),
                                               changed);
-                    },
+                    }),
                     [](int) {});
                 if (lead) acct += 12ull * (hi - lo) + static_cast<unsigned long long>(scanned) * kEngChunk;
                 acct += 16ull * tries + static_cast<unsigned long long>(NS) * changed;
@@ -2084,7 +2405,7 @@ __device__ __forceinline__ void eng_run_range(const EngField& F, const EngState&
                     return F.chunk_unk[c] != 0u || ((F.chunk_cnt[2 * c + (type >> 1)] >> (16 * (type & 1))) & 0xFFFFu);
                 },
                 chunk_counted(F),
-                [&](int i) {
+                each([&](int i) {
                     ++tries;
                     if (type == 0 || type == 3) {
                         edit_vertex<NDIM>(F.g, F.L, dirty, gr, i, changed);
@@ -2093,13 +2414,19 @@ __device__ __forceinline__ void eng_run_range(const EngField& F, const EngState&
                     // FPmin and FNmax targets may be shared
                     const int t = i + slot_offset(gr, type == 1 ? (F.dirs_f[i] & 15u) : (F.dirs_g[i] >> 4));
                     claim_edit<NDIM>(F.marks, F.g, F.L, dirty, gr, t, changed);
-                },
+                }),
                 [](int) {});
             if (lead) acct += 12ull * (hi - lo) + static_cast<unsigned long long>(scanned) * kEngChunk;
             acct += 16ull * tries + static_cast<unsigned long long>(NS) * changed;
             unsigned v[1] = {changed};
             const int idx[1] = {kCntChanged};
             block_add<1>(v, cnt, idx);
+            break;
+        }
+        case kOpSparseC: {  // lists the cases; the step's last block runs the rounds
+            int* list = reinterpret_cast<int*>(smem);
+            const int scanned = sparse_list<NDIM>(F, st.type, lo, hi, sum, list, list + kEngChunk);
+            if (lead) acct += 12ull * (hi - lo) + static_cast<unsigned long long>(scanned) * kEngChunk;
             break;
         }
         case kOpPreE:
@@ -2133,9 +2460,9 @@ __device__ __forceinline__ void eng_run_range(const EngField& F, const EngState&
                 F.dirty, gr.n, lo, hi, 0xFFFFFFFFu, sum, list, list + kEngChunk,
                 [&](int c) { return F.chunk_dirty[c] != 0u; },
                 [&](int c, unsigned, unsigned) { F.chunk_dirty[c] = 0u; },
-                [&](int j) {
-                    refresh_vertex<NDIM>(F, j, sum, c);
-                    ++nv;
+                [&](const int* vs, int np) {
+                    refresh_list<NDIM>(F, np, sum, c, [&](int e) { return vs[e]; }, [](int, unsigned) {});
+                    nv += (np + blockDim.x - 1 - threadIdx.x) / blockDim.x;
                 },
                 [&](int w) {
                     reinterpret_cast<uint4*>(F.dirty)[w] = make_uint4(0u, 0u, 0u, 0u);
@@ -2246,8 +2573,9 @@ __device__ __forceinline__ void stamp_end(unsigned long long* ts, unsigned long 
 // An apply step is followed by a refresh of the vertices around its edits, or
 // by a full pass when so many values changed that streaming the whole field is
 // cheaper (the outcome is the same either way).
+// sparse: the result of a kOpSparseC step.
 __device__ __forceinline__ EngState eng_decide(const EngField& F, EngState st, EngStats* S,
-                                                const unsigned (&c)[kCntSlots]) {
+                                                const unsigned (&c)[kCntSlots], const SparseResult* sparse) {
     auto go = [&](int op) {
         st.op = op;
         st.items = eng_items(F, op);
@@ -2270,17 +2598,27 @@ __device__ __forceinline__ EngState eng_decide(const EngField& F, EngState st, E
         for (int t = 0; t < 4; ++t)
             S->cases[t] = (full ? 0 : S->cases[t]) + static_cast<int>(c[kCntCase + t]);
     };
+    // a C round of the current type, or a run of rounds when few cases are
+    // left (all of them, or those of the type); the preemptive mode, whose
+    // edits race, keeps to rounds
+    auto apply = [&]() {
+        if (S->rounds_total >= F.cap) return finish(MSZ_ENOCONV);
+        const int limit = sparse_limit(F);
+        const bool all = S->cases[0] + S->cases[1] + S->cases[2] + S->cases[3] <= limit;
+        if (F.preempt || !(all || (st.type != kTypeMerged && cases_of(st.type) <= limit))) return go(kOpApplyC);
+        if (all) st.type += kTypeAll;
+        return go(kOpSparseC);
+    };
     // C loop: the current type while it has cases, then the next types in
     // turn, back to FPmax while any of the first three has cases; then labels.
     auto c_decide = [&]() {
         if (F.merged) {  // one type: all of them
             st.type = kTypeMerged;
-            if (S->cases[0] + S->cases[1] + S->cases[2] + S->cases[3] > 0)
-                return S->rounds_total >= F.cap ? finish(MSZ_ENOCONV) : go(kOpApplyC);
+            if (S->cases[0] + S->cases[1] + S->cases[2] + S->cases[3] > 0) return apply();
             return go(kOpRTile);
         }
         for (int guard = 0; guard < 8; ++guard) {
-            if (cases_of(st.type) > 0) return S->rounds_total >= F.cap ? finish(MSZ_ENOCONV) : go(kOpApplyC);
+            if (cases_of(st.type) > 0) return apply();
             if (st.type < 3) {
                 st.type += 1;
             } else if (S->cases[0] + S->cases[1] + S->cases[2] > 0) {
@@ -2327,6 +2665,12 @@ __device__ __forceinline__ EngState eng_decide(const EngField& F, EngState st, E
         case kOpRefreshC:
         case kOpFullC:
             set_cases(st.op == kOpFullC);
+            return c_decide();
+        case kOpSparseC:
+            S->rounds_total += sparse->total;
+            for (int t = 0; t < 4; ++t) S->rounds[t] += sparse->rounds[t], S->cases[t] = sparse->cases[t];
+            st.type = sparse->type;
+            if (sparse->stalled) return finish(MSZ_ESTALL);
             return c_decide();
         case kOpApplyC:
             if (c[kCntChanged] == 0) return finish(MSZ_ESTALL);
@@ -2391,34 +2735,11 @@ __device__ __forceinline__ EngState eng_decide(const EngField& F, EngState st, E
 // items.  tick[f] counts the finished blocks of field f and tick[nf] the
 // decided fields; the block that draws the last ticket resets it.
 //
-// Blocks hand counters, tickets and decided states to each other inside the
-// kernel through device-scope atomics only (every XCD sees one value of each),
-// and a block draws its ticket after its own memory operations have
-// completed: a device-scope fence, which on MI355X writes back the L2 of the
-// XCD, is never needed.  Everything else a step writes is read by later
-// steps, after the kernel boundary.
-__device__ __forceinline__ int ld_dev(const int* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned ld_dev(const unsigned* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_dev(int* p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
-// True in every thread of the block that draws ticket n - 1 of *ticket.
-__device__ __forceinline__ bool draw_last(int* ticket, int n, int* s_flag) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores and atomics have completed
-    __syncthreads();
-    if (threadIdx.x == 0)
-        *s_flag = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
-    __syncthreads();
-    return *s_flag != 0;
-}
-
 // The decision of field F after its step (all its blocks have finished): the
 // 256 threads reduce and clear its counter block, thread 0 runs the schedule.
 __device__ __forceinline__ void decide_field(const EngField& F, const EngState& st, EngStats* stats_f,
-                                             EngState* nxt_f, int* oplog_f, unsigned* part, unsigned* red) {
+                                             EngState* nxt_f, int* oplog_f, const SparseResult* sparse,
+                                             unsigned* part, unsigned* red) {
     unsigned* cnt = F.cnt;
     const int k = threadIdx.x % kCntSlots, s0 = threadIdx.x / kCntSlots;
     constexpr int PER = kSlots / (256 / kCntSlots);
@@ -2443,7 +2764,7 @@ __device__ __forceinline__ void decide_field(const EngField& F, const EngState& 
         EngStats S = *stats_f;
         unsigned c[kCntSlots];
         for (int j = 0; j < kCntSlots; ++j) c[j] = red[j];
-        const EngState ns = eng_decide(F, st, &S, c);
+        const EngState ns = eng_decide(F, st, &S, c, sparse);
         *stats_f = S;
         st_dev(&nxt_f->op, ns.op);
         st_dev(&nxt_f->type, ns.type);
@@ -2504,6 +2825,8 @@ __device__ __forceinline__ void scan_chain(const EngField* __restrict__ fields, 
     }
 }
 
+constexpr int kSparseBatchRounds = 16;  // a step waits for its longest field
+
 template <int NDIM>
 __global__ void __launch_bounds__(256) k_eng_step(const EngField* __restrict__ fields, const EngState* cur,
                                                   EngState* nxt, EngStats* stats, const int* pre, int* pre_next,
@@ -2511,6 +2834,7 @@ __global__ void __launch_bounds__(256) k_eng_step(const EngField* __restrict__ f
                                                   unsigned long long* ts) {
     __shared__ __align__(16) char smem[kEngSmemBytes];
     __shared__ int s_flag;
+    __shared__ SparseResult s_sparse;
     static_assert(3 * DirsGeom<3, 32, 16>::P * sizeof(float) <= sizeof(smem), "stencil planes fit the LDS");
     static_assert(kEngMaxFields * sizeof(long long) <= sizeof(smem), "the chain's units fit the LDS");
     if (ts && blockIdx.x == 0 && threadIdx.x == 0) ts[0] = static_cast<unsigned long long>(wall_clock64());
@@ -2540,8 +2864,16 @@ __global__ void __launch_bounds__(256) k_eng_step(const EngField* __restrict__ f
         const int i0 = static_cast<int>(j * st.items / nbf), i1 = static_cast<int>((j + 1) * st.items / nbf);
         if (i0 < i1) eng_run_range<NDIM, false>(fields[a], st, i0, i1, smem, fields[a].cnt, acct);
         if (draw_last(tick + a, nbf, &s_flag)) {
+            if (st.op == kOpSparseC) {
+                const EngStats* S = stats + a;
+                const int cs[4] = {S->cases[0], S->cases[1], S->cases[2], S->cases[3]};
+                const SparseResult r = sparse_rounds<NDIM>(fields[a], st.type, cs,
+                                                           min(fields[a].cap - S->rounds_total, 1ll * kSparseBatchRounds),
+                                                           false, smem, acct);
+                if (threadIdx.x == 0) s_sparse = r;
+            }
             unsigned* part = reinterpret_cast<unsigned*>(smem);
-            decide_field(fields[a], st, stats + a, nxt + a, oplog ? oplog + step * nf + a : nullptr, part,
+            decide_field(fields[a], st, stats + a, nxt + a, oplog ? oplog + step * nf + a : nullptr, &s_sparse, part,
                          part + 256);
             if (threadIdx.x == 0) st_dev(tick + a, 0);
             if (draw_last(tick + nf, pre[nf + 1], &s_flag)) {
@@ -2577,6 +2909,7 @@ __global__ void __launch_bounds__(256) k_eng_step1(const EngField* __restrict__ 
     __shared__ unsigned red[kCntSlots];
     __shared__ EngState s_next;
     __shared__ EngStats s_stats;
+    __shared__ int s_flag;
     static_assert(kEngTimeSlots % 6 == 0, "parities of 2 and 3 continue across graph launches");
     static_assert(sizeof(EngStats) % 4 == 0 && sizeof(EngStats) / 4 <= 256, "statistics copied word by word");
     if (ts && blockIdx.x == 0 && threadIdx.x == 0) ts[0] = static_cast<unsigned long long>(wall_clock64());
@@ -2622,7 +2955,7 @@ __global__ void __launch_bounds__(256) k_eng_step1(const EngField* __restrict__ 
         if (prev.items > 0 || prev.op == kOpStart) {
             unsigned c[kCntSlots];
             for (int j = 0; j < kCntSlots; ++j) c[j] = red[j];
-            ns = eng_decide(F, prev, &s_stats, c);
+            ns = eng_decide(F, prev, &s_stats, c, &F.sparse->result[p ^ 1]);
         }
         s_next = ns;
         if (blockIdx.x == 0) {
@@ -2653,6 +2986,14 @@ __global__ void __launch_bounds__(256) k_eng_step1(const EngField* __restrict__ 
         const int per = (st.items + nb - 1) / nb;
         const int lo = b * per, hi = min(st.items, lo + per);
         if (lo < hi) eng_run_range<NDIM, true>(F, st, lo, hi, smem, c_cur, acct);
+        if (st.op == kOpSparseC && lo < hi && draw_last(&F.sparse->ticket, (st.items + per - 1) / per, &s_flag)) {
+            const int cs[4] = {s_stats.cases[0], s_stats.cases[1], s_stats.cases[2], s_stats.cases[3]};
+            const SparseResult r = sparse_rounds<NDIM>(F, st.type, cs, F.cap - s_stats.rounds_total, F.sum != 0, smem, acct);
+            if (threadIdx.x == 0) {
+                F.sparse->result[p] = r;
+                st_dev(&F.sparse->ticket, 0);
+            }
+        }
     }
     if (ts) stamp_end(ts, acct);
 }
@@ -2671,6 +3012,7 @@ __global__ void __launch_bounds__(256) k_eng_setup1(const EngField F, EngField* 
         states[0] = EngState{kOpDone, 0, 0, 0};
         states[1] = EngState{kOpStart, 0, 1, 0};
         ctl[0] = 1;
+        F.sparse->count = F.sparse->ticket = 0;
         if (done_word) done_word[0] = 1;
     }
     for (int w = tid; w < 3 * kCntBlockWords; w += nthr) cnt3[w] = 0u;
@@ -2704,6 +3046,7 @@ __global__ void __launch_bounds__(256) k_eng_init(const EngField* __restrict__ f
             cs[w] = make_uint4(0u, 0u, 0u, 0u);
             dt[w] = make_uint4(0u, 0u, 0u, 0u);
         }
+        if (tid == 0) F.sparse->count = F.sparse->ticket = 0;
         const int nc = (F.gr.n + kEngChunk - 1) / kEngChunk;
         for (int c = tid; c < nc; c += nthr) {
             F.chunk_dirty[c] = F.chunk_cnt[2 * c] = F.chunk_cnt[2 * c + 1] = 0u;
