@@ -159,9 +159,14 @@ Layout layout_for(const Grid& gr) {
     l.tile_dirty = take(label_tile_count(gr));
     l.Mf = take(n * 4);
     l.mf = take(n * 4);
-    l.qu = take(n * 4);
-    l.qd = take(n * 4);
-    l.total = o;
+    l.qu = take(n * 2);
+    l.qd = take(n * 2);
+    // The size asked of callers, and with it the limit of msz_fix_noalloc, is
+    // that of four int32 pointer arrays (29 bytes per vertex); fields of a few
+    // hundred vertices need a little more.
+    const size_t chunks = (n + kEngChunk - 1) / kEngChunk, flags = align256((n + 15) & ~int64_t(15));
+    l.total = std::max(o, 6 * align256(n * 4) + 2 * align256(n) + 3 * flags + 2 * align256(chunks * 4) +
+                              align256(chunks * 8) + align256(label_tile_count(gr)));
     return l;
 }
 
@@ -733,8 +738,8 @@ void bind_field(EngField& F, char* w) {
     F.tile_dirty = reinterpret_cast<uint8_t*>(w + l.tile_dirty);
     F.Mf = reinterpret_cast<int*>(w + l.Mf);
     F.mf = reinterpret_cast<int*>(w + l.mf);
-    F.qu = reinterpret_cast<int*>(w + l.qu);
-    F.qd = reinterpret_cast<int*>(w + l.qd);
+    F.qu = reinterpret_cast<uint16_t*>(w + l.qu);
+    F.qd = reinterpret_cast<uint16_t*>(w + l.qd);
 }
 
 void copy_stats(const EngStats& e, bool counted_init, msz_stats* out) {
@@ -914,7 +919,7 @@ int msz_fix(const float* f, const float* fhat, msz_dims d, float xi, float* edit
     F.preempt = (o.flags & MSZ_FLAG_PREEMPTIVE) != 0;
     F.merged = (o.flags & MSZ_FLAG_MERGED_C) != 0 || F.preempt;
     F.count_init = (o.flags & MSZ_FLAG_COUNT_INIT) != 0;
-    F.flabels = 1;
+    F.single = 1;
     F.xi = xi;
     F.cap = o.max_rounds > 0 ? o.max_rounds : (int64_t(1) << 30);
     F.f = f;
@@ -967,7 +972,7 @@ int msz_fix_noalloc(const float* f, const float* fhat, msz_dims d, float xi, flo
     F.preempt = (o.flags & MSZ_FLAG_PREEMPTIVE) != 0;
     F.merged = (o.flags & MSZ_FLAG_MERGED_C) != 0 || F.preempt;
     F.count_init = (o.flags & MSZ_FLAG_COUNT_INIT) != 0;
-    F.flabels = 1;
+    F.single = 1;
     F.xi = xi;
     F.cap = o.max_rounds > 0 ? o.max_rounds : (int64_t(1) << 30);
     F.f = f;
@@ -1050,7 +1055,7 @@ int msz_fix_batch(const msz_job* jobs, int32_t n_jobs, const msz_options* opt, v
         // labels: cheaper than one more full step for every field (a field
         // corrected alone, whose R rounds resolve many labels, resolves them
         // once instead)
-        F.flabels = 0;
+        F.single = 0;
         F.xi = J.xi;
         F.cap = cap;
         F.f = J.f;

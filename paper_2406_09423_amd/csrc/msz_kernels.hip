@@ -7,12 +7,14 @@
 //   marks          uint8[n]   claims of the targets edited in the current round (an
 //                             edit shared by several cases is made once; padded to 16 B)
 //   dirty          uint8[n]   directions to recompute after an apply (padded to 16 B)
-//   M_f, m_f       int32[n]   pointer arrays of f's ascending / descending forests
-//   q_up, q_dn     int32[n]   pointer arrays of g's ascending / descending forests; in
-//                             both pairs a root (extremum) id as itself (>= 0), an exit
-//                             of the vertex's label tile, a vertex e of the next tile on
-//                             its line, as -e-1 (a label is the root at the end of the
-//                             vertex's chain of exits)
+//   q_up, q_dn     uint16[n]  pointers of g's ascending / descending forests after its
+//                             label tile passes: where the vertex's line ends in its label
+//                             tile, or the first vertex past the tile, as a position in the
+//                             tile's box with a one-vertex halo (TileCode)
+//   M_f, m_f       a field corrected alone: int32[n] labels of f (before that the pointers
+//                             of its forests: a root id as itself, an exit e of the tile as
+//                             -e-1); a batch field: uint16[n] pointers of f like q_up, q_dn
+//                             (a label is the root at the end of a vertex's chain of exits)
 //   tile_dirty     uint8      per label tile: a direction of g in it changed since its
 //                             last tile pass
 //   cnt            uint32[kSlots][kSlotStride] round counters; block b adds into slot
@@ -727,20 +729,50 @@ __host__ __device__ __forceinline__ int label_tiles_of(const Grid& gr) {
     return ((gr.nx + T::X - 1) / T::X) * ((gr.ny + T::Y - 1) / T::Y) * ((gr.nz + T::Z - 1) / T::Z);
 }
 
-// Pointer codes of the tile pass while it runs: an id (an extremum of the
-// grid, >= 0 and below kLocalCode), an exit -e-1 (negative), or the in-tile
-// vertex with local index l as kLocalCode + 4 l (its byte offset in the LDS
-// arrays).  Ids stay below 2^31 - 2^16, so the codes never meet, and a
-// finished pointer is stored as it is.
-constexpr int kLocalCode = 0x7FFFC000;
+// A pointer that ends a vertex's line inside its label tile, in 16 bits: the
+// position of the vertex it names -- the extremum the line reaches, or the
+// first vertex past the tile -- in the tile's box with a one-vertex halo, and
+// whether it is past the tile.  Half the bytes of an id: the tile pass writes
+// 4 bytes per vertex for both forests, and a line of memory serves twice the
+// troublemaker pass's gathers.
+template <int NDIM>
+struct TileCode {
+    using T = LabelTile<NDIM>;
+    static constexpr int HX = T::X + 2, HXY = HX * (T::Y + 2);
+    static constexpr unsigned kPos = 0x1FFFu, kExit = 0x4000u, kDone = 0x8000u;  // kDone: a finished pointer
+    static_assert((NDIM == 3 ? HXY * (T::Z + 2) : HXY) <= 0x2000, "positions fit 13 bits");
+    __device__ __forceinline__ static int of(int lx, int ly, int lz) {
+        return lx + 1 + HX * (ly + 1) + (NDIM == 3 ? HXY * (lz + 1) : 0);
+    }
+    // id of position 0 (outside the grid for the first tiles) of the tile at
+    // the origin (X0, Y0, Z0); unsigned, so that it may wrap
+    __device__ __forceinline__ static unsigned corner(const Grid& gr, int X0, int Y0, int Z0) {
+        return static_cast<unsigned>(X0 - 1) + static_cast<unsigned>(gr.nx) * static_cast<unsigned>(Y0 - 1) +
+               (NDIM == 3 ? static_cast<unsigned>(gr.nxy) * static_cast<unsigned>(Z0 - 1) : 0u);
+    }
+    // the vertex that code c of a vertex of that tile names: a root as its id, an exit e as -e-1
+    __device__ __forceinline__ static int target(const Grid& gr, unsigned corner, unsigned c) {
+        const unsigned p = c & kPos;
+        const unsigned pz = NDIM == 3 ? p / HXY : 0u, r = p - pz * HXY, py = r / HX, px = r - py * HX;
+        const unsigned id = corner + px + static_cast<unsigned>(gr.nx) * py + static_cast<unsigned>(gr.nxy) * pz;
+        return static_cast<int>((c & kExit) ? ~id : id);
+    }
+    // the same for the code c of vertex i, in whatever tile that is
+    __device__ __forceinline__ static int hop(const Grid& gr, int i, unsigned c) {
+        int x, y, z;
+        coords<NDIM>(gr, i, x, y, z);
+        return target(gr, corner(gr, x & ~(T::X - 1), y & ~(T::Y - 1), NDIM == 3 ? z & ~(T::Z - 1) : 0), c);
+    }
+};
 
 // What a slot means inside a label tile: the step in the packed coordinates
-// of tile_pos, in local codes, and the code of a target outside the tile,
-// (i ^ flip) + step_id for a vertex i.  One 16-byte LDS read per pointer
+// of TilePos, in local pointers (2 l for the vertex with local index l, its
+// byte offset in the LDS arrays), and in TileCode positions with the flags of
+// a pointer that leaves the tile there.  One 16-byte LDS read per pointer
 // replaces decoding the slot's three components and testing each against the
 // tile's box.
 struct __align__(16) SlotStep {
-    int pos, local, flip, id;
+    int pos, local, code, pad;
 };
 
 // Local coordinates packed so that a step out of the tile shows in one mask:
@@ -763,23 +795,23 @@ struct TilePos {
 // Fills the 16 entries of a block's slot table; the caller puts a barrier
 // between this and the first label_tile_body.
 template <int NDIM>
-__device__ __forceinline__ void fill_slot_steps(const Grid& gr, SlotStep* tab) {
+__device__ __forceinline__ void fill_slot_steps(SlotStep* tab) {
     using T = LabelTile<NDIM>;
     using P = TilePos<NDIM>;
+    using C = TileCode<NDIM>;
     if (threadIdx.x < 16) {
         int dx, dy, dz;
         slot_delta(threadIdx.x, dx, dy, dz);
         SlotStep s;
+        s.pad = 0;
         if (threadIdx.x < 14) {
             s.pos = dx + dy * (1 << P::SY) + (NDIM == 3 ? dz * (1 << P::SZ) : 0);
-            s.local = 4 * (dx + T::X * (dy + T::Y * dz));
-            s.flip = -1;  // -(i + off) - 1 = ~i - off
-            s.id = -(dx + gr.nx * dy + gr.nxy * dz);
-        } else {  // the vertex itself: never inside (a step of X reads 10), its id
+            s.local = 2 * (dx + T::X * (dy + T::Y * dz));
+            s.code = static_cast<int>(C::kDone | C::kExit) + dx + C::HX * dy + (NDIM == 3 ? C::HXY * dz : 0);
+        } else {  // the vertex itself: never inside (a step of X reads 10), an extremum
             s.pos = T::X;
             s.local = 0;
-            s.flip = 0;
-            s.id = 0;
+            s.code = static_cast<int>(C::kDone);
         }
         tab[threadIdx.x] = s;
     }
@@ -787,16 +819,15 @@ __device__ __forceinline__ void fill_slot_steps(const Grid& gr, SlotStep* tab) {
 
 // Follows K chains of exits from stored pointers y[k] to their roots, one
 // level per pass, so that the gathers of a pass are in flight together (y[k]
-// in q_up when k is even, in q_dn when odd; entries already >= 0 stay).  With
-// S < K, the entries from S on belong to a second forest, r_up / r_dn, whose
-// chains are followed in the same passes.  Every chain of the forest ends at
-// an extremum within finitely many tiles.  hops counts the gathers; the pass
-// cap only guards against corrupted input and sets bad.
+// in q_up when k is even, in q_dn when odd; entries already >= 0 stay; arrays
+// of ids).  Every chain of the forest ends at an extremum within finitely many
+// tiles.  hops counts the gathers; the pass cap only guards against corrupted
+// input and sets bad.
 constexpr int kMaxChain = 1 << 20;
 
-template <int K, int S = K>
+template <int K>
 __device__ __forceinline__ void follow_roots(const int* q_up, const int* q_dn, int (&y)[K], unsigned& bad,
-                                             unsigned& hops, const int* r_up = nullptr, const int* r_dn = nullptr) {
+                                             unsigned& hops) {
     for (int pass = 0;; ++pass) {
         bool any = false;
 #pragma unroll
@@ -812,8 +843,7 @@ __device__ __forceinline__ void follow_roots(const int* q_up, const int* q_dn, i
         // the whole wave), so that all K are issued before the first wait
         int z[K];
 #pragma unroll
-        for (int k = 0; k < K; ++k)
-            z[k] = (k < S ? ((k & 1) ? q_dn : q_up) : ((k & 1) ? r_dn : r_up))[y[k] < 0 ? -y[k] - 1 : 0];
+        for (int k = 0; k < K; ++k) z[k] = ((k & 1) ? q_dn : q_up)[y[k] < 0 ? -y[k] - 1 : 0];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             hops += y[k] < 0;
@@ -822,24 +852,53 @@ __device__ __forceinline__ void follow_roots(const int* q_up, const int* q_dn, i
     }
 }
 
+// The same over arrays of TileCodes, chain k in forest q[k].
+template <int NDIM, int K>
+__device__ __forceinline__ void follow_codes(const Grid& gr, const uint16_t* const (&q)[K], int (&y)[K], unsigned& bad,
+                                             unsigned& hops) {
+    for (int pass = 0;; ++pass) {
+        bool any = false;
+#pragma unroll
+        for (int k = 0; k < K; ++k) any |= y[k] < 0;
+        if (!any) return;
+        if (pass == kMaxChain) {
+            bad = kErrWalk;
+#pragma unroll
+            for (int k = 0; k < K; ++k) y[k] = max(y[k], 0);
+            return;
+        }
+        unsigned z[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) z[k] = q[k][y[k] < 0 ? -y[k] - 1 : 0];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            hops += y[k] < 0;
+            if (y[k] < 0) y[k] = TileCode<NDIM>::hop(gr, -y[k] - 1, z[k]);
+        }
+    }
+}
+
 // One label tile; su, sd: LDS arrays of the tile's vertex count; tab: the
 // block's slot table (fill_slot_steps).  The caller separates consecutive
-// tiles of one block with a barrier.
+// tiles of one block with a barrier.  Out: uint16_t stores TileCodes, int
+// the pointers as ids (a root as itself, an exit e as -e-1).
 //
 // Thread t owns the 4-vertex row groups starting at l = 4 t + 1024 k and
 // keeps their pointers in registers; the LDS copy is what other threads read.
 //
-// The pass streams 1 byte in and 8 out per vertex, but was bound by
-// instruction issue (building the two first pointers of a vertex and turning
-// the terminals into ids took most of its instructions).  With the slot table
-// and codes that need no conversion at the end the pass over 256^3 takes
-// 40.6 us where it took 74.2 (3.7 TB/s, was 2.0; a large copy reaches 5.1).
-template <int NDIM>
+// The pass was bound by instruction issue (building the two first pointers of
+// a vertex and turning the terminals into ids took most of its
+// instructions).  With the slot table, and terminals that need no conversion
+// at the end, the ids of 256^3 take 44 us where they took 74 (3.4 TB/s; a large
+// copy reaches 5.1), and the codes of 512^3, half the bytes, 306 us where its
+// ids took 378 with the table and 584 without.
+template <int NDIM, typename Out>
 __device__ __forceinline__ void label_tile_body(const uint8_t* __restrict__ dirs, const Grid& gr, int tile,
-                                                int* __restrict__ q_up, int* __restrict__ q_dn, int* su, int* sd,
-                                                const SlotStep* tab) {
+                                                Out* __restrict__ q_up, Out* __restrict__ q_dn, uint16_t* su,
+                                                uint16_t* sd, const SlotStep* tab) {
     using T = LabelTile<NDIM>;
     using P = TilePos<NDIM>;
+    using C = TileCode<NDIM>;
     constexpr int NT = T::X * T::Y * T::Z;
     constexpr int G = NT / 1024;  // row groups per thread
 
@@ -858,7 +917,7 @@ __device__ __forceinline__ void label_tile_body(const uint8_t* __restrict__ dirs
         const int xa = X0 + lx0, y = Y0 + ly, z = Z0 + lz;
         const bool row_in = y < gr.ny && z < gr.nz;
         const int i0 = xa + gr.nx * y + gr.nxy * z;
-        d4[k] = 0xFFFFFFFFu;
+        d4[k] = 0xFFFFFFFFu;  // a vertex outside the grid: nothing points at it and nothing stores it
         if (row_in && vec4 && xa + 3 < gr.nx) {
             d4[k] = *reinterpret_cast<const unsigned*>(dirs + i0);
         } else if (row_in) {
@@ -868,68 +927,81 @@ __device__ __forceinline__ void label_tile_body(const uint8_t* __restrict__ dirs
                     d4[k] = (d4[k] & ~(0xFFu << (8 * j))) | (static_cast<unsigned>(dirs[i0 + j]) << (8 * j));
         }
     }
+    auto publish = [&](uint16_t* dst, const int (&p)[4]) {
+        *reinterpret_cast<uint2*>(dst) = make_uint2(static_cast<unsigned>(p[0]) | (static_cast<unsigned>(p[1]) << 16),
+                                                    static_cast<unsigned>(p[2]) | (static_cast<unsigned>(p[3]) << 16));
+    };
 #pragma unroll
     for (int k = 0; k < G; ++k) {
         const int l0 = 4 * threadIdx.x + 1024 * k;
         const int lx0 = l0 % T::X, ly = (l0 / T::X) % T::Y, lz = l0 / (T::X * T::Y);
-        const int xa = X0 + lx0, y = Y0 + ly, z = Z0 + lz;
-        const bool row_in = y < gr.ny && z < gr.nz;
-        // a group outside the grid counts from 0: its codes are ids that
-        // nothing points at and nothing stores
-        const int i0 = row_in && xa < gr.nx ? xa + gr.nx * y + gr.nxy * z : 0;
-        const int pos0 = P::of(lx0, ly, lz);
+        const int pos0 = P::of(lx0, ly, lz), code0 = C::of(lx0, ly, lz);
         const unsigned du = d4[k], dd = d4[k] << 4;  // a slot's table offset: its nibble times 16
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const SlotStep tu = *reinterpret_cast<const SlotStep*>(reinterpret_cast<const char*>(tab) + ((du >> (8 * j)) & 0xF0u));
             const SlotStep td = *reinterpret_cast<const SlotStep*>(reinterpret_cast<const char*>(tab) + ((dd >> (8 * j)) & 0xF0u));
-            const int i = i0 + j, local = kLocalCode + 4 * (l0 + j);
-            pu[k][j] = P::inside(pos0 + j + tu.pos) ? local + tu.local : (i ^ tu.flip) + tu.id;
-            pd[k][j] = P::inside(pos0 + j + td.pos) ? local + td.local : (i ^ td.flip) + td.id;
+            pu[k][j] = P::inside(pos0 + j + tu.pos) ? 2 * (l0 + j) + tu.local : code0 + j + tu.code;
+            pd[k][j] = P::inside(pos0 + j + td.pos) ? 2 * (l0 + j) + td.local : code0 + j + td.code;
         }
-        *reinterpret_cast<int4*>(su + l0) = make_int4(pu[k][0], pu[k][1], pu[k][2], pu[k][3]);
-        *reinterpret_cast<int4*>(sd + l0) = make_int4(pd[k][0], pd[k][1], pd[k][2], pd[k][3]);
+        publish(su + l0, pu[k]);
+        publish(sd + l0, pd[k]);
     }
     __syncthreads();
     // Pointer jumping in LDS: each thread replaces each of its non-terminal
     // pointers by the pointer stored at its target, then publishes a group's
-    // four entries with one 16-byte write.  Any entry read is an ancestor of
+    // four entries with one 8-byte write.  Any entry read is an ancestor of
     // the reader on its integral line (entries only ever move up their
     // forest), so no barrier is needed between jumps and every jump makes
     // progress; a pointer needs at most one jump per vertex of its in-tile
     // path.  A group is skipped once the whole wave's copies of it are
     // terminal; otherwise its eight reads are issued together, branch-free
     // (a terminal pointer reads entry 0 and keeps its value).
-    const char* bu = reinterpret_cast<const char*>(su);
-    const char* bd = reinterpret_cast<const char*>(sd);
-    auto max8 = [](const int (&a)[4], const int (&b)[4]) {
-        return max(max(max(a[0], a[1]), max(a[2], a[3])), max(max(b[0], b[1]), max(b[2], b[3])));
+    constexpr int kDone = static_cast<int>(C::kDone);
+    auto at = [](const uint16_t* a, int p) {
+        return static_cast<int>(*reinterpret_cast<const uint16_t*>(reinterpret_cast<const char*>(a) + p));
+    };
+    auto least = [](const int (&a)[4], const int (&b)[4]) {
+        return min(min(min(a[0], a[1]), min(a[2], a[3])), min(min(b[0], b[1]), min(b[2], b[3])));
     };
     for (int iter = 0; iter < NT; ++iter) {
-        int top = 0;
+        int low = kDone;
 #pragma unroll
         for (int k = 0; k < G; ++k) {
-            if (!__any(max8(pu[k], pd[k]) >= kLocalCode)) continue;
+            if (!__any(least(pu[k], pd[k]) < kDone)) continue;
             int nu[4], nd[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                nu[j] = *reinterpret_cast<const int*>(bu + (max(pu[k][j], kLocalCode) & 0x3FFC));
-                nd[j] = *reinterpret_cast<const int*>(bd + (max(pd[k][j], kLocalCode) & 0x3FFC));
+                nu[j] = at(su, pu[k][j] < kDone ? pu[k][j] : 0);
+                nd[j] = at(sd, pd[k][j] < kDone ? pd[k][j] : 0);
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                pu[k][j] = pu[k][j] >= kLocalCode ? nu[j] : pu[k][j];
-                pd[k][j] = pd[k][j] >= kLocalCode ? nd[j] : pd[k][j];
+                pu[k][j] = pu[k][j] < kDone ? nu[j] : pu[k][j];
+                pd[k][j] = pd[k][j] < kDone ? nd[j] : pd[k][j];
             }
-            top = max(top, max8(pu[k], pd[k]));
+            low = min(low, least(pu[k], pd[k]));
             const int l0 = 4 * threadIdx.x + 1024 * k;
-            *reinterpret_cast<int4*>(su + l0) = make_int4(pu[k][0], pu[k][1], pu[k][2], pu[k][3]);
-            *reinterpret_cast<int4*>(sd + l0) = make_int4(pd[k][0], pd[k][1], pd[k][2], pd[k][3]);
+            publish(su + l0, pu[k]);
+            publish(sd + l0, pd[k]);
         }
-        if (top < kLocalCode) break;
+        if (low >= kDone) break;
     }
     // Every in-tile path is shorter than the tile, so all pointers are
-    // terminal here: ids and exit codes.
+    // terminal here.
+    const unsigned corner = C::corner(gr, X0, Y0, Z0);
+    auto store4 = [&](Out* q, const int (&p)[4]) {
+        if constexpr (sizeof(Out) == 2) {
+            publish(q, p);
+        } else {
+            *reinterpret_cast<int4*>(q) = make_int4(C::target(gr, corner, p[0]), C::target(gr, corner, p[1]),
+                                                    C::target(gr, corner, p[2]), C::target(gr, corner, p[3]));
+        }
+    };
+    auto store1 = [&](Out* q, int p) {
+        if constexpr (sizeof(Out) == 2) *q = static_cast<uint16_t>(p);
+        else *q = C::target(gr, corner, p);
+    };
 #pragma unroll
     for (int k = 0; k < G; ++k) {
         const int l0 = 4 * threadIdx.x + 1024 * k;
@@ -938,16 +1010,14 @@ __device__ __forceinline__ void label_tile_body(const uint8_t* __restrict__ dirs
         if (y >= gr.ny || z >= gr.nz) continue;
         const int i0 = xa + gr.nx * y + gr.nxy * z;
         if (vec4 && xa + 3 < gr.nx) {
-            *reinterpret_cast<int4*>(q_up + i0) =
-                make_int4(pu[k][0], pu[k][1], pu[k][2], pu[k][3]);
-            *reinterpret_cast<int4*>(q_dn + i0) =
-                make_int4(pd[k][0], pd[k][1], pd[k][2], pd[k][3]);
+            store4(q_up + i0, pu[k]);
+            store4(q_dn + i0, pd[k]);
         } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 if (xa + j < gr.nx) {
-                    q_up[i0 + j] = pu[k][j];
-                    q_dn[i0 + j] = pd[k][j];
+                    store1(q_up + i0 + j, pu[k][j]);
+                    store1(q_dn + i0 + j, pd[k][j]);
                 }
         }
     }
@@ -958,10 +1028,10 @@ __global__ void __launch_bounds__(256) k_label_tile(const uint8_t* __restrict__ 
                                                     int* __restrict__ q_up,
                                                     int* __restrict__ q_dn) {
     constexpr int NT = LabelTile<NDIM>::X * LabelTile<NDIM>::Y * LabelTile<NDIM>::Z;
-    __shared__ __align__(16) int su[NT];
-    __shared__ __align__(16) int sd[NT];
+    __shared__ __align__(16) uint16_t su[NT];
+    __shared__ __align__(16) uint16_t sd[NT];
     __shared__ __align__(16) SlotStep tab[16];
-    fill_slot_steps<NDIM>(gr, tab);
+    fill_slot_steps<NDIM>(tab);
     __syncthreads();
     label_tile_body<NDIM>(dirs, gr, xcd_logical_block(blockIdx.x, gridDim.x), q_up, q_dn, su, sd, tab);
 }
@@ -1211,128 +1281,51 @@ struct TargetList {
     }
 };
 
-// Troublemakers of one tile (Sec. 5.2).  Only a vertex whose direction in g
-// differs from f's (each family apart) can be one, so only such vertices
-// have their labels resolved -- their pointers in g's and f's forests (Mf,
-// mf hold f's tile pointers) loaded and both exit chains followed; the rest
-// of the tile costs its two direction bytes per vertex.  Mislabelled vertices need not be counted for the loop:
-// one exists exactly when a troublemaker of its family does (on the steepest
-// path in g of a mislabelled vertex, the first vertex whose direction
-// differs from f's carries the same labels in g and in f), so the
-// troublemaker count ends the R loop alike.  With full set, every vertex's
-// labels are resolved and the mislabelled ones counted in wrong (the start
-// field's count; the loop's rounds use detect_r_tile_sparse, below).  bytes
-// receives the algorithmic bytes of the loads.
-template <int NDIM>
-__device__ __forceinline__ void detect_r_tile(const uint8_t* __restrict__ dirs_f, const uint8_t* __restrict__ dirs_g,
-                                              const int* __restrict__ q_up, const int* __restrict__ q_dn,
-                                              const int* __restrict__ Mf, const int* __restrict__ mf, const Grid& gr,
-                                              int tile, bool full, bool flabels, const TargetList& tl, unsigned& wrong,
-                                              unsigned& cases, unsigned& changed, unsigned& bad, unsigned& hops,
-                                              unsigned long long& bytes) {
-    constexpr int G = LabelTile<NDIM>::X * LabelTile<NDIM>::Y * LabelTile<NDIM>::Z / 1024;
-    static_assert(G == 4, "four row groups per thread");
-    // every direction word of the tile first, all in flight together (kept
-    // in named registers: the group loop below is not unrolled, and an array
-    // indexed by its counter would go to private memory)
-    unsigned w[2 * G];
-#pragma unroll
-    for (int k = 0; k < G; ++k) {
-        const TileGroup<NDIM> t = tile_group<NDIM>(gr, tile, k);
-        unsigned a = 0u, b = 0u;
-        if (t.vec) {
-            a = *reinterpret_cast<const unsigned*>(dirs_f + t.i0);
-            b = *reinterpret_cast<const unsigned*>(dirs_g + t.i0);
-        } else {
-            for (int j = 0; j < t.count; ++j) {
-                a |= static_cast<unsigned>(dirs_f[t.i0 + j]) << (8 * j);
-                b |= static_cast<unsigned>(dirs_g[t.i0 + j]) << (8 * j);
-            }
-        }
-        w[2 * k] = a;
-        w[2 * k + 1] = b;
-    }
-    const unsigned f0 = w[0], g0 = w[1], f1 = w[2], g1 = w[3], f2 = w[4], g2 = w[5], f3 = w[6], g3 = w[7];
+// f's side of the troublemaker passes: its labels (int32, resolved once before
+// the loop: a field corrected alone), or the pointers of its forests (TileCode,
+// a batch field), whose chains are followed where a label is needed.
+struct Forests {
+    const uint16_t *q_up, *q_dn;  // g's
+    const void *Mf, *mf;          // f's
+};
+template <int NDIM, bool FLABELS>
+__device__ __forceinline__ int f_pointer(const Grid& gr, const void* a, int i, unsigned corner) {
+    if constexpr (FLABELS) return static_cast<const int*>(a)[i];
+    else return TileCode<NDIM>::target(gr, corner, static_cast<const uint16_t*>(a)[i]);
+}
+
+// Mislabelled vertices of one tile (the start field's count): every vertex's
+// labels in g and f are resolved.  bytes receives the algorithmic bytes.
+template <int NDIM, bool FLABELS>
+__device__ __forceinline__ void count_wrong_tile(const Forests& fo, const Grid& gr, int tile, unsigned& wrong,
+                                                 unsigned& bad, unsigned& hops, unsigned long long& bytes) {
+    using C = TileCode<NDIM>;
+    const int3 o = tile_origin<NDIM>(gr, tile);
+    const unsigned corner = C::corner(gr, o.x, o.y, o.z);
 #pragma unroll 1
-    for (int k = 0; k < G; ++k) {
-        const unsigned dfw = k == 0 ? f0 : k == 1 ? f1 : k == 2 ? f2 : f3;
-        const unsigned dgw = k == 0 ? g0 : k == 1 ? g1 : k == 2 ? g2 : g3;
-        // bit j: vertex j's ascent (dup) / descent (ddn) differs (bytes past
-        // the group's count are equal zeros); up, dn: the labels to resolve
-        const unsigned x = dfw ^ dgw;
-        unsigned dup = 0, ddn = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            dup |= ((x >> (8 * j + 4)) & 15u) ? 1u << j : 0u;
-            ddn |= ((x >> (8 * j)) & 15u) ? 1u << j : 0u;
-        }
+    for (int k = 0; k < 4; ++k) {
         const TileGroup<NDIM> t = tile_group<NDIM>(gr, tile, k);
-        const unsigned all = (1u << t.count) - 1u;
-        const unsigned up = full ? all : dup, dn = full ? all : ddn;
-        if (!__any(up | dn)) continue;
-        const int i0 = t.i0;
-        // pointers and f's labels of the differing vertices (int4 lanes x..w
-        // are the group's vertices 0..3; no arrays, which would be indexed
-        // at run time in the scalar path and go to private memory)
-        int4 u = make_int4(0, 0, 0, 0), U = u, d = u, D = u;
-        if (t.vec) {
-            if (up) {
-                u = *reinterpret_cast<const int4*>(q_up + i0);
-                U = *reinterpret_cast<const int4*>(Mf + i0);
-                bytes += 32;
-            }
-            if (dn) {
-                d = *reinterpret_cast<const int4*>(q_dn + i0);
-                D = *reinterpret_cast<const int4*>(mf + i0);
-                bytes += 32;
-            }
-        } else {  // bits past the count are clear
-            if (up & 1u) u.x = q_up[i0], U.x = Mf[i0];
-            if (up & 2u) u.y = q_up[i0 + 1], U.y = Mf[i0 + 1];
-            if (up & 4u) u.z = q_up[i0 + 2], U.z = Mf[i0 + 2];
-            if (up & 8u) u.w = q_up[i0 + 3], U.w = Mf[i0 + 3];
-            if (dn & 1u) d.x = q_dn[i0], D.x = mf[i0];
-            if (dn & 2u) d.y = q_dn[i0 + 1], D.y = mf[i0 + 1];
-            if (dn & 4u) d.z = q_dn[i0 + 2], D.z = mf[i0 + 2];
-            if (dn & 8u) d.w = q_dn[i0 + 3], D.w = mf[i0 + 3];
-            bytes += 8 * (__popc(up) + __popc(dn));
-        }
-        // chains of the differing directions only (0: nothing to follow) in
-        // g's forest, then f's labels along f's chains (entries 8..15): with
-        // f's labels resolved (flabels) they are roots already; else both
-        // forests' chains are followed in the same passes
-        int y[16] = {(up & 1u) ? u.x : 0, (dn & 1u) ? d.x : 0, (up & 2u) ? u.y : 0, (dn & 2u) ? d.y : 0,
-                     (up & 4u) ? u.z : 0, (dn & 4u) ? d.z : 0, (up & 8u) ? u.w : 0, (dn & 8u) ? d.w : 0,
-                     (up & 1u) ? U.x : 0, (dn & 1u) ? D.x : 0, (up & 2u) ? U.y : 0, (dn & 2u) ? D.y : 0,
-                     (up & 4u) ? U.z : 0, (dn & 4u) ? D.z : 0, (up & 8u) ? U.w : 0, (dn & 8u) ? D.w : 0};
-        if (flabels) {
-            int yg[8] = {y[0], y[1], y[2], y[3], y[4], y[5], y[6], y[7]};
-            int yf[8] = {y[8], y[9], y[10], y[11], y[12], y[13], y[14], y[15]};
-            follow_roots<8>(q_up, q_dn, yg, bad, hops);
-            follow_roots<8>(Mf, mf, yf, bad, hops);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) y[k] = yg[k], y[8 + k] = yf[k];
-        } else {
-            follow_roots<16, 8>(q_up, q_dn, y, bad, hops, Mf, mf);
-        }
-        const int Ms[4] = {y[8], y[10], y[12], y[14]}, ms[4] = {y[9], y[11], y[13], y[15]};
-        int tn[4], tx[4], nloc = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            tn[j] = tx[j] = -1;
-            const int i = i0 + j;
-            const unsigned df = (dfw >> (8 * j)) & 0xFFu, dg = (dgw >> (8 * j)) & 0xFFu;
-            const bool wM = ((up >> j) & 1u) && y[2 * j] != Ms[j];
-            const bool wm = ((dn >> j) & 1u) && y[2 * j + 1] != ms[j];
-            wrong += wM || wm;  // all resolved only when full
-            const bool rmax = wM && ((dup >> j) & 1u);
-            const bool rmin = wm && ((ddn >> j) & 1u);
-            cases += rmin + rmax;
-            nloc += rmin + rmax;
-            if (rmin) tn[j] = i + slot_offset(gr, df & 15u);
-            if (rmax) tx[j] = i + slot_offset(gr, dg >> 4);
+            int y[4] = {0, 0, 0, 0};  // g's ascent and descent, f's
+            if (j < t.count) {
+                const int i = t.i0 + j;
+                y[0] = C::target(gr, corner, fo.q_up[i]), y[1] = C::target(gr, corner, fo.q_dn[i]);
+                y[2] = f_pointer<NDIM, FLABELS>(gr, fo.Mf, i, corner), y[3] = f_pointer<NDIM, FLABELS>(gr, fo.mf, i, corner);
+                bytes += FLABELS ? 12 : 8;
+            }
+            if constexpr (FLABELS) {
+                const uint16_t* const q[2] = {fo.q_up, fo.q_dn};
+                int yg[2] = {y[0], y[1]};
+                follow_codes<NDIM, 2>(gr, q, yg, bad, hops);
+                y[0] = yg[0], y[1] = yg[1];
+            } else {
+                const uint16_t* const q[4] = {fo.q_up, fo.q_dn, static_cast<const uint16_t*>(fo.Mf),
+                                              static_cast<const uint16_t*>(fo.mf)};
+                follow_codes<NDIM, 4>(gr, q, y, bad, hops);
+            }
+            wrong += y[0] != y[2] || y[1] != y[3];
         }
-        if (tl.list) tl.add_wave<NDIM>(gr, tn, tx, nloc, changed);
     }
 }
 
@@ -1347,25 +1340,36 @@ __device__ __forceinline__ int tile_vertex(const Grid& gr, int tile, int l) {
     return x + gr.nx * y + gr.nxy * z;
 }
 
-// The troublemakers of one tile as detect_r_tile finds them without full, in
-// two phases: the vertices whose ascent (descent) differs are listed in LDS
+// Troublemakers of one tile (Sec. 5.2).  Only a vertex whose direction in g
+// differs from f's (each family apart) can be one, so only such vertices have
+// their labels resolved -- their pointers in g's and f's forests loaded and
+// the exit chains followed; the rest of the tile costs its two direction bytes
+// per vertex.  Mislabelled vertices need not be counted for the loop: one
+// exists exactly when a troublemaker of its family does (on the steepest path
+// in g of a mislabelled vertex, the first vertex whose direction differs from
+// f's carries the same labels in g and in f), so the troublemaker count ends
+// the R loop alike.
+//
+// Two phases: the vertices whose ascent (descent) differs are listed in LDS
 // first (cand_up / cand_dn, 4096 entries each: the tile-local index in bits
 // 0..11 and the slot of the target's direction -- g's ascent, f's descent --
 // in bits 12..15; *s_n counts them, ascents in its low and descents in its
 // high 16 bits, and is 0 on entry and on return), then resolved four per
 // thread, every walk of a round in flight together.  A wave then waits for
 // one round of pointer loads and walks per 1024 listed vertices of the tile
-// instead of one per row group it holds.
-template <int NDIM>
+// instead of one per row group it holds.  Bound by whole-line fetches around
+// the scattered pointers and chains: 512^3, whose later rounds list 5 million
+// directions, takes 320 to 390 us a round (1080 the first, with 33 million);
+// with id pointers 330 to 430 (1160).
+template <int NDIM, bool FLABELS>
 __device__ __forceinline__ void detect_r_tile_sparse(const uint8_t* __restrict__ dirs_f,
-                                                     const uint8_t* __restrict__ dirs_g,
-                                                     const int* __restrict__ q_up, const int* __restrict__ q_dn,
-                                                     const int* __restrict__ Mf, const int* __restrict__ mf,
+                                                     const uint8_t* __restrict__ dirs_g, const Forests& fo,
                                                      const Grid& gr, int tile, const TargetList& tl,
                                                      unsigned short* cand_up, unsigned short* cand_dn, unsigned* s_n,
                                                      unsigned& cases, unsigned& changed, unsigned& bad,
                                                      unsigned& hops, unsigned long long& bytes) {
     using T = LabelTile<NDIM>;
+    using C = TileCode<NDIM>;
     constexpr int G = T::X * T::Y * T::Z / 1024;
     static_assert(G == 4 && T::X * T::Y * T::Z == 4096, "4096 vertices, four row groups per thread");
     unsigned w[2 * G];
@@ -1416,6 +1420,8 @@ __device__ __forceinline__ void detect_r_tile_sparse(const uint8_t* __restrict__
         }
     }
     __syncthreads();
+    const int3 o = tile_origin<NDIM>(gr, tile);
+    const unsigned corner = C::corner(gr, o.x, o.y, o.z);
     const unsigned nn = *s_n;
     const int nu = static_cast<int>(nn & 0xFFFFu), n = nu + static_cast<int>(nn >> 16);
     for (int b0 = 0; b0 < n; b0 += 4 * static_cast<int>(blockDim.x)) {  // block-uniform rounds
@@ -1430,35 +1436,27 @@ __device__ __forceinline__ void detect_r_tile_sparse(const uint8_t* __restrict__
             code[e] = ok[e] ? (dn[e] ? cand_dn[idx - nu] : cand_up[idx]) : 0u;
             vi[e] = ok[e] ? tile_vertex<NDIM>(gr, tile, static_cast<int>(code[e] & 4095u)) : 0;
         }
+        unsigned cg[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {  // g's tile pointer and f's (a label when f's are resolved)
-            yg[e] = ok[e] ? (dn[e] ? q_dn : q_up)[vi[e]] : 0;
-            yf[e] = ok[e] ? (dn[e] ? mf : Mf)[vi[e]] : 0;
-        }
-        // both walks of every entry, one gather level per pass
-        for (int pass = 0;; ++pass) {
-            bool any = false;
+        for (int e = 0; e < 4; ++e) cg[e] = ok[e] ? (dn[e] ? fo.q_dn : fo.q_up)[vi[e]] : 0u;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) any |= (yg[e] < 0) | (yf[e] < 0);
-            if (!any) break;
-            if (pass == kMaxChain) {
-                bad = kErrWalk;
+        for (int e = 0; e < 4; ++e) yf[e] = ok[e] ? f_pointer<NDIM, FLABELS>(gr, dn[e] ? fo.mf : fo.Mf, vi[e], corner) : 0;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) yg[e] = max(yg[e], 0), yf[e] = max(yf[e], 0);
-                break;
-            }
-            int zg[4], zf[4];
+        for (int e = 0; e < 4; ++e) yg[e] = ok[e] ? C::target(gr, corner, cg[e]) : 0;
+        // the walks of every entry, one gather level per pass
+        if constexpr (FLABELS) {
+            const uint16_t* const q[4] = {dn[0] ? fo.q_dn : fo.q_up, dn[1] ? fo.q_dn : fo.q_up,
+                                          dn[2] ? fo.q_dn : fo.q_up, dn[3] ? fo.q_dn : fo.q_up};
+            follow_codes<NDIM, 4>(gr, q, yg, bad, hops);
+        } else {
+            const uint16_t *fu = static_cast<const uint16_t*>(fo.Mf), *fd = static_cast<const uint16_t*>(fo.mf);
+            const uint16_t* const q[8] = {dn[0] ? fo.q_dn : fo.q_up, dn[1] ? fo.q_dn : fo.q_up,
+                                          dn[2] ? fo.q_dn : fo.q_up, dn[3] ? fo.q_dn : fo.q_up,
+                                          dn[0] ? fd : fu, dn[1] ? fd : fu, dn[2] ? fd : fu, dn[3] ? fd : fu};
+            int y[8] = {yg[0], yg[1], yg[2], yg[3], yf[0], yf[1], yf[2], yf[3]};
+            follow_codes<NDIM, 8>(gr, q, y, bad, hops);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                zg[e] = (dn[e] ? q_dn : q_up)[yg[e] < 0 ? -yg[e] - 1 : 0];
-                zf[e] = (dn[e] ? mf : Mf)[yf[e] < 0 ? -yf[e] - 1 : 0];
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                hops += (yg[e] < 0) + (yf[e] < 0);
-                yg[e] = yg[e] < 0 ? zg[e] : yg[e];
-                yf[e] = yf[e] < 0 ? zf[e] : yf[e];
-            }
+            for (int e = 0; e < 4; ++e) yg[e] = y[e], yf[e] = y[4 + e];
         }
         // a listed vertex with different labels is a troublemaker; its target
         // is the neighbour along g's ascent (max) or f's descent (min)
@@ -1466,7 +1464,7 @@ __device__ __forceinline__ void detect_r_tile_sparse(const uint8_t* __restrict__
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             tn[e] = tx[e] = -1;
-            bytes += ok[e] ? 8u : 0u;
+            bytes += ok[e] ? (FLABELS ? 6u : 4u) : 0u;
             if (ok[e] && yg[e] != yf[e]) {
                 const int t = vi[e] + slot_offset(gr, code[e] >> 12);
                 if (dn[e]) tn[e] = t;
@@ -1939,10 +1937,10 @@ __device__ __forceinline__ auto chunk_counted(const EngField& F) {
 template <int NDIM>
 struct RefreshIn {
     int j;
-    unsigned df, dg, cases;
+    unsigned df, dg;
     Around<NDIM> a;
     __device__ __forceinline__ RefreshIn(const EngField& F, int vertex)
-        : j(vertex), df(F.dirs_f[vertex]), dg(F.dirs_g[vertex]), cases(F.cases[vertex]), a(F.g, F.gr, vertex) {}
+        : j(vertex), df(F.dirs_f[vertex]), dg(F.dirs_g[vertex]), a(F.g, F.gr, vertex) {}
 };
 
 // Directions and case byte of vertex j recomputed from g; c receives the
@@ -1953,7 +1951,7 @@ template <int NDIM>
 __device__ __forceinline__ unsigned refresh_vertex(const EngField& F, const RefreshIn<NDIM>& in, bool sum,
                                                    unsigned (&c)[4]) {
     const int j = in.j;
-    const unsigned df = in.df, was_dg = in.dg, was = in.cases;
+    const unsigned df = in.df, was_dg = in.dg, was = case_bits(df, was_dg);  // the stored case byte, not read
     const unsigned dg = in.a.steepest();
     const unsigned now = case_bits(df, dg);
     if (dg != was_dg) {
@@ -2248,13 +2246,13 @@ __device__ __forceinline__ SparseResult sparse_rounds(const EngField& F, int typ
 // its blocks visited (per unit, the compulsory reads and writes of the
 // operation; halo and cache re-reads are not counted):
 //   validate 16 B per vertex (20 with a warm start), directions of f 5,
-//   full direction and case pass over g 9, label tile 9 per vertex of a
-//   relabelled tile plus 10 per saved face vertex (16 per restored one of an
-//   unchanged tile), labels of f 16 per vertex of a visited tile,
-//   troublemakers 2 per vertex of a visited tile plus 8 per vertex whose
-//   labels are resolved in a direction that differs (16 per direction of a
-//   4-vertex group in the start field's count), both plus 4 per gather
-//   along an exit chain, 16 per edit attempt and 1 per neighbour flagged
+//   full direction and case pass over g 9, label tile 5 per vertex of a
+//   relabelled tile (9 for f's in a field corrected alone), labels of f 16 per
+//   vertex of a visited tile plus 4 per gather along an exit chain,
+//   troublemakers 2 per vertex of a visited tile plus 6 (4 in a batch) per
+//   vertex whose labels are resolved in a direction that differs (twice that
+//   per vertex in the start field's count) plus 2 per gather along an exit
+//   chain, 16 per edit attempt and 1 per neighbour flagged
 //   after a change; deltas 16; an
 //   apply or refresh 1 per flag byte of a chunk it reads (an apply reads only
 //   chunks that may hold a case of its type, a refresh only chunks an edit
@@ -2294,19 +2292,21 @@ __device__ __forceinline__ long long chunk_vertices(const Grid& gr, int lo, int 
 }
 
 // acct: this thread's share of the algorithmic bytes of the range (see above).
-// SUM: keep and use the chunk summaries of the flag arrays where the field
-// asks for them (F.sum: the one-field kernel on a field whose blocks scan
-// long ranges of chunks; a batch step sizes its blocks' shares for a full
-// scan and waits for the slowest, so skipping chunks gains it nothing).
-template <int NDIM, bool SUM>
+// SINGLE: the one-field kernel.  Its field has f's labels resolved once before
+// the loop (a batch field's passes follow f's chains instead), and keeps and
+// uses the chunk summaries of the flag arrays where it asks for them (F.sum:
+// blocks that scan long ranges of chunks; a batch step sizes its blocks'
+// shares for a full scan and waits for the slowest, so skipping chunks gains
+// it nothing).
+template <int NDIM, bool SINGLE>
 __device__ __forceinline__ void eng_run_range(const EngField& F, const EngState& st, int lo, int hi, char* smem,
                                               unsigned* cnt, unsigned long long& acct) {
     constexpr int NS = NDIM == 3 ? 14 : 6;
     const bool lead = threadIdx.x == 0;  // adds the bytes that are fixed per range
-    const bool sum = SUM && F.sum != 0;  // this field keeps chunk summaries
+    const bool sum = SINGLE && F.sum != 0;  // this field keeps chunk summaries
     const Grid& gr = F.gr;
-    int* su = reinterpret_cast<int*>(smem);
-    int* sd = su + 4096;
+    uint16_t* su = reinterpret_cast<uint16_t*>(smem);
+    uint16_t* sd = su + 4096;
     float* sm = reinterpret_cast<float*>(smem);
     const int cidx[4] = {kCntCase + 0, kCntCase + 1, kCntCase + 2, kCntCase + 3};
     __shared__ __align__(16) SlotStep s_tab[16];  // label tile passes
@@ -2330,18 +2330,23 @@ __device__ __forceinline__ void eng_run_range(const EngField& F, const EngState&
             break;
         }
         case kOpPreB:  // the pointers of f's forests, kept for the troublemaker passes
-            fill_slot_steps<NDIM>(gr, s_tab);
+            fill_slot_steps<NDIM>(s_tab);
             __syncthreads();
             for (int item = lo; item < hi; ++item) {
-                label_tile_body<NDIM>(F.dirs_f, gr, item, F.Mf, F.mf, su, sd, s_tab);
+                if constexpr (SINGLE) {
+                    label_tile_body<NDIM>(F.dirs_f, gr, item, F.Mf, F.mf, su, sd, s_tab);
+                } else {
+                    label_tile_body<NDIM>(F.dirs_f, gr, item, reinterpret_cast<uint16_t*>(F.Mf),
+                                          reinterpret_cast<uint16_t*>(F.mf), su, sd, s_tab);
+                }
                 __syncthreads();
-                if (lead) acct += 9 * tile_vertices<NDIM>(gr, item);
+                if (lead) acct += (SINGLE ? 9 : 5) * tile_vertices<NDIM>(gr, item);
             }
             break;
         case kOpRTile:
             // only tiles with a changed direction are redone: the others'
             // pointers are still those of their last pass
-            fill_slot_steps<NDIM>(gr, s_tab);
+            fill_slot_steps<NDIM>(s_tab);
             __syncthreads();
             for (int item = lo; item < hi; ++item) {
                 if (!F.tile_dirty[item]) continue;
@@ -2349,7 +2354,7 @@ __device__ __forceinline__ void eng_run_range(const EngField& F, const EngState&
                 __syncthreads();
                 if (threadIdx.x == 0) {
                     F.tile_dirty[item] = 0;
-                    acct += 9 * tile_vertices<NDIM>(gr, item);
+                    acct += 5 * tile_vertices<NDIM>(gr, item);
                 }
             }
             break;
@@ -2502,16 +2507,16 @@ __device__ __forceinline__ void eng_run_range(const EngField& F, const EngState&
             static_assert(kEngSmemBytes / 2 >= 2 * 4096 * sizeof(unsigned short), "candidate lists fit");
             if (threadIdx.x == 0) s_targets = 0, s_cand = 0;
             __syncthreads();
+            const Forests fo{F.qu, F.qd, F.Mf, F.mf};
             unsigned bad = 0, hops = 0;
             for (int item = lo; item < hi; ++item) {
                 // the start field's count needs every mislabelled vertex;
                 // the loop's rounds need only the troublemakers
                 if (st.init)
-                    detect_r_tile<NDIM>(F.dirs_f, F.dirs_g, F.qu, F.qd, F.Mf, F.mf, gr, item, true,
-                                        F.flabels != 0, tl, wrong, cases, changed, bad, hops, acct);
+                    count_wrong_tile<NDIM, SINGLE>(fo, gr, item, wrong, bad, hops, acct);
                 else
-                    detect_r_tile_sparse<NDIM>(F.dirs_f, F.dirs_g, F.qu, F.qd, F.Mf, F.mf, gr, item, tl, cand_up,
-                                               cand_dn, &s_cand, cases, changed, bad, hops, acct);
+                    detect_r_tile_sparse<NDIM, SINGLE>(F.dirs_f, F.dirs_g, fo, gr, item, tl, cand_up, cand_dn, &s_cand,
+                                                       cases, changed, bad, hops, acct);
                 if (lead) acct += 2 * tile_vertices<NDIM>(gr, item);
                 __syncthreads();  // every wave's additions to the list are in s_targets
                 // past half the list: edit what it holds and empty it
@@ -2525,7 +2530,7 @@ __device__ __forceinline__ void eng_run_range(const EngField& F, const EngState&
                 __syncthreads();
                 edit_targets();
             }
-            acct += 16ull * tries + static_cast<unsigned long long>(NS) * changed + 4ull * hops;
+            acct += 16ull * tries + static_cast<unsigned long long>(NS) * changed + 2ull * hops;
             if (bad) atomicOr(cnt + kCntErr, bad);
             unsigned v[3] = {wrong, cases, changed};
             const int idx[3] = {kCntWrong, kCntRCases, kCntChanged};
@@ -2648,7 +2653,7 @@ __device__ __forceinline__ EngState eng_decide(const EngField& F, EngState st, E
             return go(kOpPreB);
         case kOpPreB:  // f's labels: resolved once, or followed where the troublemaker passes need them
             st.type = 0;
-            return go(F.flabels ? kOpPreD : kOpPreE);
+            return go(F.single ? kOpPreD : kOpPreE);
         case kOpPreD:
             if (c[kCntErr] & kErrWalk) return stop(MSZ_EDEVICE);
             return go(kOpPreE);
