@@ -32,6 +32,37 @@ namespace msz {
 
 // ---------------------------------------------------------------- helpers ---
 
+// Four elements of a row at whatever address its length gives them: the rows
+// of a field start at every multiple of the element's size, and gfx950 loads
+// and stores 4, 8 and 16 bytes at any such address.  Element by element, as
+// rows with nx % 4 != 0 were taken before, a correction of 1795x1153 took 1.37
+// ms (1.28 so), of 177x95x48 0.68 ms (0.62), the 96-field batch 21.8 ms (19.8).
+struct __attribute__((packed)) Bytes4 {
+    unsigned v;
+};
+struct __attribute__((packed, aligned(2))) Shorts4 {
+    unsigned x, y;
+};
+struct __attribute__((packed, aligned(4))) Floats4 {
+    float x, y, z, w;
+};
+struct __attribute__((packed, aligned(4))) Ints4 {
+    int x, y, z, w;
+};
+__device__ __forceinline__ unsigned load_bytes4(const uint8_t* p) { return reinterpret_cast<const Bytes4*>(p)->v; }
+__device__ __forceinline__ void store_bytes4(uint8_t* p, unsigned v) { reinterpret_cast<Bytes4*>(p)->v = v; }
+__device__ __forceinline__ float4 load_floats4(const float* p) {
+    const Floats4 v = *reinterpret_cast<const Floats4*>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ int4 load_ints4(const int* p) {
+    const Ints4 v = *reinterpret_cast<const Ints4*>(p);
+    return make_int4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void store_ints4(int* p, int a, int b, int c, int d) {
+    *reinterpret_cast<Ints4*>(p) = Ints4{a, b, c, d};
+}
+
 __device__ __forceinline__ unsigned wave_sum(unsigned v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
@@ -264,23 +295,22 @@ struct ItemPos {
 };
 
 template <int NDIM, int TY, int ZC>
-__device__ __forceinline__ ItemPos item_pos(const DirsGeom<NDIM, TY, ZC>& geo, const Grid& gr, int it, bool vec4) {
+__device__ __forceinline__ ItemPos item_pos(const DirsGeom<NDIM, TY, ZC>& geo, const Grid& gr, int it) {
     ItemPos p;
     geo.origin(it, p.x0, p.y0, p.z0);
     p.planes = geo.planes(gr, it);
     const bool zin = NDIM == 2 || (p.z0 >= 1 && p.z0 + ZC < gr.nz);
-    p.interior = vec4 && zin && p.x0 >= 1 && p.x0 + kTileX < gr.nx && p.y0 >= 1 && p.y0 + TY < gr.ny;
+    p.interior = zin && p.x0 >= 1 && p.x0 + kTileX < gr.nx && p.y0 >= 1 && p.y0 + TY < gr.ny;
     return p;
 }
 
 // Issues the loads of plane j of the item at pos into registers (and, in
 // MODE 1, the dirs_f words of the plane that is computed once this one is in
 // LDS).  Outside the grid a value is NaN, which never wins a comparison.
-// vec4: rows start 16-byte aligned (nx % 4 == 0 and an aligned base), so
-// whole in-grid groups of four are one dwordx4 load.
+// Whole in-grid groups of four are one dwordx4 load.
 template <int NDIM, int TY, int ZC, int MODE>
 __device__ __forceinline__ void dirs_load(const float* __restrict__ h, const uint8_t* __restrict__ dirs_f,
-                                          const Grid& gr, const ItemPos& pos, bool vec4, int j,
+                                          const Grid& gr, const ItemPos& pos, int j,
                                           PlaneRegs<NDIM, TY, ZC>& pr) {
     using G = DirsGeom<NDIM, TY, ZC>;
     const int x0 = pos.x0, y0 = pos.y0;
@@ -295,8 +325,7 @@ __device__ __forceinline__ void dirs_load(const float* __restrict__ h, const uin
             const int u = threadIdx.x + 256 * k;
             float4 v = make_float4(nan, nan, nan, nan);
             if (G::NV % 256 == 0 || u < G::NV)
-                v = *reinterpret_cast<const float4*>(plane + static_cast<long>(gr.nx) * (y0 + (u >> 4) - 1) + x0 +
-                                                     4 * (u & 15));
+                v = load_floats4(plane + static_cast<long>(gr.nx) * (y0 + (u >> 4) - 1) + x0 + 4 * (u & 15));
             pr.v[k] = v;
         }
 #pragma unroll
@@ -310,8 +339,8 @@ __device__ __forceinline__ void dirs_load(const float* __restrict__ h, const uin
             if (NDIM == 2 || j >= 2) {
 #pragma unroll
                 for (int q = 0; q < G::RPT; ++q)
-                    pr.d[q] = *reinterpret_cast<const unsigned*>(
-                        dirs_f + static_cast<long>(zc) * gr.nxy + static_cast<long>(gr.nx) * (y0 + ty + 16 * q) + x0 + 4 * tx);
+                    pr.d[q] = load_bytes4(dirs_f + static_cast<long>(zc) * gr.nxy +
+                                          static_cast<long>(gr.nx) * (y0 + ty + 16 * q) + x0 + 4 * tx);
             }
         }
         return;
@@ -324,8 +353,8 @@ __device__ __forceinline__ void dirs_load(const float* __restrict__ h, const uin
         float4 v = make_float4(nan, nan, nan, nan);
         if (u < G::NV && zin && y >= 0 && y < gr.ny && x < gr.nx) {
             const float* src = plane + static_cast<long>(gr.nx) * y + x;
-            if (vec4 && x + 3 < gr.nx) {
-                v = *reinterpret_cast<const float4*>(src);
+            if (x + 3 < gr.nx) {
+                v = load_floats4(src);
             } else {
                 v.x = src[0];
                 if (x + 1 < gr.nx) v.y = src[1];
@@ -345,7 +374,6 @@ __device__ __forceinline__ void dirs_load(const float* __restrict__ h, const uin
         pr.h[k] = v;
     }
     if constexpr (MODE == 1) {
-        const bool dvec = (gr.nx & 3) == 0;
         const bool zok = NDIM == 3 ? (j >= 2 && zc < gr.nz) : true;
 #pragma unroll
         for (int q = 0; q < G::RPT; ++q) {
@@ -353,8 +381,8 @@ __device__ __forceinline__ void dirs_load(const float* __restrict__ h, const uin
             const long i0 = static_cast<long>(zc) * gr.nxy + static_cast<long>(gr.nx) * y + xa;
             unsigned d = 0xFFFFFFFFu;
             if (zok && y < gr.ny) {
-                if (dvec && xa + 3 < gr.nx) {
-                    d = *reinterpret_cast<const unsigned*>(dirs_f + i0);
+                if (xa + 3 < gr.nx) {
+                    d = load_bytes4(dirs_f + i0);
                 } else {
 #pragma unroll
                     for (int k = 0; k < 4; ++k)
@@ -409,12 +437,11 @@ __device__ __forceinline__ void dirs_compute(const float* C, const float* A, con
     using G = DirsGeom<NDIM, TY, ZC>;
     constexpr int W = G::W;
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const bool vec4 = (gr.nx & 3) == 0;
 #pragma unroll
     for (int q = 0; q < G::RPT; ++q) {
         const int y = pos.y0 + ty + 16 * q, xa = pos.x0 + tx * 4, r = ty + 16 * q + 1;
         const long i0 = static_cast<long>(z) * gr.nxy + static_cast<long>(gr.nx) * y + xa;
-        const bool full = pos.interior || (vec4 && xa + 3 < gr.nx && y < gr.ny);
+        const bool full = pos.interior || (xa + 3 < gr.nx && y < gr.ny);
         const int col = 4 + 4 * tx;
         const Row6 cm(C + (r - 1) * W + col), c0(C + r * W + col), cp(C + (r + 1) * W + col);
         Row6 bm = c0, b0 = c0, a0 = c0, ap = c0;
@@ -455,15 +482,15 @@ __device__ __forceinline__ void dirs_compute(const float* C, const float* A, con
                 if (!full) dirs_out[i0 + k] = static_cast<uint8_t>(packed);
             }
         }
-        if (full) *reinterpret_cast<unsigned*>(dirs_out + i0) = out4;
+        if (full) store_bytes4(dirs_out + i0, out4);
         if constexpr (MODE == 1) {
             // 32-bit offsets (n < 2^31) keep the three stores on one address register
             const unsigned u0 = static_cast<unsigned>(i0);
             const unsigned cw = cases4(df4[q], out4, c);
             if (full) {
-                *reinterpret_cast<unsigned*>(ca.cases + u0) = cw;
-                *reinterpret_cast<unsigned*>(ca.dirty + u0) = 0u;
-                *reinterpret_cast<unsigned*>(ca.marks + u0) = 0u;
+                store_bytes4(ca.cases + u0, cw);
+                store_bytes4(ca.dirty + u0, 0u);
+                store_bytes4(ca.marks + u0, 0u);
             } else {
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
@@ -486,15 +513,12 @@ __device__ __forceinline__ void dirs_stream(const float* __restrict__ h, const G
                                             const CaseArrays& ca, float* sm, unsigned (&c)[4]) {
     using G = DirsGeom<NDIM, TY, ZC>;
     const G geo(gr);
-    const bool vec4 = (gr.nx & 3) == 0 && (reinterpret_cast<uintptr_t>(h) & 15u) == 0 &&
-                      (MODE == 0 || (reinterpret_cast<uintptr_t>(dirs_f) & 3u) == 0) &&
-                      (reinterpret_cast<uintptr_t>(dirs_out) & 3u) == 0;
     PlaneRegs<NDIM, TY, ZC> pr;
     int it = range.first, j = 0;
     ItemPos pos{};
     if (it < range.hi) {
-        pos = item_pos(geo, gr, it, vec4);
-        dirs_load<NDIM, TY, ZC, MODE>(h, dirs_f, gr, pos, vec4, 0, pr);
+        pos = item_pos(geo, gr, it);
+        dirs_load<NDIM, TY, ZC, MODE>(h, dirs_f, gr, pos, 0, pr);
     }
     int ring = 0;  // LDS slot of the plane held in registers
     while (it < range.hi) {
@@ -509,10 +533,10 @@ __device__ __forceinline__ void dirs_stream(const float* __restrict__ h, const G
         if (++j == pos.planes) {
             j = 0;
             it += range.stride;
-            if (it < range.hi) pos = item_pos(geo, gr, it, vec4);
+            if (it < range.hi) pos = item_pos(geo, gr, it);
         }
         ring = G::NP == 3 ? (ring + 1) % 3 : 0;
-        if (it < range.hi) dirs_load<NDIM, TY, ZC, MODE>(h, dirs_f, gr, pos, vec4, j, pr);
+        if (it < range.hi) dirs_load<NDIM, TY, ZC, MODE>(h, dirs_f, gr, pos, j, pr);
         if (NDIM == 2 || cur_j >= 2) {
             const int z = NDIM == 3 ? cur.z0 + cur_j - 2 : 0;
             const float* A = sm + cur_ring * G::P;                             // plane z + 1
@@ -907,7 +931,6 @@ __device__ __forceinline__ void label_tile_body(const uint8_t* __restrict__ dirs
     const int bx = tile % tx_n, by = (tile / tx_n) % ty_n, bz = tile / (tx_n * ty_n);
     const int X0 = bx * T::X, Y0 = by * T::Y, Z0 = bz * T::Z;
 
-    const bool vec4 = (gr.nx & 3) == 0;
     int pu[G][4], pd[G][4];
     unsigned d4[G];
 #pragma unroll
@@ -918,8 +941,8 @@ __device__ __forceinline__ void label_tile_body(const uint8_t* __restrict__ dirs
         const bool row_in = y < gr.ny && z < gr.nz;
         const int i0 = xa + gr.nx * y + gr.nxy * z;
         d4[k] = 0xFFFFFFFFu;  // a vertex outside the grid: nothing points at it and nothing stores it
-        if (row_in && vec4 && xa + 3 < gr.nx) {
-            d4[k] = *reinterpret_cast<const unsigned*>(dirs + i0);
+        if (row_in && xa + 3 < gr.nx) {
+            d4[k] = load_bytes4(dirs + i0);
         } else if (row_in) {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -992,10 +1015,11 @@ __device__ __forceinline__ void label_tile_body(const uint8_t* __restrict__ dirs
     const unsigned corner = C::corner(gr, X0, Y0, Z0);
     auto store4 = [&](Out* q, const int (&p)[4]) {
         if constexpr (sizeof(Out) == 2) {
-            publish(q, p);
+            *reinterpret_cast<Shorts4*>(q) = Shorts4{static_cast<unsigned>(p[0]) | (static_cast<unsigned>(p[1]) << 16),
+                                                     static_cast<unsigned>(p[2]) | (static_cast<unsigned>(p[3]) << 16)};
         } else {
-            *reinterpret_cast<int4*>(q) = make_int4(C::target(gr, corner, p[0]), C::target(gr, corner, p[1]),
-                                                    C::target(gr, corner, p[2]), C::target(gr, corner, p[3]));
+            store_ints4(q, C::target(gr, corner, p[0]), C::target(gr, corner, p[1]), C::target(gr, corner, p[2]),
+                        C::target(gr, corner, p[3]));
         }
     };
     auto store1 = [&](Out* q, int p) {
@@ -1009,7 +1033,7 @@ __device__ __forceinline__ void label_tile_body(const uint8_t* __restrict__ dirs
         const int xa = X0 + lx0, y = Y0 + ly, z = Z0 + lz;
         if (y >= gr.ny || z >= gr.nz) continue;
         const int i0 = xa + gr.nx * y + gr.nxy * z;
-        if (vec4 && xa + 3 < gr.nx) {
+        if (xa + 3 < gr.nx) {
             store4(q_up + i0, pu[k]);
             store4(q_dn + i0, pd[k]);
         } else {
@@ -1160,7 +1184,7 @@ template <int NDIM>
 struct TileGroup {
     int i0;     // global id of the group's first vertex
     int count;  // in-grid vertices of the group (0..4)
-    bool vec;   // the four are in the grid, consecutive and 16-byte aligned
+    bool vec;   // the four are in the grid
 };
 
 template <int NDIM>
@@ -1173,7 +1197,7 @@ __device__ __forceinline__ TileGroup<NDIM> tile_group(const Grid& gr, int tile, 
     TileGroup<NDIM> g;
     g.i0 = xa + gr.nx * y + gr.nxy * z;
     g.count = (y < gr.ny && z < gr.nz) ? max(0, min(4, gr.nx - xa)) : 0;
-    g.vec = g.count == 4 && (gr.nx & 3) == 0;
+    g.vec = g.count == 4;
     return g;
 }
 
@@ -1193,8 +1217,7 @@ __device__ __forceinline__ unsigned label_final_tile(const int* q_up, const int*
 #pragma unroll
         for (int j = 0; j < 4; ++j) a[k][j] = b[k][j] = 0;
         if (tg[k].vec) {
-            const int4 u = *reinterpret_cast<const int4*>(q_up + tg[k].i0);
-            const int4 d = *reinterpret_cast<const int4*>(q_dn + tg[k].i0);
+            const int4 u = load_ints4(q_up + tg[k].i0), d = load_ints4(q_dn + tg[k].i0);
             a[k][0] = u.x, a[k][1] = u.y, a[k][2] = u.z, a[k][3] = u.w;
             b[k][0] = d.x, b[k][1] = d.y, b[k][2] = d.z, b[k][3] = d.w;
         } else {
@@ -1218,8 +1241,8 @@ __device__ __forceinline__ unsigned label_final_tile(const int* q_up, const int*
             rb[j] = y[2 * j + 1];
         }
         if (tg[k].vec) {
-            *reinterpret_cast<int4*>(M + tg[k].i0) = make_int4(ra[0], ra[1], ra[2], ra[3]);
-            *reinterpret_cast<int4*>(m + tg[k].i0) = make_int4(rb[0], rb[1], rb[2], rb[3]);
+            store_ints4(M + tg[k].i0, ra[0], ra[1], ra[2], ra[3]);
+            store_ints4(m + tg[k].i0, rb[0], rb[1], rb[2], rb[3]);
         } else {
             for (int j = 0; j < tg[k].count; ++j) M[tg[k].i0 + j] = ra[j], m[tg[k].i0 + j] = rb[j];
         }
@@ -1378,8 +1401,8 @@ __device__ __forceinline__ void detect_r_tile_sparse(const uint8_t* __restrict__
         const TileGroup<NDIM> t = tile_group<NDIM>(gr, tile, k);
         unsigned a = 0u, b = 0u;
         if (t.vec) {
-            a = *reinterpret_cast<const unsigned*>(dirs_f + t.i0);
-            b = *reinterpret_cast<const unsigned*>(dirs_g + t.i0);
+            a = load_bytes4(dirs_f + t.i0);
+            b = load_bytes4(dirs_g + t.i0);
         } else {  // bytes past the count stay equal zeros
             for (int j = 0; j < t.count; ++j) {
                 a |= static_cast<unsigned>(dirs_f[t.i0 + j]) << (8 * j);
