@@ -69,6 +69,20 @@ __device__ __forceinline__ unsigned wave_sum(unsigned v) {
     return v;
 }
 
+// Inclusive prefix sum over a wave in the VALU (shifts within the rows of 16
+// lanes, then the row totals broadcast onward), without the LDS round trip
+// per step of a lane shuffle.
+__device__ __forceinline__ unsigned wave_prefix(unsigned v) {
+    auto add = [&](unsigned w) { v += w; };
+    add(__builtin_amdgcn_update_dpp(0u, v, 0x111, 0xF, 0xF, false));  // row_shr:1
+    add(__builtin_amdgcn_update_dpp(0u, v, 0x112, 0xF, 0xF, false));  // row_shr:2
+    add(__builtin_amdgcn_update_dpp(0u, v, 0x114, 0xF, 0xF, false));  // row_shr:4
+    add(__builtin_amdgcn_update_dpp(0u, v, 0x118, 0xF, 0xF, false));  // row_shr:8
+    add(__builtin_amdgcn_update_dpp(0u, v, 0x142, 0xA, 0xF, false));  // row_bcast:15 into rows 1 and 3
+    add(__builtin_amdgcn_update_dpp(0u, v, 0x143, 0xC, 0xF, false));  // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
 // Block-wide reduction of K counters followed by one atomic per non-zero total.
 template <int K>
 __device__ __forceinline__ void block_add(unsigned (&v)[K], unsigned* dst, const int* idx, int nslots = kSlots,
@@ -876,10 +890,13 @@ __device__ __forceinline__ void follow_roots(const int* q_up, const int* q_dn, i
     }
 }
 
-// The same over arrays of TileCodes, chain k in forest q[k].
-template <int NDIM, int K>
-__device__ __forceinline__ void follow_codes(const Grid& gr, const uint16_t* const (&q)[K], int (&y)[K], unsigned& bad,
-                                             unsigned& hops) {
+// The same over arrays of TileCodes: chain k in q_up, or in q_dn when dn[k];
+// from S on, in a second pair of forests, r_up and r_dn.  (The forest is
+// chosen at each load: a pointer per chain would cost two registers each.)
+template <int NDIM, int K, int S>
+__device__ __forceinline__ void follow_codes(const Grid& gr, const uint16_t* q_up, const uint16_t* q_dn,
+                                             const uint16_t* r_up, const uint16_t* r_dn, const bool (&dn)[K],
+                                             int (&y)[K], unsigned& bad, unsigned& hops) {
     for (int pass = 0;; ++pass) {
         bool any = false;
 #pragma unroll
@@ -893,7 +910,8 @@ __device__ __forceinline__ void follow_codes(const Grid& gr, const uint16_t* con
         }
         unsigned z[K];
 #pragma unroll
-        for (int k = 0; k < K; ++k) z[k] = q[k][y[k] < 0 ? -y[k] - 1 : 0];
+        for (int k = 0; k < K; ++k)
+            z[k] = (k < S ? (dn[k] ? q_dn : q_up) : (dn[k] ? r_dn : r_up))[y[k] < 0 ? -y[k] - 1 : 0];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             hops += y[k] < 0;
@@ -1281,26 +1299,17 @@ struct TargetList {
         else target_edit<NDIM>(preempt, marks, g, L, dirty, gr, t, changed);
     }
     // Appends each lane's targets (-1: none; nloc of them): one LDS atomic per
-    // wave, positions from a prefix sum over the wave.
-    template <int NDIM>
-    __device__ __forceinline__ void add_wave(const Grid& gr, const int (&tn)[4], const int (&tx)[4], int nloc,
-                                             unsigned& changed) const {
+    // wave, positions from a prefix sum over the wave.  By whole waves.
+    template <int NDIM, int E>
+    __device__ __forceinline__ void add_wave(const Grid& gr, const int (&t)[E], int nloc, unsigned& changed) const {
         if (!__any(nloc)) return;
-        const int lane = threadIdx.x & 63;
-        int incl = nloc;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int v = __shfl_up(incl, o);
-            if (lane >= o) incl += v;
-        }
+        const unsigned incl = wave_prefix(static_cast<unsigned>(nloc));
         unsigned base = 0;
-        if (lane == 63) base = atomicAdd(count, static_cast<unsigned>(incl));
-        unsigned k = __shfl(base, 63) + static_cast<unsigned>(incl - nloc);
+        if ((threadIdx.x & 63) == 63) base = atomicAdd(count, incl);
+        unsigned k = __builtin_amdgcn_readlane(base, 63) + incl - static_cast<unsigned>(nloc);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (tn[j] >= 0) put<NDIM>(gr, k++, tn[j], changed);
-            if (tx[j] >= 0) put<NDIM>(gr, k++, tx[j], changed);
-        }
+        for (int e = 0; e < E; ++e)
+            if (t[e] >= 0) put<NDIM>(gr, k++, t[e], changed);
     }
 };
 
@@ -1338,14 +1347,14 @@ __device__ __forceinline__ void count_wrong_tile(const Forests& fo, const Grid& 
                 bytes += FLABELS ? 12 : 8;
             }
             if constexpr (FLABELS) {
-                const uint16_t* const q[2] = {fo.q_up, fo.q_dn};
+                const bool dn[2] = {false, true};
                 int yg[2] = {y[0], y[1]};
-                follow_codes<NDIM, 2>(gr, q, yg, bad, hops);
+                follow_codes<NDIM, 2, 2>(gr, fo.q_up, fo.q_dn, nullptr, nullptr, dn, yg, bad, hops);
                 y[0] = yg[0], y[1] = yg[1];
             } else {
-                const uint16_t* const q[4] = {fo.q_up, fo.q_dn, static_cast<const uint16_t*>(fo.Mf),
-                                              static_cast<const uint16_t*>(fo.mf)};
-                follow_codes<NDIM, 4>(gr, q, y, bad, hops);
+                const bool dn[4] = {false, true, false, true};
+                follow_codes<NDIM, 4, 2>(gr, fo.q_up, fo.q_dn, static_cast<const uint16_t*>(fo.Mf),
+                                         static_cast<const uint16_t*>(fo.mf), dn, y, bad, hops);
             }
             wrong += y[0] != y[2] || y[1] != y[3];
         }
@@ -1377,27 +1386,26 @@ __device__ __forceinline__ int tile_vertex(const Grid& gr, int tile, int l) {
 // first (cand_up / cand_dn, 4096 entries each: the tile-local index in bits
 // 0..11 and the slot of the target's direction -- g's ascent, f's descent --
 // in bits 12..15; *s_n counts them, ascents in its low and descents in its
-// high 16 bits, and is 0 on entry and on return), then resolved four per
+// high 16 bits, and is 0 on entry and on return), then resolved up to four per
 // thread, every walk of a round in flight together.  A wave then waits for
 // one round of pointer loads and walks per 1024 listed vertices of the tile
-// instead of one per row group it holds.  Bound by whole-line fetches around
-// the scattered pointers and chains: 512^3, whose later rounds list 5 million
-// directions, takes 320 to 390 us a round (1080 the first, with 33 million);
-// with id pointers 330 to 430 (1160).
-template <int NDIM, bool FLABELS>
-__device__ __forceinline__ void detect_r_tile_sparse(const uint8_t* __restrict__ dirs_f,
-                                                     const uint8_t* __restrict__ dirs_g, const Forests& fo,
-                                                     const Grid& gr, int tile, const TargetList& tl,
-                                                     unsigned short* cand_up, unsigned short* cand_dn, unsigned* s_n,
-                                                     unsigned& cases, unsigned& changed, unsigned& bad,
-                                                     unsigned& hops, unsigned long long& bytes) {
-    using T = LabelTile<NDIM>;
-    using C = TileCode<NDIM>;
-    constexpr int G = T::X * T::Y * T::Z / 1024;
-    static_assert(G == 4 && T::X * T::Y * T::Z == 4096, "4096 vertices, four row groups per thread");
-    unsigned w[2 * G];
+// instead of one per row group it holds.  A tile is a chain of memory round
+// trips (directions, pointers, one per hop) for four waves, so the next
+// tile's directions are loaded (DirWords) before this one's pointers are
+// waited for, and a tile with few listed vertices runs the resolution for one
+// or two per thread instead of four.
+// In the 96-field batch a tile takes a block 13 us (2D) and 15.5 us (3D) where
+// four row groups listed one after another and four entries per thread took
+// 18 and 19; 512^3 takes 290 to 370 us in its later rounds.
+struct DirWords {  // a thread's four row groups of a tile: direction bytes in f and g
+    unsigned f[4], g[4];
+};
+template <int NDIM>
+__device__ __forceinline__ DirWords load_dir_words(const uint8_t* __restrict__ dirs_f,
+                                                   const uint8_t* __restrict__ dirs_g, const Grid& gr, int tile) {
+    DirWords w;
 #pragma unroll
-    for (int k = 0; k < G; ++k) {
+    for (int k = 0; k < 4; ++k) {
         const TileGroup<NDIM> t = tile_group<NDIM>(gr, tile, k);
         unsigned a = 0u, b = 0u;
         if (t.vec) {
@@ -1409,94 +1417,128 @@ __device__ __forceinline__ void detect_r_tile_sparse(const uint8_t* __restrict__
                 b |= static_cast<unsigned>(dirs_g[t.i0 + j]) << (8 * j);
             }
         }
-        w[2 * k] = a;
-        w[2 * k + 1] = b;
+        w.f[k] = a;
+        w.g[k] = b;
     }
-    const int lane = threadIdx.x & 63;
+    return w;
+}
+
+// The listed entries b0 + threadIdx.x + 256 e, e < E, of n (the first nu of
+// them ascents): the targets of those that are troublemakers go to tl.
+template <int NDIM, bool FLABELS, int E>
+__device__ __forceinline__ void resolve_listed(const Forests& fo, const Grid& gr, int tile, unsigned corner, int b0,
+                                               int n, int nu, const unsigned short* cand_up,
+                                               const unsigned short* cand_dn, const TargetList& tl, unsigned& cases,
+                                               unsigned& changed, unsigned& bad, unsigned& hops,
+                                               unsigned long long& bytes) {
+    using C = TileCode<NDIM>;
+    int vi[E], yg[E], yf[E];
+    unsigned code[E], cg[E];
+    bool dn[E], ok[E];
 #pragma unroll
-    for (int k = 0; k < G; ++k) {
-        const unsigned dfw = w[2 * k], dgw = w[2 * k + 1], x = dfw ^ dgw;
-        unsigned dup = 0, ddn = 0;
+    for (int e = 0; e < E; ++e) {
+        const int idx = b0 + e * 256 + static_cast<int>(threadIdx.x);
+        ok[e] = idx < n;
+        dn[e] = idx >= nu;
+        code[e] = ok[e] ? (dn[e] ? cand_dn[idx - nu] : cand_up[idx]) : 0u;
+        vi[e] = ok[e] ? tile_vertex<NDIM>(gr, tile, static_cast<int>(code[e] & 4095u)) : 0;
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) cg[e] = ok[e] ? (dn[e] ? fo.q_dn : fo.q_up)[vi[e]] : 0u;
+#pragma unroll
+    for (int e = 0; e < E; ++e) yf[e] = ok[e] ? f_pointer<NDIM, FLABELS>(gr, dn[e] ? fo.mf : fo.Mf, vi[e], corner) : 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) yg[e] = ok[e] ? C::target(gr, corner, cg[e]) : 0;
+    // the walks of every entry, one gather level per pass
+    if constexpr (FLABELS) {
+        follow_codes<NDIM, E, E>(gr, fo.q_up, fo.q_dn, nullptr, nullptr, dn, yg, bad, hops);
+    } else {
+        bool dn2[2 * E];
+        int y[2 * E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) dn2[e] = dn2[E + e] = dn[e], y[e] = yg[e], y[E + e] = yf[e];
+        follow_codes<NDIM, 2 * E, E>(gr, fo.q_up, fo.q_dn, static_cast<const uint16_t*>(fo.Mf),
+                                     static_cast<const uint16_t*>(fo.mf), dn2, y, bad, hops);
+#pragma unroll
+        for (int e = 0; e < E; ++e) yg[e] = y[e], yf[e] = y[E + e];
+    }
+    // a listed vertex with different labels is a troublemaker; its target
+    // is the neighbour along g's ascent (max) or f's descent (min)
+    int t[E], nloc = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        bytes += ok[e] ? (FLABELS ? 6u : 4u) : 0u;
+        const bool hit = ok[e] && yg[e] != yf[e];
+        t[e] = hit ? vi[e] + slot_offset(gr, code[e] >> 12) : -1;
+        nloc += hit;
+    }
+    cases += nloc;
+    if (tl.list) tl.add_wave<NDIM>(gr, t, nloc, changed);
+}
+
+// w: the tile's direction words; on return those of tile next (if it is one
+// of the caller's: next < hi).
+template <int NDIM, bool FLABELS>
+__device__ __forceinline__ void detect_r_tile_sparse(const uint8_t* __restrict__ dirs_f,
+                                                     const uint8_t* __restrict__ dirs_g, const Forests& fo,
+                                                     const Grid& gr, int tile, int next, int hi, DirWords& w,
+                                                     const TargetList& tl, unsigned short* cand_up,
+                                                     unsigned short* cand_dn, unsigned* s_n, unsigned& cases,
+                                                     unsigned& changed, unsigned& bad, unsigned& hops,
+                                                     unsigned long long& bytes) {
+    using T = LabelTile<NDIM>;
+    static_assert(T::X * T::Y * T::Z == 4096, "4096 vertices, four row groups per thread");
+    // bit 4 k + j: vertex j of group k differs in its ascent / descent
+    unsigned up = 0u, dn = 0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const unsigned x = w.f[k] ^ w.g[k];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            dup |= ((x >> (8 * j + 4)) & 15u) ? 1u << j : 0u;
-            ddn |= ((x >> (8 * j)) & 15u) ? 1u << j : 0u;
+            up |= ((x >> (8 * j + 4)) & 15u) ? 1u << (4 * k + j) : 0u;
+            dn |= ((x >> (8 * j)) & 15u) ? 1u << (4 * k + j) : 0u;
         }
-        if (!__any(dup | ddn)) continue;
-        const unsigned mine = static_cast<unsigned>(__popc(dup)) | (static_cast<unsigned>(__popc(ddn)) << 16);
-        unsigned incl = mine;  // each half stays below 2^13: no carry between them
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const unsigned v = __shfl_up(incl, o);
-            if (lane >= o) incl += v;
-        }
+    }
+    if (__any(up | dn)) {
+        const unsigned mine = static_cast<unsigned>(__popc(up)) | (static_cast<unsigned>(__popc(dn)) << 16);
+        const unsigned incl = wave_prefix(mine);  // each half stays below 2^11: no carry between them
         unsigned base = 0;
-        if (lane == 63) base = atomicAdd(s_n, incl);
-        base = __shfl(base, 63);
-        const unsigned before = incl - mine;
-        unsigned pu = (base & 0xFFFFu) + (before & 0xFFFFu), pd = (base >> 16) + (before >> 16);
-        const unsigned l0 = 4u * threadIdx.x + 1024u * k;
+        if ((threadIdx.x & 63) == 63) base = atomicAdd(s_n, incl);
+        base = __builtin_amdgcn_readlane(base, 63) + incl - mine;
+        unsigned pu = base & 0xFFFFu, pd = base >> 16;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if ((dup >> j) & 1u) cand_up[pu++] = static_cast<unsigned short>((l0 + j) | (((dgw >> (8 * j + 4)) & 15u) << 12));
-            if ((ddn >> j) & 1u) cand_dn[pd++] = static_cast<unsigned short>((l0 + j) | (((dfw >> (8 * j)) & 15u) << 12));
-        }
-    }
-    __syncthreads();
-    const int3 o = tile_origin<NDIM>(gr, tile);
-    const unsigned corner = C::corner(gr, o.x, o.y, o.z);
-    const unsigned nn = *s_n;
-    const int nu = static_cast<int>(nn & 0xFFFFu), n = nu + static_cast<int>(nn >> 16);
-    for (int b0 = 0; b0 < n; b0 += 4 * static_cast<int>(blockDim.x)) {  // block-uniform rounds
-        int vi[4], yg[4], yf[4];
-        unsigned code[4];
-        bool dn[4], ok[4];
+        for (int k = 0; k < 4; ++k) {
+            const unsigned l0 = 4u * threadIdx.x + 1024u * k;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int idx = b0 + e * static_cast<int>(blockDim.x) + static_cast<int>(threadIdx.x);
-            ok[e] = idx < n;
-            dn[e] = idx >= nu;
-            code[e] = ok[e] ? (dn[e] ? cand_dn[idx - nu] : cand_up[idx]) : 0u;
-            vi[e] = ok[e] ? tile_vertex<NDIM>(gr, tile, static_cast<int>(code[e] & 4095u)) : 0;
-        }
-        unsigned cg[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) cg[e] = ok[e] ? (dn[e] ? fo.q_dn : fo.q_up)[vi[e]] : 0u;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) yf[e] = ok[e] ? f_pointer<NDIM, FLABELS>(gr, dn[e] ? fo.mf : fo.Mf, vi[e], corner) : 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) yg[e] = ok[e] ? C::target(gr, corner, cg[e]) : 0;
-        // the walks of every entry, one gather level per pass
-        if constexpr (FLABELS) {
-            const uint16_t* const q[4] = {dn[0] ? fo.q_dn : fo.q_up, dn[1] ? fo.q_dn : fo.q_up,
-                                          dn[2] ? fo.q_dn : fo.q_up, dn[3] ? fo.q_dn : fo.q_up};
-            follow_codes<NDIM, 4>(gr, q, yg, bad, hops);
-        } else {
-            const uint16_t *fu = static_cast<const uint16_t*>(fo.Mf), *fd = static_cast<const uint16_t*>(fo.mf);
-            const uint16_t* const q[8] = {dn[0] ? fo.q_dn : fo.q_up, dn[1] ? fo.q_dn : fo.q_up,
-                                          dn[2] ? fo.q_dn : fo.q_up, dn[3] ? fo.q_dn : fo.q_up,
-                                          dn[0] ? fd : fu, dn[1] ? fd : fu, dn[2] ? fd : fu, dn[3] ? fd : fu};
-            int y[8] = {yg[0], yg[1], yg[2], yg[3], yf[0], yf[1], yf[2], yf[3]};
-            follow_codes<NDIM, 8>(gr, q, y, bad, hops);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) yg[e] = y[e], yf[e] = y[4 + e];
-        }
-        // a listed vertex with different labels is a troublemaker; its target
-        // is the neighbour along g's ascent (max) or f's descent (min)
-        int tn[4], tx[4], nloc = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            tn[e] = tx[e] = -1;
-            bytes += ok[e] ? (FLABELS ? 6u : 4u) : 0u;
-            if (ok[e] && yg[e] != yf[e]) {
-                const int t = vi[e] + slot_offset(gr, code[e] >> 12);
-                if (dn[e]) tn[e] = t;
-                else tx[e] = t;
-                ++cases;
-                ++nloc;
+            for (int j = 0; j < 4; ++j) {
+                if ((up >> (4 * k + j)) & 1u)
+                    cand_up[pu++] = static_cast<unsigned short>((l0 + j) | (((w.g[k] >> (8 * j + 4)) & 15u) << 12));
+                if ((dn >> (4 * k + j)) & 1u)
+                    cand_dn[pd++] = static_cast<unsigned short>((l0 + j) | (((w.f[k] >> (8 * j)) & 15u) << 12));
             }
         }
-        if (tl.list) tl.add_wave<NDIM>(gr, tn, tx, nloc, changed);
+    }
+    if (next < hi) w = load_dir_words<NDIM>(dirs_f, dirs_g, gr, next);
+    __syncthreads();
+    const int3 o = tile_origin<NDIM>(gr, tile);
+    const unsigned corner = TileCode<NDIM>::corner(gr, o.x, o.y, o.z);
+    const unsigned nn = *s_n;
+    const int nu = static_cast<int>(nn & 0xFFFFu), n = nu + static_cast<int>(nn >> 16);
+    for (int b0 = 0; b0 < n;) {  // block-uniform rounds
+        const int left = n - b0;
+        // (a batch's entries walk two chains each: four per thread would cost
+        // its step kernels a fourth of their occupancy in registers)
+        constexpr int E = FLABELS ? 4 : 2;
+        if (left > 256 * E / 2) {
+            resolve_listed<NDIM, FLABELS, E>(fo, gr, tile, corner, b0, n, nu, cand_up, cand_dn, tl, cases, changed, bad, hops, bytes);
+            b0 += 256 * E;
+        } else if (FLABELS && left > 256) {
+            resolve_listed<NDIM, FLABELS, 2>(fo, gr, tile, corner, b0, n, nu, cand_up, cand_dn, tl, cases, changed, bad, hops, bytes);
+            b0 += 512;
+        } else {
+            resolve_listed<NDIM, FLABELS, 1>(fo, gr, tile, corner, b0, n, nu, cand_up, cand_dn, tl, cases, changed, bad, hops, bytes);
+            b0 += 256;
+        }
     }
     __syncthreads();  // every entry read before the next tile lists its own
     if (threadIdx.x == 0) *s_n = 0u;
@@ -2532,14 +2574,15 @@ __device__ __forceinline__ void eng_run_range(const EngField& F, const EngState&
             __syncthreads();
             const Forests fo{F.qu, F.qd, F.Mf, F.mf};
             unsigned bad = 0, hops = 0;
+            DirWords words = load_dir_words<NDIM>(F.dirs_f, F.dirs_g, gr, lo);
             for (int item = lo; item < hi; ++item) {
                 // the start field's count needs every mislabelled vertex;
                 // the loop's rounds need only the troublemakers
                 if (st.init)
                     count_wrong_tile<NDIM, SINGLE>(fo, gr, item, wrong, bad, hops, acct);
                 else
-                    detect_r_tile_sparse<NDIM, SINGLE>(F.dirs_f, F.dirs_g, fo, gr, item, tl, cand_up, cand_dn, &s_cand,
-                                                       cases, changed, bad, hops, acct);
+                    detect_r_tile_sparse<NDIM, SINGLE>(F.dirs_f, F.dirs_g, fo, gr, item, item + 1, hi, words, tl,
+                                                       cand_up, cand_dn, &s_cand, cases, changed, bad, hops, acct);
                 if (lead) acct += 2 * tile_vertices<NDIM>(gr, item);
                 __syncthreads();  // every wave's additions to the list are in s_targets
                 // past half the list: edit what it holds and empty it
