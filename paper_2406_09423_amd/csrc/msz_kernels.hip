@@ -1748,26 +1748,29 @@ __host__ __device__ inline int eng_items(const EngField& F, int op) {
 
 int eng_items_host(const EngField& F, int op) { return eng_items(F, op); }
 
-// Cost of one work item of op, in units of about 1 us of one block (per-item
+// Cost of one work item of op, in units of about 0.5 us of one block (per-item
 // block times measured inside the 96-field batch): a batch step splits the
 // weighted index space, not the item count, evenly over its blocks, so a
 // block that draws troublemaker tiles draws fewer of them than one that
 // draws sparse apply chunks.  Direction items scale with their tile's vertex
-// count (per 4096 vertices: 5.6 for the directions of f, 8.5 with the cases).
+// count (per 4096 vertices, 2D and 3D: 8.3 and 14.3 us for the directions of
+// f, 11.2 and 19.5 with the cases).
 __host__ __device__ inline int eng_weight(const EngField& F, int op) {
     const DirsVariant v = variant_of(F.gr.ndim, F.variant);
-    const int dv = kTileX * v.ty * (F.gr.ndim == 3 ? v.zc : 1);  // vertices of a direction item
+    const bool three = F.gr.ndim == 3;
+    const int dv = kTileX * v.ty * (three ? v.zc : 1);  // vertices of a direction item
+    auto dirs = [&](int per4096) { return (per4096 * dv + kEngChunk - 1) / kEngChunk; };
     switch (op) {
-        case kOpPreA: return F.warm ? 12 : 10;
-        case kOpPreA2: return (56 * dv + 10 * kEngChunk - 1) / (10 * kEngChunk);
-        case kOpPreE: case kOpFullC: case kOpFullR: return (85 * dv + 10 * kEngChunk - 1) / (10 * kEngChunk);
-        case kOpPreB: return 21;
-        case kOpPreD: return 22;
-        case kOpRTile: return 13;  // the clean tiles of g are skipped
-        case kOpRDetect: return 22;
-        case kOpApplyC: case kOpSparseC: case kOpRefreshC: return 2;
-        case kOpRefreshR: return 3;
-        case kOpDelta: return 5;
+        case kOpPreA: return F.warm ? 29 : 25;
+        case kOpPreA2: return dirs(three ? 29 : 17);
+        case kOpPreE: case kOpFullC: case kOpFullR: return dirs(three ? 38 : 22);
+        case kOpPreB: return 17;
+        case kOpRTile: return 11;  // the clean tiles of g are skipped
+        case kOpRDetect: return three ? 31 : 26;
+        case kOpApplyC: case kOpRefreshC: return 7;
+        case kOpRefreshR: return three ? 6 : 5;
+        case kOpSparseC: return 2;
+        case kOpDelta: return 13;
         default: return 1;
     }
 }
