@@ -43,24 +43,25 @@ struct __attribute__((packed)) Bytes4 {
 struct __attribute__((packed, aligned(2))) Shorts4 {
     unsigned x, y;
 };
-struct __attribute__((packed, aligned(4))) Floats4 {
-    float x, y, z, w;
-};
-struct __attribute__((packed, aligned(4))) Ints4 {
-    int x, y, z, w;
-};
+typedef float Floats4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef int Ints4 __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ unsigned load_bytes4(const uint8_t* p) { return reinterpret_cast<const Bytes4*>(p)->v; }
 __device__ __forceinline__ void store_bytes4(uint8_t* p, unsigned v) { reinterpret_cast<Bytes4*>(p)->v = v; }
 __device__ __forceinline__ float4 load_floats4(const float* p) {
-    const Floats4 v = *reinterpret_cast<const Floats4*>(p);
-    return make_float4(v.x, v.y, v.z, v.w);
+    // (a vector type, which stays in four consecutive registers: as a struct
+    // the direction passes of 512^3 took 565 and 625 us instead of 470 and 550)
+    typedef float V __attribute__((ext_vector_type(4)));
+    const V v = *reinterpret_cast<const Floats4*>(p);
+    return __builtin_bit_cast(float4, v);
 }
 __device__ __forceinline__ int4 load_ints4(const int* p) {
-    const Ints4 v = *reinterpret_cast<const Ints4*>(p);
-    return make_int4(v.x, v.y, v.z, v.w);
+    typedef int V __attribute__((ext_vector_type(4)));
+    const V v = *reinterpret_cast<const Ints4*>(p);
+    return __builtin_bit_cast(int4, v);
 }
 __device__ __forceinline__ void store_ints4(int* p, int a, int b, int c, int d) {
-    *reinterpret_cast<Ints4*>(p) = Ints4{a, b, c, d};
+    typedef int V __attribute__((ext_vector_type(4)));
+    *reinterpret_cast<Ints4*>(p) = V{a, b, c, d};
 }
 
 __device__ __forceinline__ unsigned wave_sum(unsigned v) {
