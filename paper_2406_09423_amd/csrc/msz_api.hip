@@ -212,6 +212,18 @@ int check_xi(float xi) {
 // ------------------------------------------------------------- engine ---
 
 constexpr int kGraphSteps = kEngTimeSlots;  // steps per graph launch (even: parities line up)
+
+// A field corrected alone none of whose operations has more than kSmallGrid
+// work items (up to about a million vertices) runs its steps with that many
+// blocks, not one resident grid (1024), since every block takes part in every
+// step's decision: 177x95x48 takes 0.437 ms where 1024 blocks take 0.516, 512
+// 0.460 and 128 0.541 (a 128x128 field takes the same with any number; a
+// 1795x1153 one, 2117 direction items, 1.39 ms with 256 and 1.29 with 1024).
+// Its graphs hold fewer steps: with the sparse rounds such a field is done
+// after about 25, and each idle step costs 1.7 us.
+constexpr int kSmallGrid = 256;
+constexpr int kSmallSteps = 30;
+static_assert(kSmallSteps % 6 == 0, "parities of 2 and 3 continue across graph launches");
 static_assert(kGraphSteps % 2 == 0, "states alternate between two buffers");
 // a batch chain's block prefix of one step: nf + 1 prefix sums, then the
 // number of fields given blocks; two of them, by step parity
@@ -239,20 +251,28 @@ struct EngineCtx {
     // each batch chain; ev[3]: the caller's stream reached the batch's start
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     hipStream_t cs[2] = {nullptr, nullptr};  // the batch chains' streams (default priority)
-    // cached graphs: a single field's, or one per batch chain
-    int g_nf = -1, g_n2 = -1, g_grid2 = 0, g_grid3 = 0;
-    bool g_timing = false;
-    hipGraph_t graph[2] = {nullptr, nullptr};
-    hipGraphExec_t exec[2] = {nullptr, nullptr};
+    // cached graphs, a set each for batches (one per chain), single fields and
+    // small single fields, so that a program that alternates between them
+    // does not build them anew
+    struct Graphs {
+        int nf = -1, n2 = -1, grid2 = 0, grid3 = 0;
+        bool timing = false;
+        hipGraph_t graph[2] = {nullptr, nullptr};
+        hipGraphExec_t exec[2] = {nullptr, nullptr};
+        void drop() {
+            for (int d = 0; d < 2; ++d) {
+                if (exec[d]) (void)hipGraphExecDestroy(exec[d]);
+                if (graph[d]) (void)hipGraphDestroy(graph[d]);
+                exec[d] = nullptr;
+                graph[d] = nullptr;
+            }
+            nf = -1;
+        }
+    };
+    Graphs sets[3];
 
     void drop_graph() {
-        for (int d = 0; d < 2; ++d) {
-            if (exec[d]) (void)hipGraphExecDestroy(exec[d]);
-            if (graph[d]) (void)hipGraphDestroy(graph[d]);
-            exec[d] = nullptr;
-            graph[d] = nullptr;
-        }
-        g_nf = -1;
+        for (Graphs& G : sets) G.drop();
     }
     // No destructor work: at process exit the HIP runtime may already be torn
     // down, and the device memory (about 0.4 MB per host thread) is reclaimed
@@ -323,12 +343,15 @@ struct EngineCtx {
         return MSZ_OK;
     }
 
-    // (Re)builds the graphs when the topology changed.  A batch's table holds
-    // its n2 2D fields first, then its 3D fields.
-    int graph_for(int nf, int n2, bool timing, int grid2, int grid3) {
-        if (g_nf == nf && g_n2 == n2 && g_timing == timing && g_grid2 == grid2 && g_grid3 == grid3)
+    // (Re)builds the graphs of a set when the topology changed: `steps` steps
+    // for one field, kGraphSteps for a batch.  A batch's table holds its n2 2D
+    // fields first, then its 3D fields.
+    int graph_for(Graphs& G, int nf, int n2, bool timing, int grid2, int grid3, int steps) {
+        if (G.nf == nf && G.n2 == n2 && G.timing == timing && G.grid2 == grid2 && G.grid3 == grid3)
             return MSZ_OK;
-        drop_graph();
+        G.drop();
+        hipGraph_t(&graph)[2] = G.graph;
+        hipGraphExec_t(&exec)[2] = G.exec;
         hipGraph_t gcur = nullptr;
         hipGraphNode_t last = nullptr;
         // a kernel node after the last one added to the current graph
@@ -351,7 +374,7 @@ struct EngineCtx {
             gcur = graph[0];
             const void* fn = eng_step1_kernel(has3 ? 3 : 2);
             const int grid = has3 ? grid3 : grid2;
-            for (int st = 0; st < kGraphSteps; ++st) {
+            for (int st = 0; st < steps; ++st) {
                 unsigned long long* ts = timing ? tstamp + 2 * st * kEngStampWords : nullptr;
                 int* log = timing ? oplog : nullptr;
                 int stp = st;
@@ -390,11 +413,11 @@ struct EngineCtx {
             }
             if (hipGraphInstantiate(&exec[d], graph[d], nullptr, nullptr, 0) != hipSuccess) return MSZ_EDEVICE;
         }
-        g_nf = nf;
-        g_n2 = n2;
-        g_timing = timing;
-        g_grid2 = grid2;
-        g_grid3 = grid3;
+        G.nf = nf;
+        G.n2 = n2;
+        G.timing = timing;
+        G.grid2 = grid2;
+        G.grid3 = grid3;
         return MSZ_OK;
     }
 };
@@ -435,6 +458,13 @@ int step_grid(int dev, int ndim, bool single) {
         cached_dev = dev;
     }
     return cached[(single ? 2 : 0) + (ndim == 3 ? 1 : 0)];
+}
+
+// Whether no operation of a field corrected alone has more work items than
+// kSmallGrid (chunks, label tiles and direction columns).
+bool small_field(const EngField& F) {
+    return eng_items_host(F, kOpPreA) <= kSmallGrid && eng_items_host(F, kOpRTile) <= kSmallGrid &&
+           eng_items_host(F, kOpPreE) <= kSmallGrid;
 }
 
 // Schedule of the calling thread's last timed single-field run: the phase of
@@ -528,7 +558,11 @@ int run_engine(std::vector<EngField>& hf, std::vector<EngStats>& st, bool timing
         const int64_t chunks = (static_cast<int64_t>(tab[0].gr.n) + kEngChunk - 1) / kEngChunk;
         tab[0].sum = chunks >= static_cast<int64_t>(kSelectChunks) * (has3 ? grid3 : grid2) ? 1 : 0;
     }
-    if (int rc = E.graph_for(nf, n2, timing, grid2, grid3)) {
+    const bool small = single && !timing && small_field(tab[0]);
+    if (small) grid2 = std::min(grid2, kSmallGrid), grid3 = std::min(grid3, kSmallGrid);
+    EngineCtx::Graphs& graphs = E.sets[single ? (small ? 2 : 1) : 0];
+    const int launch_steps = small ? kSmallSteps : kGraphSteps;
+    if (int rc = E.graph_for(graphs, nf, n2, timing, grid2, grid3, launch_steps)) {
         E.drop_graph();
         return rc;
     }
@@ -588,7 +622,7 @@ int run_engine(std::vector<EngField>& hf, std::vector<EngStats>& st, bool timing
     };
     auto launch_chain = [&](int d) {
         chain_steps[d] += kGraphSteps;
-        return hipGraphLaunch(E.exec[d], E.cs[d]) == hipSuccess && hipEventRecord(E.ev[1 + d], E.cs[d]) == hipSuccess;
+        return hipGraphLaunch(graphs.exec[d], E.cs[d]) == hipSuccess && hipEventRecord(E.ev[1 + d], E.cs[d]) == hipSuccess;
     };
     auto caller_after_chains = [&]() {
         for (int d = 0; d < 2; ++d)
@@ -599,12 +633,12 @@ int run_engine(std::vector<EngField>& hf, std::vector<EngStats>& st, bool timing
         // Relaunch until the device clears the done word (pinned host memory):
         // no read-back copy per launch.
         for (;;) {
-            if (hipGraphLaunch(E.exec[0], s) != hipSuccess || hipEventRecord(E.ev[0], s) != hipSuccess ||
+            if (hipGraphLaunch(graphs.exec[0], s) != hipSuccess || hipEventRecord(E.ev[0], s) != hipSuccess ||
                 hipEventSynchronize(E.ev[0]) != hipSuccess) {
                 rc = MSZ_EDEVICE;
                 break;
             }
-            steps += kGraphSteps;
+            steps += launch_steps;
             if (*flag == 0) break;
             if (steps > max_steps) { rc = MSZ_EDEVICE; break; }
         }
@@ -640,7 +674,7 @@ int run_engine(std::vector<EngField>& hf, std::vector<EngStats>& st, bool timing
         if (hipMemsetAsync(E.tstamp, 0, EngineCtx::stamp_bytes(), s) != hipSuccess) { rc = MSZ_EDEVICE; break; }
         bool launched[2] = {live[0], live[1]};
         if (single) {
-            if (hipGraphLaunch(E.exec[0], s) != hipSuccess) { rc = MSZ_EDEVICE; break; }
+            if (hipGraphLaunch(graphs.exec[0], s) != hipSuccess) { rc = MSZ_EDEVICE; break; }
         } else {
             bool ok = chains_after_caller();
             for (int d = 0; ok && d < 2; ++d)
@@ -825,8 +859,11 @@ int run_noalloc(EngField F, char* base, int64_t max_steps, EngStats& out, hipStr
     int* lp = reinterpret_cast<int*>(base + c.ctl);
     unsigned* cp = reinterpret_cast<unsigned*>(base + c.cnt3);
     int* wp = reinterpret_cast<int*>(base + c.words);
-    const int grid = step_grid(dev, F.gr.ndim, true);
-    if (grid < 1) return MSZ_EDEVICE;
+    const int resident = step_grid(dev, F.gr.ndim, true);
+    if (resident < 1) return MSZ_EDEVICE;
+    const bool small = small_field(F);
+    const int grid = small ? std::min(resident, kSmallGrid) : resident;
+    const int launch_steps = small ? kSmallSteps : kGraphSteps;
     F.cnt = cp;
     {
         void* a[] = {&F, &fp, &sp, &tp, &cp, &lp, &wp};
@@ -840,14 +877,14 @@ int run_noalloc(EngField F, char* base, int64_t max_steps, EngStats& out, hipStr
     int words[128];
     static_assert(sizeof(words) == 512, "the done word block");
     for (int64_t steps = 0;;) {
-        for (int k = 0; k < kGraphSteps; ++k) {
+        for (int k = 0; k < launch_steps; ++k) {
             int kk = k;
             void* a[] = {&fp, &sp, &sp, &tp, &cp, &lp, &wp, &no_log, &kk, &no_stamps};
             MSZ_HIP(hipLaunchKernel(fn, dim3(grid), dim3(256), a, 0, s));
         }
         MSZ_HIP(hipMemcpyAsync(words, wp, sizeof(words), hipMemcpyDeviceToHost, s));
         MSZ_HIP(hipStreamSynchronize(s));
-        steps += kGraphSteps;
+        steps += launch_steps;
         if (words[0] == 0) break;
         if (steps > max_steps) return MSZ_EDEVICE;
     }

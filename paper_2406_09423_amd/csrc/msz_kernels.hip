@@ -1632,15 +1632,23 @@ static int blocks_for(long work, int per_block, int cap = 1 << 20) {
 struct DirsVariant {
     int ty, zc;
 };
-// Tile variants of the direction kernel selectable per call (index 1..);
-// index 0 is the default (2D: 64 x 16 tiles; 3D: 64 x 16 x 16 columns).
-__host__ __device__ inline DirsVariant variant_of(int ndim, int v) {
-    if (ndim == 2) return v == 2 ? DirsVariant{32, 1} : DirsVariant{16, 1};
+// Tile variants of the direction kernel selectable per call (index 1..), and
+// the default (index 0): 2D 64 x 16 tiles; 3D 64 x 16 columns of 16 planes,
+// or of 4 when 16 would leave fewer than kMinColumns columns (a column is a
+// serial chain of its planes, two of them halo): the pass over 177x95x48 takes
+// 45 us with 54 columns of 16 planes, 25 with 216 of 4 (with the cases 66, 30).
+constexpr int kMinColumns = 512;
+__host__ __device__ inline DirsVariant variant_of(const Grid& gr, int v) {
+    if (gr.ndim == 2) return v == 2 ? DirsVariant{32, 1} : DirsVariant{16, 1};
     switch (v) {
+        case 1: return {16, 16};
         case 2: return {16, 8};
         case 3: return {16, 32};
         case 4: return {32, 16};
-        default: return {16, 16};
+        default: {
+            const int columns = ((gr.nx + kTileX - 1) / kTileX) * ((gr.ny + 15) / 16) * ((gr.nz + 15) / 16);
+            return columns < kMinColumns ? DirsVariant{16, 4} : DirsVariant{16, 16};
+        }
     }
 }
 
@@ -1662,11 +1670,12 @@ static void launch_dirs_t(const float* h, const Grid& gr, uint8_t* dirs_out, hip
 
 void launch_dirs(const float* h, const Grid& gr, int variant, uint8_t* dirs_out, hipStream_t s) {
     if (gr.ndim == 2) {
-        if (variant_of(2, variant).ty == 32) launch_dirs_t<2, 32, 1>(h, gr, dirs_out, s);
+        if (variant_of(gr, variant).ty == 32) launch_dirs_t<2, 32, 1>(h, gr, dirs_out, s);
         else launch_dirs_t<2, 16, 1>(h, gr, dirs_out, s);
     } else {
-        const DirsVariant v = variant_of(3, variant);
+        const DirsVariant v = variant_of(gr, variant);
         if (v.ty == 32) launch_dirs_t<3, 32, 16>(h, gr, dirs_out, s);
+        else if (v.zc == 4) launch_dirs_t<3, 16, 4>(h, gr, dirs_out, s);
         else if (v.zc == 8) launch_dirs_t<3, 16, 8>(h, gr, dirs_out, s);
         else if (v.zc == 32) launch_dirs_t<3, 16, 32>(h, gr, dirs_out, s);
         else launch_dirs_t<3, 16, 16>(h, gr, dirs_out, s);
@@ -1728,7 +1737,7 @@ void launch_check_finite(const float* h, int n, unsigned* cnt, hipStream_t s) {
 // invalidate the L2 of each XCD).
 
 __host__ __device__ inline int dirs_items_of(const Grid& gr, int variant) {
-    const DirsVariant v = variant_of(gr.ndim, variant);
+    const DirsVariant v = variant_of(gr, variant);
     const int tx = (gr.nx + kTileX - 1) / kTileX, ty = (gr.ny + v.ty - 1) / v.ty;
     const int tz = gr.ndim == 3 ? (gr.nz + v.zc - 1) / v.zc : 1;
     return tx * ty * tz;
@@ -1757,7 +1766,7 @@ int eng_items_host(const EngField& F, int op) { return eng_items(F, op); }
 // count (per 4096 vertices, 2D and 3D: 8.3 and 14.3 us for the directions of
 // f, 11.2 and 19.5 with the cases).
 __host__ __device__ inline int eng_weight(const EngField& F, int op) {
-    const DirsVariant v = variant_of(F.gr.ndim, F.variant);
+    const DirsVariant v = variant_of(F.gr, F.variant);
     const bool three = F.gr.ndim == 3;
     const int dv = kTileX * v.ty * (three ? v.zc : 1);  // vertices of a direction item
     auto dirs = [&](int per4096) { return (per4096 * dv + kEngChunk - 1) / kEngChunk; };
@@ -1786,11 +1795,12 @@ __device__ __forceinline__ void eng_dirs(const EngField& F, const float* h, uint
     const Grid& gr = F.gr;
     const CaseArrays ca{F.cases, F.dirty, F.marks};
     if constexpr (NDIM == 2) {
-        if (variant_of(2, F.variant).ty == 32) dirs_stream<2, 32, 1, MODE>(h, gr, r, out, F.dirs_f, ca, sm, c);
+        if (variant_of(gr, F.variant).ty == 32) dirs_stream<2, 32, 1, MODE>(h, gr, r, out, F.dirs_f, ca, sm, c);
         else dirs_stream<2, 16, 1, MODE>(h, gr, r, out, F.dirs_f, ca, sm, c);
     } else {
-        const DirsVariant v = variant_of(3, F.variant);
+        const DirsVariant v = variant_of(gr, F.variant);
         if (v.ty == 32) dirs_stream<3, 32, 16, MODE>(h, gr, r, out, F.dirs_f, ca, sm, c);
+        else if (v.zc == 4) dirs_stream<3, 16, 4, MODE>(h, gr, r, out, F.dirs_f, ca, sm, c);
         else if (v.zc == 8) dirs_stream<3, 16, 8, MODE>(h, gr, r, out, F.dirs_f, ca, sm, c);
         else if (v.zc == 32) dirs_stream<3, 16, 32, MODE>(h, gr, r, out, F.dirs_f, ca, sm, c);
         else dirs_stream<3, 16, 16, MODE>(h, gr, r, out, F.dirs_f, ca, sm, c);
@@ -2333,8 +2343,8 @@ __device__ __forceinline__ SparseResult sparse_rounds(const EngField& F, int typ
 // Vertices of the direction work items [lo, hi) of F.
 template <int NDIM>
 __device__ __forceinline__ long long dirs_vertices(const EngField& F, int lo, int hi) {
-    const DirsVariant v = variant_of(NDIM, F.variant);
     const Grid& gr = F.gr;
+    const DirsVariant v = variant_of(gr, F.variant);
     const int tx = (gr.nx + kTileX - 1) / kTileX, ty = (gr.ny + v.ty - 1) / v.ty;
     const int zc = NDIM == 3 ? v.zc : 1;
     long long n = 0;
