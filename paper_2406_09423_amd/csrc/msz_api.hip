@@ -756,8 +756,10 @@ int run_engine(std::vector<EngField>& hf, std::vector<EngStats>& st, bool timing
     return MSZ_OK;
 }
 
+// Workspace pointers and item counts of a field whose grid and variant are set.
 void bind_field(EngField& F, char* w) {
     const Layout l = layout_for(F.gr);
+    eng_count_items(F);
     F.L = reinterpret_cast<float*>(w + l.L);
     F.g = reinterpret_cast<float*>(w + l.g);
     F.dirs_f = reinterpret_cast<uint8_t*>(w + l.dirs_f);

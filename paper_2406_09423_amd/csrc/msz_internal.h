@@ -216,6 +216,7 @@ struct SparseBuf {
 struct EngField {
     Grid gr;
     int variant;
+    int chunks, tiles, columns;  // work items per operation (eng_count_items)
     int merged;      // 1: merged C rounds
     int preempt;     // 1: shared targets edited without claims (preemptive mode; implies merged)
     int count_init;  // 1: label the start field once and count its mislabelled vertices
@@ -253,6 +254,7 @@ struct EngStats {
 };
 
 // Number of work items of operation op for one field (device and host).
+void eng_count_items(EngField& F);  // needs F.gr and F.variant
 int eng_items_host(const EngField& F, int op);
 int eng_weight_host(const EngField& F, int op);  // cost units of one item (batch splits)
 int label_tile_count(const Grid& gr);   // label tiles of the grid

@@ -1743,15 +1743,21 @@ __host__ __device__ inline int dirs_items_of(const Grid& gr, int variant) {
     return tx * ty * tz;
 }
 
+// The numbers of work items of a field's operations, kept in its table entry:
+// every step's decision needs one, and forming it there (divisions by the
+// tiles' sides, in the one thread that decides) is on every block's path.
+void eng_count_items(EngField& F) {
+    F.chunks = (F.gr.n + kEngChunk - 1) / kEngChunk;
+    F.tiles = label_tiles_of(F.gr);
+    F.columns = dirs_items_of(F.gr, F.variant);
+}
+
 __host__ __device__ inline int eng_items(const EngField& F, int op) {
-    const int chunks = (F.gr.n + kEngChunk - 1) / kEngChunk;
-    const int tiles = label_tiles_of(F.gr);
-    const int dirs = dirs_items_of(F.gr, F.variant);
     switch (op) {
         case kOpPreA: case kOpApplyC: case kOpSparseC: case kOpRefreshC: case kOpRefreshR: case kOpDelta:
-            return chunks;
-        case kOpPreB: case kOpPreD: case kOpRTile: case kOpRDetect: return tiles;
-        case kOpPreA2: case kOpPreE: case kOpFullC: case kOpFullR: return dirs;
+            return F.chunks;
+        case kOpPreB: case kOpPreD: case kOpRTile: case kOpRDetect: return F.tiles;
+        case kOpPreA2: case kOpPreE: case kOpFullC: case kOpFullR: return F.columns;
         default: return 0;
     }
 }
@@ -3067,9 +3073,23 @@ __global__ void __launch_bounds__(256) k_eng_step1(const EngField* __restrict__ 
     const EngState st = s_next;
     unsigned long long acct = 0;
     if (st.items > 0) {
+        // shares of ceil(items / nb) for the first blocks, which keeps the
+        // items of small steps on few XCDs; but where there are fewer items
+        // than blocks, though more than one XCD's blocks, one item each for
+        // blocks spread over all XCDs: block b takes item floor((b + 1) items
+        // / nb) - 1 if that is past floor(b items / nb) - 1 (in doubles, whose
+        // added half keeps the product away from the quotient's integers).
+        // 1795x1153 (506 chunks on 1024 blocks) 1.18 ms spread, 1.29 not;
+        // 128x128 (4 chunks on 256) 0.505 and 0.490, 3600x2400 (2110 chunks,
+        // even shares of two and three against 704 of three) 1.72 and 1.70.
         const int nb = gridDim.x, b = xcd_logical_block(blockIdx.x, nb);
         const int per = (st.items + nb - 1) / nb;
-        const int lo = b * per, hi = min(st.items, lo + per);
+        int lo = b * per, hi = min(st.items, lo + per);
+        if (per == 1 && 8 * st.items > nb) {
+            const double inv = 1.0 / nb, items = st.items;
+            lo = static_cast<int>((b * items + 0.5) * inv);
+            hi = static_cast<int>(((b + 1) * items + 0.5) * inv);
+        }
         if (lo < hi) eng_run_range<NDIM, true>(F, st, lo, hi, smem, c_cur, acct);
         if (st.op == kOpSparseC && lo < hi && draw_last(&F.sparse->ticket, (st.items + per - 1) / per, &s_flag)) {
             const int cs[4] = {s_stats.cases[0], s_stats.cases[1], s_stats.cases[2], s_stats.cases[3]};
