@@ -28,7 +28,7 @@ enum : int {
     kCntWrongMin = 12,
     kCntSlots = 16
 };
-enum : unsigned { kErrNonFinite = 1u, kErrBound = 2u, kErrWarmNonFinite = 4u, kErrWarmBound = 8u, kErrWalk = 16u };
+enum : unsigned { kErrNonFinite = 1u, kErrBound = 2u, kErrWarmNonFinite = 4u, kErrWarmBound = 8u, kErrWalk = 16u, kErrLong = 32u };
 
 // Exact quotients of ids (0 <= i < 2^31) by a fixed divisor d: with
 // l = ceil(log2 d) and m = floor(2^(31 + l) / d) + 1 <= 2^32 - 1,
@@ -140,10 +140,16 @@ struct Scratch {
     int get(void* user, size_t user_bytes, size_t need, hipStream_t stream);
 };
 
-void launch_check_finite(const float* h, int n, unsigned* cnt, hipStream_t s);
-void launch_dirs(const float* h, const Grid& gr, int variant, uint8_t* dirs_out, hipStream_t s);
-void launch_label_tile(const uint8_t* dirs, const Grid& gr, int* q_up, int* q_dn, hipStream_t s);
-void launch_label_compress(const Grid& gr, int* q_up, int* q_dn, unsigned* cnt, hipStream_t s);
+// cnt: where a non-finite value is reported (NULL: not checked)
+void launch_dirs(const float* h, const Grid& gr, uint8_t* dirs_out, unsigned* cnt, hipStream_t s);
+// Labels and their comparison straight from tile codes; kErrLong is reported
+// where a chain is too long for that.
+void launch_label_codes(const uint8_t* dirs, const Grid& gr, uint16_t* q_up, uint16_t* q_dn, hipStream_t s);
+void launch_label_direct(const uint16_t* q_up, const uint16_t* q_dn, const Grid& gr, int* M, int* m, unsigned* cnt,
+                         hipStream_t s);
+void launch_compare_direct(const uint8_t* dirs_f, const uint8_t* dirs_g, const uint16_t* qfu, const uint16_t* qfd,
+                           const uint16_t* qgu, const uint16_t* qgd, const Grid& gr, unsigned* cnt, hipStream_t s);
+// The same through compressed pointers, for any chains.
 void launch_label_forests(const uint8_t* dirs, const Grid& gr, int* q_up, int* q_dn, unsigned* cnt,
                           hipStream_t s);
 void launch_label_final(const int* q_up, const int* q_dn, const Grid& gr, int* M, int* m, unsigned* cnt,

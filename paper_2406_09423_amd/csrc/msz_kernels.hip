@@ -158,15 +158,6 @@ __device__ __forceinline__ void validate_group(const float* __restrict__ f, cons
     }
 }
 
-// Finite-value check of a field handed to msz_labels / msz_count_false.
-__global__ void __launch_bounds__(256) k_check_finite(const float* __restrict__ h, int n,
-                                                      unsigned* __restrict__ cnt) {
-    unsigned bad = 0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        if (!value_ok(h[i])) bad = kErrNonFinite;
-    if (bad) atomicOr(cnt + kCntErr, bad);
-}
-
 // ------------------------------------------------------------ detection ---
 
 // The four C-loop predicates (Defs. 1-3) of a vertex from its packed
@@ -228,6 +219,7 @@ struct CaseArrays {
 //
 // MODE 0: write dirs only.  MODE 1: also write the case bits of every vertex
 // against dirs_f, count each type and clear the dirty flags and marks.
+// MODE 2: write dirs and set c[0] if a value is not finite (or too large).
 
 // Maps the hardware block id to a tile so that consecutive tiles land on the
 // same XCD (blocks are dealt to the 8 XCDs round-robin).
@@ -492,6 +484,7 @@ __device__ __forceinline__ void dirs_compute(const float* C, const float* A, con
                     b.above(ap.at(k), 10);
                     b.above(ap.at(k + 1), 12);
                 }
+                if constexpr (MODE == 2) c[0] |= !value_ok(v);
                 const unsigned packed = (b.us << 4) | b.ds;
                 out4 = (out4 & ~(0xFFu << (8 * k))) | (packed << (8 * k));
                 if (!full) dirs_out[i0 + k] = static_cast<uint8_t>(packed);
@@ -563,15 +556,18 @@ __device__ __forceinline__ void dirs_stream(const float* __restrict__ h, const G
     }
 }
 
-// Directions only (msz_labels, msz_count_false and the network features).
-template <int NDIM, int TY, int ZC>
-__global__ void __launch_bounds__(256) k_dirs(const float* __restrict__ h, Grid gr, uint8_t* __restrict__ dirs_out) {
+// Directions only (msz_labels and msz_count_false, which check the values in
+// the same pass and report to cnt; the network features, cnt NULL).
+template <int NDIM, int TY, int ZC, int MODE>
+__global__ void __launch_bounds__(256) k_dirs(const float* __restrict__ h, Grid gr, uint8_t* __restrict__ dirs_out,
+                                              unsigned* __restrict__ cnt) {
     using G = DirsGeom<NDIM, TY, ZC>;
     static_assert(TY % 16 == 0, "a thread row covers 16 tile rows");
     __shared__ __align__(16) float sm[G::NP * G::P];
     unsigned c[4] = {0u, 0u, 0u, 0u};
     const CaseArrays none{nullptr, nullptr, nullptr};
-    dirs_stream<NDIM, TY, ZC, 0>(h, gr, xcd_items(G(gr).items()), dirs_out, nullptr, none, sm, c);
+    dirs_stream<NDIM, TY, ZC, MODE>(h, gr, xcd_items(G(gr).items()), dirs_out, nullptr, none, sm, c);
+    if (MODE == 2 && c[0]) atomicOr(cnt + kCntErr, kErrNonFinite);
 }
 
 // ---------------------------------------------------------------- apply ---
@@ -891,20 +887,21 @@ __device__ __forceinline__ void follow_roots(const int* q_up, const int* q_dn, i
     }
 }
 
-// The same over arrays of TileCodes: chain k in q_up, or in q_dn when dn[k];
+// The same over arrays of TileCodes, with at most CAP gathers per chain (err
+// is set in bad when a chain is longer): chain k in q_up, or in q_dn when dn[k];
 // from S on, in a second pair of forests, r_up and r_dn.  (The forest is
 // chosen at each load: a pointer per chain would cost two registers each.)
-template <int NDIM, int K, int S>
+template <int NDIM, int K, int S, int CAP = kMaxChain>
 __device__ __forceinline__ void follow_codes(const Grid& gr, const uint16_t* q_up, const uint16_t* q_dn,
                                              const uint16_t* r_up, const uint16_t* r_dn, const bool (&dn)[K],
-                                             int (&y)[K], unsigned& bad, unsigned& hops) {
+                                             int (&y)[K], unsigned& bad, unsigned& hops, unsigned err = kErrWalk) {
     for (int pass = 0;; ++pass) {
         bool any = false;
 #pragma unroll
         for (int k = 0; k < K; ++k) any |= y[k] < 0;
         if (!any) return;
-        if (pass == kMaxChain) {
-            bad = kErrWalk;
+        if (pass == CAP) {
+            bad |= err;
 #pragma unroll
             for (int k = 0; k < K; ++k) y[k] = max(y[k], 0);
             return;
@@ -1066,10 +1063,9 @@ __device__ __forceinline__ void label_tile_body(const uint8_t* __restrict__ dirs
     }
 }
 
-template <int NDIM>
+template <int NDIM, typename Out>
 __global__ void __launch_bounds__(256) k_label_tile(const uint8_t* __restrict__ dirs, Grid gr,
-                                                    int* __restrict__ q_up,
-                                                    int* __restrict__ q_dn) {
+                                                    Out* __restrict__ q_up, Out* __restrict__ q_dn) {
     constexpr int NT = LabelTile<NDIM>::X * LabelTile<NDIM>::Y * LabelTile<NDIM>::Z;
     __shared__ __align__(16) uint16_t su[NT];
     __shared__ __align__(16) uint16_t sd[NT];
@@ -1220,6 +1216,16 @@ __device__ __forceinline__ TileGroup<NDIM> tile_group(const Grid& gr, int tile, 
     return g;
 }
 
+// The codes of a group's vertices (zeros past its count).
+__device__ __forceinline__ Shorts4 load_codes4(const uint16_t* q, int i0, int count) {
+    if (count == 4) return *reinterpret_cast<const Shorts4*>(q + i0);
+    Shorts4 v{0u, 0u};
+    if (count > 0) v.x = q[i0];
+    if (count > 1) v.x |= static_cast<unsigned>(q[i0 + 1]) << 16;
+    if (count > 2) v.y = q[i0 + 2];
+    return v;
+}
+
 // Writes the final labels (the root at the end of each vertex's chain), tile
 // by tile; returns kErrWalk if a chain hit the step cap.  May run in place
 // (M == q_up, m == q_dn): a value read is then a pointer along the chain or,
@@ -1276,6 +1282,61 @@ __global__ void __launch_bounds__(256) k_label_final(const int* q_up, const int*
     unsigned bad = 0, hops = 0;
     for (int tile = range.first; tile < range.hi; tile += range.stride)
         bad |= label_final_tile<NDIM>(q_up, q_dn, gr, tile, M, m, hops);
+    if (bad) atomicOr(cnt + kCntErr, bad);
+}
+
+// Labels straight from the tile codes: every vertex follows its own chain.
+// The chains of measured fields cross 0.3 tiles on average and at most 9; a
+// chain of more than kDirectHops (a line that winds through the whole grid, of
+// which there may be one per vertex) sets kErrLong, and the caller then takes
+// the route through compressed pointers, which halves such chains instead of
+// walking each.  Against that route (ids out, three compressions, final
+// labels) the two int32 forests are not stored and read back four times:
+// labels of a 256^3 field 267 -> 227 us, the comparison of two 3600 x 2400
+// fields 195 -> 167 us (calls timed whole, with the value check in the
+// direction pass instead of a pass of its own).
+constexpr int kDirectHops = 64;
+template <int NDIM>
+__global__ void __launch_bounds__(256) k_label_direct(const uint16_t* __restrict__ q_up,
+                                                      const uint16_t* __restrict__ q_dn, Grid gr,
+                                                      int* __restrict__ M, int* __restrict__ m,
+                                                      unsigned* __restrict__ cnt) {
+    using C = TileCode<NDIM>;
+    const ItemRange range = xcd_items(label_tiles_of(gr));
+    unsigned bad = 0, hops = 0;
+    for (int tile = range.first; tile < range.hi; tile += range.stride) {
+        const int3 o = tile_origin<NDIM>(gr, tile);
+        const unsigned corner = C::corner(gr, o.x, o.y, o.z);
+        TileGroup<NDIM> tg[4];
+        Shorts4 u[4], d[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            tg[k] = tile_group<NDIM>(gr, tile, k);
+            u[k] = load_codes4(q_up, tg[k].i0, tg[k].count);
+            d[k] = load_codes4(q_dn, tg[k].i0, tg[k].count);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const unsigned cu[4] = {u[k].x & 0xFFFFu, u[k].x >> 16, u[k].y & 0xFFFFu, u[k].y >> 16};
+            const unsigned cd[4] = {d[k].x & 0xFFFFu, d[k].x >> 16, d[k].y & 0xFFFFu, d[k].y >> 16};
+            const bool dn[8] = {false, true, false, true, false, true, false, true};
+            int y[8];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                y[2 * j] = j < tg[k].count ? C::target(gr, corner, cu[j]) : 0;
+                y[2 * j + 1] = j < tg[k].count ? C::target(gr, corner, cd[j]) : 0;
+            }
+            follow_codes<NDIM, 8, 8, kDirectHops>(gr, q_up, q_dn, nullptr, nullptr, dn, y, bad, hops, kErrLong);
+            if (tg[k].vec) {
+                store_ints4(M + tg[k].i0, y[0], y[2], y[4], y[6]);
+                store_ints4(m + tg[k].i0, y[1], y[3], y[5], y[7]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (j < tg[k].count) M[tg[k].i0 + j] = y[2 * j], m[tg[k].i0 + j] = y[2 * j + 1];
+            }
+        }
+    }
     if (bad) atomicOr(cnt + kCntErr, bad);
 }
 
@@ -1576,6 +1637,69 @@ __global__ void __launch_bounds__(256) k_compare(const uint8_t* __restrict__ dir
     block_add<7>(c, cnt, idx);
 }
 
+// The same from tile codes, tile by tile (see k_label_direct).  A vertex whose
+// codes in g and f agree and end in the tile needs no walk.
+template <int NDIM>
+__global__ void __launch_bounds__(256) k_compare_direct(const uint8_t* __restrict__ dirs_f,
+                                                        const uint8_t* __restrict__ dirs_g,
+                                                        const uint16_t* __restrict__ qfu,
+                                                        const uint16_t* __restrict__ qfd,
+                                                        const uint16_t* __restrict__ qgu,
+                                                        const uint16_t* __restrict__ qgd, Grid gr,
+                                                        unsigned* __restrict__ cnt) {
+    using C = TileCode<NDIM>;
+    const ItemRange range = xcd_items(label_tiles_of(gr));
+    unsigned c[7] = {0, 0, 0, 0, 0, 0, 0}, cases[4] = {0, 0, 0, 0};
+    unsigned bad = 0, hops = 0;
+    for (int tile = range.first; tile < range.hi; tile += range.stride) {
+        const int3 o = tile_origin<NDIM>(gr, tile);
+        const unsigned corner = C::corner(gr, o.x, o.y, o.z);
+#pragma unroll 2
+        for (int k = 0; k < 4; ++k) {
+            const TileGroup<NDIM> t = tile_group<NDIM>(gr, tile, k);
+            unsigned df = 0u, dg = 0u;
+            if (t.vec) {
+                df = load_bytes4(dirs_f + t.i0);
+                dg = load_bytes4(dirs_g + t.i0);
+            } else {  // bytes past the count stay equal zeros: no case
+                for (int j = 0; j < t.count; ++j) {
+                    df |= static_cast<unsigned>(dirs_f[t.i0 + j]) << (8 * j);
+                    dg |= static_cast<unsigned>(dirs_g[t.i0 + j]) << (8 * j);
+                }
+            }
+            const Shorts4 fu = load_codes4(qfu, t.i0, t.count), fd = load_codes4(qfd, t.i0, t.count);
+            const Shorts4 gu = load_codes4(qgu, t.i0, t.count), gd = load_codes4(qgd, t.i0, t.count);
+            (void)cases4(df, dg, cases);
+            const unsigned a[4] = {gu.x, gu.y, gd.x, gd.y}, b[4] = {fu.x, fu.y, fd.x, fd.y};
+            // chains of g in 0..7 (ascents of the four vertices, then descents), of f in 8..15
+            int y[16];
+            bool dn[16];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const unsigned cg = (a[e >> 1] >> (16 * (e & 1))) & 0xFFFFu, cf = (b[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
+                const bool same = cg == cf && !(cg & C::kExit);
+                dn[e] = dn[8 + e] = e >= 4;
+                y[e] = same ? 0 : C::target(gr, corner, cg);
+                y[8 + e] = same ? 0 : C::target(gr, corner, cf);
+            }
+            follow_codes<NDIM, 16, 8, kDirectHops>(gr, qgu, qgd, qfu, qfd, dn, y, bad, hops, kErrLong);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool wM = y[j] != y[8 + j], wm = y[4 + j] != y[12 + j];
+                c[4] += wM;
+                c[5] += wm;
+                c[6] += wM || wm;
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) c[t] = cases[t];
+    const int idx[7] = {kCntCase + 0, kCntCase + 1, kCntCase + 2, kCntCase + 3,
+                        kCntWrongMax, kCntWrongMin, kCntWrong};
+    if (bad) atomicOr(cnt + kCntErr, bad);
+    block_add<7>(c, cnt, idx);
+}
+
 // ---------------------------------------------------------------- output ---
 //
 // delta = fl(g - fhat); when fl(fhat + delta) misses g, the floats up to two
@@ -1654,38 +1778,57 @@ __host__ __device__ inline DirsVariant variant_of(const Grid& gr, int v) {
 
 int tile_variant_count(int ndim) { return ndim == 2 ? 2 : 4; }
 
+__host__ __device__ inline int dirs_items_of(const Grid& gr, int variant) {
+    const DirsVariant v = variant_of(gr, variant);
+    const int tx = (gr.nx + kTileX - 1) / kTileX, ty = (gr.ny + v.ty - 1) / v.ty;
+    const int tz = gr.ndim == 3 ? (gr.nz + v.zc - 1) / v.zc : 1;
+    return tx * ty * tz;
+}
+
 // Persistent grid: at most kDirsBlocks blocks (8 per compute unit), each walking
 // a contiguous run of work items of its XCD.
 constexpr int kDirsBlocks = 2048;
 
-template <int NDIM, int TY, int ZC>
-static void launch_dirs_t(const float* h, const Grid& gr, uint8_t* dirs_out, hipStream_t s) {
-    const int tx = (gr.nx + kTileX - 1) / kTileX;
-    const int ty = (gr.ny + TY - 1) / TY;
-    const int tz = NDIM == 3 ? (gr.nz + ZC - 1) / ZC : 1;
-    const int items = tx * ty * tz;
-    const int nb = items < kDirsBlocks ? items : kDirsBlocks;
-    hipLaunchKernelGGL((k_dirs<NDIM, TY, ZC>), dim3(nb), dim3(256), 0, s, h, gr, dirs_out);
+template <int NDIM, int ZC>
+static void launch_dirs_t(const float* h, const Grid& gr, uint8_t* dirs_out, unsigned* cnt, hipStream_t s) {
+    const int items = dirs_items_of(gr, 0);
+    const dim3 nb(items < kDirsBlocks ? items : kDirsBlocks);
+    if (cnt) hipLaunchKernelGGL((k_dirs<NDIM, 16, ZC, 2>), nb, dim3(256), 0, s, h, gr, dirs_out, cnt);
+    else hipLaunchKernelGGL((k_dirs<NDIM, 16, ZC, 0>), nb, dim3(256), 0, s, h, gr, dirs_out, cnt);
 }
 
-void launch_dirs(const float* h, const Grid& gr, int variant, uint8_t* dirs_out, hipStream_t s) {
-    if (gr.ndim == 2) {
-        if (variant_of(gr, variant).ty == 32) launch_dirs_t<2, 32, 1>(h, gr, dirs_out, s);
-        else launch_dirs_t<2, 16, 1>(h, gr, dirs_out, s);
-    } else {
-        const DirsVariant v = variant_of(gr, variant);
-        if (v.ty == 32) launch_dirs_t<3, 32, 16>(h, gr, dirs_out, s);
-        else if (v.zc == 4) launch_dirs_t<3, 16, 4>(h, gr, dirs_out, s);
-        else if (v.zc == 8) launch_dirs_t<3, 16, 8>(h, gr, dirs_out, s);
-        else if (v.zc == 32) launch_dirs_t<3, 16, 32>(h, gr, dirs_out, s);
-        else launch_dirs_t<3, 16, 16>(h, gr, dirs_out, s);
-    }
+// The default variant's tiles.
+void launch_dirs(const float* h, const Grid& gr, uint8_t* dirs_out, unsigned* cnt, hipStream_t s) {
+    if (gr.ndim == 2) launch_dirs_t<2, 1>(h, gr, dirs_out, cnt, s);
+    else if (variant_of(gr, 0).zc == 4) launch_dirs_t<3, 4>(h, gr, dirs_out, cnt, s);
+    else launch_dirs_t<3, 16>(h, gr, dirs_out, cnt, s);
 }
 
-void launch_label_tile(const uint8_t* dirs, const Grid& gr, int* q_up, int* q_dn, hipStream_t s) {
+template <typename Out>
+static void launch_label_tile(const uint8_t* dirs, const Grid& gr, Out* q_up, Out* q_dn, hipStream_t s) {
     const int nb = label_tiles_of(gr);
-    if (gr.ndim == 2) hipLaunchKernelGGL(k_label_tile<2>, dim3(nb), dim3(256), 0, s, dirs, gr, q_up, q_dn);
-    else hipLaunchKernelGGL(k_label_tile<3>, dim3(nb), dim3(256), 0, s, dirs, gr, q_up, q_dn);
+    if (gr.ndim == 2) hipLaunchKernelGGL((k_label_tile<2, Out>), dim3(nb), dim3(256), 0, s, dirs, gr, q_up, q_dn);
+    else hipLaunchKernelGGL((k_label_tile<3, Out>), dim3(nb), dim3(256), 0, s, dirs, gr, q_up, q_dn);
+}
+
+void launch_label_codes(const uint8_t* dirs, const Grid& gr, uint16_t* q_up, uint16_t* q_dn, hipStream_t s) {
+    launch_label_tile(dirs, gr, q_up, q_dn, s);
+}
+
+void launch_label_direct(const uint16_t* q_up, const uint16_t* q_dn, const Grid& gr, int* M, int* m, unsigned* cnt,
+                         hipStream_t s) {
+    const int nt = label_tiles_of(gr), nb = nt < kDirsBlocks ? nt : kDirsBlocks;
+    if (gr.ndim == 2) hipLaunchKernelGGL(k_label_direct<2>, dim3(nb), dim3(256), 0, s, q_up, q_dn, gr, M, m, cnt);
+    else hipLaunchKernelGGL(k_label_direct<3>, dim3(nb), dim3(256), 0, s, q_up, q_dn, gr, M, m, cnt);
+}
+
+void launch_compare_direct(const uint8_t* dirs_f, const uint8_t* dirs_g, const uint16_t* qfu, const uint16_t* qfd,
+                           const uint16_t* qgu, const uint16_t* qgd, const Grid& gr, unsigned* cnt, hipStream_t s) {
+    const int nt = label_tiles_of(gr), nb = nt < kDirsBlocks ? nt : kDirsBlocks;
+    if (gr.ndim == 2)
+        hipLaunchKernelGGL(k_compare_direct<2>, dim3(nb), dim3(256), 0, s, dirs_f, dirs_g, qfu, qfd, qgu, qgd, gr, cnt);
+    else
+        hipLaunchKernelGGL(k_compare_direct<3>, dim3(nb), dim3(256), 0, s, dirs_f, dirs_g, qfu, qfd, qgu, qgd, gr, cnt);
 }
 
 void launch_label_compress(const Grid& gr, int* q_up, int* q_dn, unsigned* cnt, hipStream_t s) {
@@ -1714,10 +1857,6 @@ void launch_compare(const uint8_t* dirs_f, const uint8_t* dirs_g, const int* qfu
                        qfu, qfd, qgu, qgd, n, cnt);
 }
 
-void launch_check_finite(const float* h, int n, unsigned* cnt, hipStream_t s) {
-    hipLaunchKernelGGL(k_check_finite, dim3(blocks_for(n, 256 * 4, kGridCap)), dim3(256), 0, s, h, n, cnt);
-}
-
 // ============================================================ batch engine ==
 //
 // The schedule of the correction loop (Sec. 5) runs on the device.  A step
@@ -1735,13 +1874,6 @@ void launch_check_finite(const float* h, int n, unsigned* cnt, hipStream_t s) {
 // the steps: every write of a step is visible to the next one without
 // device-scope fences inside a kernel (which on MI355X write back and
 // invalidate the L2 of each XCD).
-
-__host__ __device__ inline int dirs_items_of(const Grid& gr, int variant) {
-    const DirsVariant v = variant_of(gr, variant);
-    const int tx = (gr.nx + kTileX - 1) / kTileX, ty = (gr.ny + v.ty - 1) / v.ty;
-    const int tz = gr.ndim == 3 ? (gr.nz + v.zc - 1) / v.zc : 1;
-    return tx * ty * tz;
-}
 
 // The numbers of work items of a field's operations, kept in its table entry:
 // every step's decision needs one, and forming it there (divisions by the

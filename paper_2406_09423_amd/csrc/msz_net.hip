@@ -856,8 +856,8 @@ int features_impl(const float* f, const float* fhat, const Grid& gr, float xi, u
     const double range = static_cast<double>(hi) - static_cast<double>(lo);
     if (!(range > 0.0) || !std::isfinite(range)) return MSZ_EINVAL;
     const float xi_ch = static_cast<float>(std::log10(static_cast<double>(xi) / range) / 4.0 + 1.0);
-    launch_dirs(f, gr, 0, df, s);
-    launch_dirs(fhat, gr, 0, dh, s);
+    launch_dirs(f, gr, df, nullptr, s);
+    launch_dirs(fhat, gr, dh, nullptr, s);
     const int nt = ((gr.nx + kFeatX - 1) / kFeatX) * ((gr.ny + kFeatY - 1) / kFeatY) * ((gr.nz + kFeatZ - 1) / kFeatZ);
     hipLaunchKernelGGL(k_features, dim3(nt), dim3(256), 0, s, f, fhat, df, dh, gr, xi, xi_ch, feat);
     return hipGetLastError() == hipSuccess ? MSZ_OK : MSZ_EDEVICE;
