@@ -25,17 +25,18 @@
  *  - Streams: `stream` is a hipStream_t passed as void* (NULL = the default
  *    stream).  All work is enqueued on it; each call synchronises on it
  *    before returning.  The schedule of the loop runs on the device: a HIP
- *    graph of 48 steps is relaunched until the device clears a done word in
- *    pinned host memory.
- *  - Memory: the library allocates scratch per call when no workspace is
- *    given (hipMallocAsync on the stream), and keeps one control block
- *    (about 9 MB: field table, step states, round counters, statistics, the
- *    cached graph) and 512 bytes of pinned, device-mapped host memory (the
- *    done word and the final statistics of one-field runs) per host thread
- *    and device for the life of the process.  msz_fix_noalloc allocates
+ *    graph of 48 steps (30 for a small field alone) is relaunched until the
+ *    device clears a done word in pinned host memory.
+ *  - Memory: when no workspace is given, the library takes scratch for the
+ *    call, ordered on the stream, from a memory pool of its own, which keeps
+ *    at most 256 MB per device between calls.  It also keeps one control block
+ *    (about 9 MB: field table, step states, round counters, statistics) with
+ *    up to three cached graphs, and 512 bytes of pinned, device-mapped host
+ *    memory (the done word and the final statistics of one-field runs) per
+ *    host thread and device for the life of the process.  msz_fix_noalloc allocates
  *    nothing: it works in a static device array instead (see there).
  *  - Errors: the return code is the only error channel; no global state
- *    besides the control block above.  msz_strerror() names a code.  Inputs
+ *    besides the pool and control block above.  msz_strerror() names a code.  Inputs
  *    must be finite with magnitude at most 2^100 (so that no edit can
  *    overflow float32).
  *  - Concurrency: calls on different streams with separate workspaces are
@@ -97,8 +98,8 @@ enum {
 #define MSZ_FLAG_MERGED_C 2
 /* Count the mislabelled vertices of the start field (stats.mislabel_init:
  * the N_f of the right-labelled ratio before any edit, Appendix B).  This
- * costs one extra labelling of the start field (a label tile pass, the face
- * compression and a comparison pass), so it is opt-in; without the flag
+ * costs one extra labelling of the start field (a label tile pass and a
+ * comparison pass), so it is opt-in; without the flag
  * stats.mislabel_init is -1.  Accepted by msz_fix, msz_fix_batch and
  * msz_fix_learned (there the start field is the network's warm start). */
 #define MSZ_FLAG_COUNT_INIT 4
@@ -217,10 +218,9 @@ int msz_fix_noalloc(const float* f, const float* fhat, msz_dims d, float xi, flo
  * block's start and its last block's end, and the algorithmic bytes of the
  * units its blocks visited: per operation, the compulsory reads and writes of
  * each vertex of a visited direction or label tile, each scanned flag byte,
- * edit attempt, recomputed vertex, face-layer pointer, the two forests'
- * pointers of each vertex whose labels the troublemaker search resolves, and
- * each pointer load of an exit-chain walk or load or store of a compression
- * walk (halo and cache re-reads not counted). */
+ * edit attempt, recomputed vertex, the two forests' pointers of each vertex
+ * whose labels the troublemaker search resolves, and each pointer load of an
+ * exit-chain walk (halo and cache re-reads not counted). */
 enum {
     MSZ_KERNEL_STEP1_2D = 0, /* one field: the step kernel of a 2D field (decides and runs) */
     MSZ_KERNEL_STEP1_3D = 1,
@@ -347,8 +347,8 @@ size_t msz_edits_bound(int64_t n);
  * (DEVICE, 16-byte aligned, capacity bytes).  *out_bytes (HOST) receives the
  * encoded size; MSZ_EINVAL if it exceeds capacity (msz_edits_bound(n) always
  * suffices) or if the stream would pass 2^32 words (more than about 1.4e9
- * edits).  stats (HOST) may be NULL.  Allocates its scratch per call
- * (about 12 bytes per entry) on the stream and synchronises before returning. */
+ * edits).  stats (HOST) may be NULL.  Takes its scratch (about 8 bytes per
+ * edit) from the library's pool and synchronises before returning. */
 int msz_encode_edits(const float* edits, int64_t n, void* out, size_t capacity, size_t* out_bytes,
                      msz_edit_stats* stats, void* stream);
 
@@ -416,7 +416,8 @@ int msz_net_gradients(const float* params, const uint16_t* feat, const float* ta
 
 /* Training target: k_out[i] = the number of halvings that take fhat_i to g_i
  * (L from f and xi as in msz_fix), or -1 where g_i is not on that chain
- * within 256 steps.  All arrays DEVICE, n floats; scratch: n floats. */
+ * within 256 steps.  All arrays DEVICE, n floats;
+ * workspace (optional): n floats, not written. */
 int msz_net_halvings(const float* f, const float* fhat, const float* g, msz_dims d, float xi,
                      float* k_out, void* workspace, size_t workspace_bytes, void* stream);
 

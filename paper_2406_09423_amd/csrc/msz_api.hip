@@ -3,15 +3,15 @@
 // The schedule of the correction loop (Sec. 5) runs on the device (the
 // engine in msz_kernels.hip): every step runs one operation per field, and
 // the next operation of each field follows from its counters (decided inside
-// the step kernel for one field, by a decide kernel for a batch) --
+// the step kernel) --
 //   C phase  sub-loops FPmax, FPmin, FNmax, FNmin, each until it finds no case
 //            of its type, repeated until no false critical point remains (or,
 //            with MSZ_FLAG_MERGED_C, rounds over all four types at once);
 //   R phase  labels of g, then troublemaker detection, which also edits the
 //            troublemakers' targets; back to the C phase whenever those edits
 //            created a false critical point.
-// The host captures kGraphSteps steps in a HIP graph and relaunches it until
-// the device clears a done word in pinned host memory; a batch has one graph
+// The host captures kGraphSteps steps (kSmallSteps for a small field alone) in
+// a HIP graph and relaunches it until the device clears a done word in pinned host memory; a batch has one graph
 // and one stream per chain (its 2D fields, its 3D fields), each relaunched
 // on its own.  msz_fix runs the same schedule for one field.
 #include <algorithm>
@@ -230,7 +230,7 @@ static_assert(kGraphSteps % 2 == 0, "states alternate between two buffers");
 constexpr int kPreWords = kEngMaxFields + 2;
 
 // Per host thread and device: the engine's control block (device), a pinned
-// read-back word, and the graph of kGraphSteps steps for the last topology.
+// read-back word, and the graphs of the last topologies.
 struct EngineCtx {
     int device = -1;
     char* ctl_mem = nullptr;  // fields, states, stats, pre2, pre3, tick2, tick3, ctl, oplog
@@ -849,7 +849,7 @@ char* scratch_base(int dev) {
 }
 
 // The one-field schedule on the control block at `base`: the setup kernel,
-// then the step kernel launched kGraphSteps times between checks of the done
+// then the step kernel launched a graph's number of times between checks of the done
 // word (copied back into host stack memory), until the device lowers it.
 int run_noalloc(EngField F, char* base, int64_t max_steps, EngStats& out, hipStream_t s) {
     int dev = 0;

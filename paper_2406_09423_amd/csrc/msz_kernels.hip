@@ -734,15 +734,16 @@ __device__ __forceinline__ void target_edit(bool preempt, uint8_t* __restrict__ 
 // is then the end of a short chain of exits (on the fields here a tile exit
 // leads on through another tile a quarter of the time): follow_root walks it.
 // The correction loop follows the chains where it needs labels (a few
-// gathers per hundred vertices).  msz_labels and msz_count_false first
-// compress the exit targets' pointers to their roots (each thread walks its
-// own chain, writing back every step; any value read is an ancestor, so no
-// barrier is needed and each walk strictly advances).
+// gathers per hundred vertices), and so do msz_labels and msz_count_false.
+// Where a chain is too long for that (k_label_direct), these compress the exit
+// targets' pointers to their roots first (each thread walks its own chain,
+// writing back every step; any value read is an ancestor, so no barrier is
+// needed and each walk strictly advances).
 
 // Label tiles of 4096 vertices, wide in x: a tile row fills whole 128-byte
-// lines of the int32 arrays the label passes stream (16^3 tiles used half of
-// each line and fetched 2.8 times the pass's bytes); measured best among
-// 16x16x16, 32x16x8, 32x32x4, 64x16x4, 64x8x8 and 128x8x4 (3D) and 64x64,
+// lines of the label passes' int32 arrays and halves of their 16-bit ones
+// (with int32 arrays throughout, 16^3 tiles used half of each line and
+// fetched 2.8 times the pass's bytes); measured best among 16x16x16, 32x16x8, 32x32x4, 64x16x4, 64x8x8 and 128x8x4 (3D) and 64x64,
 // 128x32 and 256x16 (2D).
 template <int NDIM>
 struct LabelTile;
@@ -3119,9 +3120,8 @@ __global__ void __launch_bounds__(256) k_eng_step(const EngField* __restrict__ f
 // read and step k + 1 fills).  stats[2] receives the statistics once the
 // field is done; then the final statistics go to the done word block hflag
 // (pinned host memory, or device memory for the no-allocation entry point;
-// skipped when NULL) and its first word is cleared.  A
-// graph holds kEngTimeSlots (a multiple of 6) steps, so the parities continue
-// across launches.
+// skipped when NULL) and its first word is cleared.  A graph holds a multiple
+// of 6 steps, so the parities continue across launches.
 template <int NDIM>
 __global__ void __launch_bounds__(256) k_eng_step1(const EngField* __restrict__ fields, EngState* states,
                                                    const EngState* __restrict__ states_in, EngStats* stats,
