@@ -1638,9 +1638,15 @@ __global__ void __launch_bounds__(256) k_compare(const uint8_t* __restrict__ dir
     block_add<7>(c, cnt, idx);
 }
 
-// The same from tile codes, tile by tile (see k_label_direct).  A vertex whose
-// codes in g and f agree and end in the tile needs no walk.
-template <int NDIM>
+// The same from tile codes (see k_label_direct).  A vertex whose codes in g and
+// f agree and end in the tile needs no walk.  An item is a tile, or a quarter
+// of one (a row group per thread) where the tiles are fewer than the grid's
+// blocks: the walks of a block's groups one after the other then are the
+// kernel's time.  Whole calls: 40x50x60 127 us with tiles, 97 with quarters,
+// 100x110x120 145 and 125, 3600x2400 (2175 tiles) 174 and 175, 512^3 2.70 and
+// 2.78 ms.
+static_assert(LabelTile<2>::X * LabelTile<2>::Y == 4096, "four row groups per thread");
+template <int NDIM, int PARTS>
 __global__ void __launch_bounds__(256) k_compare_direct(const uint8_t* __restrict__ dirs_f,
                                                         const uint8_t* __restrict__ dirs_g,
                                                         const uint16_t* __restrict__ qfu,
@@ -1649,14 +1655,16 @@ __global__ void __launch_bounds__(256) k_compare_direct(const uint8_t* __restric
                                                         const uint16_t* __restrict__ qgd, Grid gr,
                                                         unsigned* __restrict__ cnt) {
     using C = TileCode<NDIM>;
-    const ItemRange range = xcd_items(label_tiles_of(gr));
+    const ItemRange range = xcd_items(PARTS * label_tiles_of(gr));
     unsigned c[7] = {0, 0, 0, 0, 0, 0, 0}, cases[4] = {0, 0, 0, 0};
     unsigned bad = 0, hops = 0;
-    for (int tile = range.first; tile < range.hi; tile += range.stride) {
+    for (int item = range.first; item < range.hi; item += range.stride) {
+        const int tile = item / PARTS;
         const int3 o = tile_origin<NDIM>(gr, tile);
         const unsigned corner = C::corner(gr, o.x, o.y, o.z);
 #pragma unroll 2
-        for (int k = 0; k < 4; ++k) {
+        for (int part = 0; part < 4 / PARTS; ++part) {
+            const int k = PARTS == 4 ? item & 3 : part;
             const TileGroup<NDIM> t = tile_group<NDIM>(gr, tile, k);
             unsigned df = 0u, dg = 0u;
             if (t.vec) {
@@ -1823,13 +1831,22 @@ void launch_label_direct(const uint16_t* q_up, const uint16_t* q_dn, const Grid&
     else hipLaunchKernelGGL(k_label_direct<3>, dim3(nb), dim3(256), 0, s, q_up, q_dn, gr, M, m, cnt);
 }
 
+template <int PARTS>
+static void launch_compare_direct_t(const uint8_t* df, const uint8_t* dg, const uint16_t* qfu, const uint16_t* qfd,
+                                    const uint16_t* qgu, const uint16_t* qgd, const Grid& gr, unsigned* cnt,
+                                    hipStream_t s) {
+    const int items = PARTS * label_tiles_of(gr);
+    const dim3 nb(items < kDirsBlocks ? items : kDirsBlocks);
+    if (gr.ndim == 2)
+        hipLaunchKernelGGL((k_compare_direct<2, PARTS>), nb, dim3(256), 0, s, df, dg, qfu, qfd, qgu, qgd, gr, cnt);
+    else
+        hipLaunchKernelGGL((k_compare_direct<3, PARTS>), nb, dim3(256), 0, s, df, dg, qfu, qfd, qgu, qgd, gr, cnt);
+}
+
 void launch_compare_direct(const uint8_t* dirs_f, const uint8_t* dirs_g, const uint16_t* qfu, const uint16_t* qfd,
                            const uint16_t* qgu, const uint16_t* qgd, const Grid& gr, unsigned* cnt, hipStream_t s) {
-    const int nt = label_tiles_of(gr), nb = nt < kDirsBlocks ? nt : kDirsBlocks;
-    if (gr.ndim == 2)
-        hipLaunchKernelGGL(k_compare_direct<2>, dim3(nb), dim3(256), 0, s, dirs_f, dirs_g, qfu, qfd, qgu, qgd, gr, cnt);
-    else
-        hipLaunchKernelGGL(k_compare_direct<3>, dim3(nb), dim3(256), 0, s, dirs_f, dirs_g, qfu, qfd, qgu, qgd, gr, cnt);
+    if (label_tiles_of(gr) < kDirsBlocks) launch_compare_direct_t<4>(dirs_f, dirs_g, qfu, qfd, qgu, qgd, gr, cnt, s);
+    else launch_compare_direct_t<1>(dirs_f, dirs_g, qfu, qfd, qgu, qgd, gr, cnt, s);
 }
 
 void launch_label_compress(const Grid& gr, int* q_up, int* q_dn, unsigned* cnt, hipStream_t s) {

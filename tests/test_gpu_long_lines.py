@@ -54,3 +54,16 @@ def test_lines_through_hundreds_of_tiles(msz, shape):
         want = oracle.count_false(a, b)
         for key in want:
             assert int(got[key]) == int(want[key]), key
+
+
+@pytest.mark.parametrize("shape", [(65472, 128), (65504, 128), (65505, 129), (7, 9, 64 * 682), (8, 16, 64 * 1024)])
+def test_counts_beside_the_tile_rule(msz, shape):
+    """2046, 2047 and 4096 label tiles in 2D, 1364 and 2048 in 3D: items of a
+    quarter tile below 2048 tiles, of a tile from there on."""
+    rng = np.random.default_rng(17)
+    f = np.round(rng.standard_normal(shape) * 8).astype(np.float32)
+    g = (f + rng.integers(-1, 2, shape)).astype(np.float32)
+    got = msz.count_false(torch.from_numpy(f).cuda(), torch.from_numpy(g).cuda())
+    want = oracle.count_false(f, g)
+    for key in want:
+        assert int(got[key]) == int(want[key]), key
