@@ -502,7 +502,15 @@ int run_engine(std::vector<EngField>& hf, std::vector<EngStats>& st, bool timing
     for (int j = 0; j < nf; ++j) order[j] = j;
     std::stable_partition(order.begin(), order.end(), [&](int j) { return hf[j].gr.ndim == 2; });
     std::vector<EngField> tab(nf);
-    for (int p = 0; p < nf; ++p) tab[p] = hf[order[p]];
+    for (int p = 0; p < nf; ++p) {
+        tab[p] = hf[order[p]];
+        // The schedule follows the kernel that runs it, also in a batch of
+        // one: the one-field kernel reads f's labels, resolved once before the
+        // loop (its R rounds resolve many of them); a batch's troublemaker
+        // passes follow f's chains where they need f's labels, cheaper than
+        // one more full step for every field.
+        tab[p].single = single ? 1 : 0;
+    }
     int n2 = 0;
     std::vector<EngState> hs(2 * nf);
     std::vector<int64_t> u2, u3;  // a batch: each chain's fields' units (items x weight) of the first step
@@ -866,6 +874,7 @@ int run_noalloc(EngField F, char* base, int64_t max_steps, EngStats& out, hipStr
     const bool small = small_field(F);
     const int grid = small ? std::min(resident, kSmallGrid) : resident;
     const int launch_steps = small ? kSmallSteps : kGraphSteps;
+    F.single = 1;  // for the one-field kernel
     F.cnt = cp;
     {
         void* a[] = {&F, &fp, &sp, &tp, &cp, &lp, &wp};
@@ -958,7 +967,6 @@ int msz_fix(const float* f, const float* fhat, msz_dims d, float xi, float* edit
     F.preempt = (o.flags & MSZ_FLAG_PREEMPTIVE) != 0;
     F.merged = (o.flags & MSZ_FLAG_MERGED_C) != 0 || F.preempt;
     F.count_init = (o.flags & MSZ_FLAG_COUNT_INIT) != 0;
-    F.single = 1;
     F.xi = xi;
     F.cap = o.max_rounds > 0 ? o.max_rounds : (int64_t(1) << 30);
     F.f = f;
@@ -1011,7 +1019,6 @@ int msz_fix_noalloc(const float* f, const float* fhat, msz_dims d, float xi, flo
     F.preempt = (o.flags & MSZ_FLAG_PREEMPTIVE) != 0;
     F.merged = (o.flags & MSZ_FLAG_MERGED_C) != 0 || F.preempt;
     F.count_init = (o.flags & MSZ_FLAG_COUNT_INIT) != 0;
-    F.single = 1;
     F.xi = xi;
     F.cap = o.max_rounds > 0 ? o.max_rounds : (int64_t(1) << 30);
     F.f = f;
@@ -1090,11 +1097,6 @@ int msz_fix_batch(const msz_job* jobs, int32_t n_jobs, const msz_options* opt, v
         F.preempt = (o.flags & MSZ_FLAG_PREEMPTIVE) != 0;
         F.merged = (o.flags & MSZ_FLAG_MERGED_C) != 0 || F.preempt;
         F.count_init = (o.flags & MSZ_FLAG_COUNT_INIT) != 0;
-        // a batch's troublemaker passes follow f's chains where they need f's
-        // labels: cheaper than one more full step for every field (a field
-        // corrected alone, whose R rounds resolve many labels, resolves them
-        // once instead)
-        F.single = 0;
         F.xi = J.xi;
         F.cap = cap;
         F.f = J.f;

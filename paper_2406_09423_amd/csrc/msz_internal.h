@@ -227,8 +227,8 @@ struct EngField {
     int preempt;     // 1: shared targets edited without claims (preemptive mode; implies merged)
     int count_init;  // 1: label the start field once and count its mislabelled vertices
     int sum;         // 1: keep chunk summaries of the flag arrays and skip empty chunks (large single fields)
-    int single;      // 1: corrected alone: f's labels are resolved once before the loop (else the troublemaker
-                     // passes follow f's chains)
+    int single;      // 1: run by the one-field kernel: f's labels are resolved once before the loop (else the
+                     // troublemaker passes follow f's chains); set where the kernel is chosen
     float xi;
     long long cap;
     const float *f, *fhat, *warm;
