@@ -469,9 +469,8 @@ __global__ void __launch_bounds__(1024) k_reduce_dw(const float* __restrict__ pa
 // and targets nothing).  A thread reads its 3 x 3 neighbourhood and carries
 // what the planes above and below need of it in registers: the box sums of
 // planes z - 1 and z, and the target bits it hands to each side.  Quotients
-// by the box count and by xi use a reciprocal, one residual and one
-// correction (correctly rounded, as the division is: the reciprocals are
-// correctly rounded and no divisor's significand is all ones).
+// by the box count and by xi are correctly rounded, as the division is (the
+// reciprocals are correctly rounded and no divisor's significand is all ones).
 // Moves 42 bytes per vertex: 213 us for 256^3 (3.3 TB/s), where one thread
 // per column, loading its 36 values per vertex itself, took 788.
 constexpr int kFeatX = 32, kFeatY = 8, kFeatZ = 16, kFeatHX = kFeatX + 2, kFeatHY = kFeatY + 2;
@@ -496,9 +495,14 @@ __device__ __forceinline__ void add_target(uint2& t, const uint2& w, int s) {
     t.y |= (w.y >> (s ^ 1)) & 0x00010001u;
 }
 
-__device__ __forceinline__ double quotient(double x, double d, double r) {  // x / d, r = 1 / d
+// x / d for a positive finite d, r = 1 / d: a reciprocal, one residual and one
+// correction (Markstein's method), and the product itself where that is a zero
+// or an infinity (the residual would lose the sign of the one and make the
+// other not a number; no other product is either, x being a sum of a few
+// float32 values).
+__device__ __forceinline__ double quotient(double x, double d, double r) {
     const double q = __dmul_rn(x, r);
-    return __fma_rn(__fma_rn(-q, d, x), r, q);
+    return q + q == q ? q : __fma_rn(__fma_rn(-q, d, x), r, q);
 }
 
 __global__ void __launch_bounds__(256) k_features(const float* __restrict__ f, const float* __restrict__ fhat,
