@@ -76,10 +76,11 @@ hipMemPool_t scratch_pool() {
         props.location.type = hipMemLocationTypeDevice;
         props.location.id = dev;
         hipMemPool_t p = nullptr;
-        if (hipMemPoolCreate(&p, &props) != hipSuccess) return nullptr;
         uint64_t keep = kPoolKeep;
-        if (hipMemPoolSetAttribute(p, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
-            (void)hipMemPoolDestroy(p);
+        if (hipMemPoolCreate(&p, &props) != hipSuccess ||
+            hipMemPoolSetAttribute(p, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
+            if (p) (void)hipMemPoolDestroy(p);
+            (void)hipGetLastError();  // the call goes on with the default pool
             return nullptr;
         }
         pools[dev] = p;
@@ -109,6 +110,7 @@ int Scratch::get(void* user, size_t user_bytes, size_t need, hipStream_t stream)
         (void)hipMemPoolTrimTo(pool, 0);
     }
     if (hipMallocAsync(&p, need, stream) != hipSuccess) {
+        (void)hipGetLastError();  // said by the result; left, it would pass for an error of the next launch
         p = nullptr;
         return MSZ_ENOMEM;
     }

@@ -1,0 +1,100 @@
+// A stand-in for the HIP runtime on a machine without a GPU: device memory is
+// host memory (zeros), kernels do nothing, and every request is written down.
+// Loaded ahead of libmsz.so, its functions take the place of the runtime's, so
+// that the host side of the library can be tested on its own: where scratch
+// comes from, what happens when memory is short, what grids are launched.
+#include <hip/hip_runtime_api.h>
+#include <sys/mman.h>
+
+#include <cstring>
+#include <map>
+#include <string>
+
+namespace {
+std::map<void*, size_t> live;
+std::string text;
+size_t largest = ~size_t(0);  // a larger request of device memory fails
+int current = 0, of_stream = 0;
+hipError_t last = hipSuccess;
+
+hipError_t result(hipError_t e) {  // the last error stays until it is asked for
+    if (e != hipSuccess) last = e;
+    return e;
+}
+hipError_t take(void** p, size_t bytes, const std::string& from) {
+    const bool fails = from != "host" && bytes > largest;
+    text += from + " " + std::to_string(bytes) + (fails ? " fails\n" : "\n");
+    if (fails) return result(hipErrorOutOfMemory);
+    void* q = mmap(nullptr, bytes, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+    if (q == MAP_FAILED) return result(hipErrorOutOfMemory);
+    live[q] = bytes;
+    *p = q;
+    return hipSuccess;
+}
+dim3 pushed_grid, pushed_block;
+size_t pushed_shared;
+hipStream_t pushed_stream;
+}  // namespace
+
+extern "C" {
+
+void fake_set(size_t largest_request, int current_device, int device_of_streams) {
+    largest = largest_request;
+    current = current_device;
+    of_stream = device_of_streams;
+    text.clear();
+}
+const char* fake_log() { return text.c_str(); }
+size_t fake_live() { return live.size(); }
+
+hipError_t hipGetDevice(int* dev) { return *dev = current, hipSuccess; }
+hipError_t hipStreamGetDevice(hipStream_t, hipDevice_t* dev) { return *dev = of_stream, hipSuccess; }
+hipError_t hipGetLastError() {
+    const hipError_t e = last;
+    last = hipSuccess;
+    return e;
+}
+hipError_t hipMemPoolCreate(hipMemPool_t* pool, const hipMemPoolProps* props) {
+    *pool = reinterpret_cast<hipMemPool_t>(static_cast<uintptr_t>(1 + props->location.id));
+    return hipSuccess;
+}
+hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void*) { return hipSuccess; }
+hipError_t hipMemPoolDestroy(hipMemPool_t) { return hipSuccess; }
+hipError_t hipMemPoolTrimTo(hipMemPool_t, size_t) { return hipSuccess; }
+hipError_t hipMallocFromPoolAsync(void** p, size_t bytes, hipMemPool_t pool, hipStream_t) {
+    return take(p, bytes, "pool " + std::to_string(reinterpret_cast<uintptr_t>(pool) - 1));
+}
+hipError_t hipMallocAsync(void** p, size_t bytes, hipStream_t) { return take(p, bytes, "default"); }
+hipError_t hipHostMalloc(void** p, size_t bytes, unsigned) { return take(p, bytes, "host"); }
+hipError_t hipFreeAsync(void* p, hipStream_t) {
+    const auto it = live.find(p);
+    if (it == live.end()) return result(hipErrorInvalidValue);
+    munmap(p, it->second);
+    live.erase(it);
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKind, hipStream_t) {
+    std::memcpy(dst, src, bytes);
+    return hipSuccess;
+}
+hipError_t hipMemsetAsync(void* dst, int v, size_t bytes, hipStream_t) {
+    std::memset(dst, v, bytes);
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t shared, hipStream_t s) {
+    pushed_grid = grid, pushed_block = block, pushed_shared = shared, pushed_stream = s;
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, hipStream_t* s) {
+    *grid = pushed_grid, *block = pushed_block, *shared = pushed_shared, *s = pushed_stream;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void*, dim3 grid, dim3 block, void**, size_t, hipStream_t) {
+    text += "launch " + std::to_string(grid.x) + " " + std::to_string(block.x) + "\n";
+    // (the runtime takes fewer than 2^32 threads)
+    return static_cast<unsigned long long>(grid.x) * block.x >= 1ull << 32 ? result(hipErrorInvalidConfiguration)
+                                                                           : hipSuccess;
+}
+
+}  // extern "C"

@@ -1,0 +1,71 @@
+"""The host side of the library on a stand-in for the HIP runtime
+(fake_hip.cpp), without a GPU: where the scratch of a call comes from, and what
+a call does when memory is short."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PREAMBLE = """
+import ctypes, sys
+sys.path.insert(0, sys.argv[2])
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)  # ahead of the library's own runtime
+fake.fake_set.argtypes = [ctypes.c_size_t, ctypes.c_int, ctypes.c_int]
+fake.fake_log.restype = ctypes.c_char_p
+fake.fake_live.restype = ctypes.c_size_t
+import paper_2406_09423_amd as msz
+L = msz.lib()
+EVERY = 2 ** 63
+STREAM = 4096  # the handle of a stream; never looked into
+def log():
+    return fake.fake_log().decode().split("\\n")[:-1]
+def array(nbytes):
+    a = (ctypes.c_char * (nbytes + 16))()
+    keep.append(a)
+    return (ctypes.addressof(a) + 15) & ~15
+keep = []
+n = 300 * 200
+d = msz.dims_of((200, 300))
+f, M, m = array(4 * n), array(4 * n), array(4 * n)
+counts = msz.FalseCounts()
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-o", out, os.path.join(HERE, "fake_hip.cpp")], check=True)
+    return out
+
+
+def run(fake, code):
+    r = subprocess.run([sys.executable, "-c", PREAMBLE + code, fake, ROOT], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_labels_with_little_memory(fake):
+    """The scratch of the first route (5 bytes per vertex) does not fit, that of
+    the second (one byte) does: the labels are computed."""
+    run(fake, """
+fake.fake_set(3 * n, 0, 0)
+assert L.msz_labels(f, d, M, m, None) == msz.OK
+asked = [x for x in log() if x.startswith(("pool", "default"))]
+assert [x.endswith("fails") for x in asked] == [True, True, False], asked
+assert fake.fake_live() == 1  # the pinned counters
+""")
+
+
+def test_calls_after_one_without_memory(fake):
+    """A call that found no memory says so, and the next one is not affected."""
+    run(fake, """
+for call in (lambda: L.msz_count_false(f, f, d, ctypes.byref(counts), None), lambda: L.msz_labels(f, d, M, m, None)):
+    fake.fake_set(100, 0, 0)
+    assert call() == msz.ENOMEM
+    fake.fake_set(EVERY, 0, 0)
+    assert call() == msz.OK
+""")
