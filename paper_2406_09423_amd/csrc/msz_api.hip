@@ -63,11 +63,21 @@ bool make_grid(const msz_dims& d, Grid& gr) {
 constexpr uint64_t kPoolKeep = 256u << 20;
 constexpr int kMaxDevices = 64;
 
-hipMemPool_t scratch_pool() {
+// The device of a stream (as an allocation on the stream takes it); -1 if
+// there is none.  The null stream and the two other handles that name no
+// stream object (1 and 2) stand for streams of the current device.
+int device_of(hipStream_t stream) {
+    int dev = 0;
+    const bool object = reinterpret_cast<uintptr_t>(stream) > 2;
+    if ((object ? hipStreamGetDevice(stream, &dev) : hipGetDevice(&dev)) == hipSuccess) return dev;
+    (void)hipGetLastError();
+    return -1;
+}
+
+hipMemPool_t scratch_pool(int dev) {
     static std::mutex mu;
     static hipMemPool_t pools[kMaxDevices] = {};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
+    if (dev < 0 || dev >= kMaxDevices) return nullptr;
     std::lock_guard<std::mutex> lock(mu);
     if (!pools[dev]) {
         hipMemPoolProps props{};
@@ -100,7 +110,7 @@ int Scratch::get(void* user, size_t user_bytes, size_t need, hipStream_t stream)
         return MSZ_OK;
     }
     need = std::max<size_t>(need, 256);
-    hipMemPool_t pool = scratch_pool();
+    hipMemPool_t pool = scratch_pool(device_of(stream));
     if (pool) {
         if (hipMallocFromPoolAsync(&p, need, pool, stream) == hipSuccess) {
             owned = true;

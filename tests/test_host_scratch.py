@@ -69,3 +69,23 @@ for call in (lambda: L.msz_count_false(f, f, d, ctypes.byref(counts), None), lam
     fake.fake_set(EVERY, 0, 0)
     assert call() == msz.OK
 """)
+
+
+def test_scratch_lies_on_the_device_of_the_stream(fake):
+    """A call on a stream of another device than the current one takes its
+    scratch there; on the null stream, from the current device."""
+    run(fake, """
+size = ctypes.c_size_t()
+edits, blob = array(4 * n), array(L.msz_edits_bound(n))
+feat, p = array(32 * n), array(4 * n)
+params = array(4 * msz.NET_PARAMS)
+for stream, device in ((STREAM, 3), (None, 1)):
+    for call in (lambda: L.msz_labels(f, d, M, m, stream), lambda: L.msz_count_false(f, f, d, ctypes.byref(counts), stream),
+                 lambda: L.msz_encode_edits(edits, n, blob, L.msz_edits_bound(n), ctypes.byref(size), None, stream),
+                 lambda: L.msz_decode_edits(blob, size.value, edits, n, stream),
+                 lambda: L.msz_net_forward(params, feat, d, p, None, None, None, 0, stream)):
+        fake.fake_set(EVERY, 1, 3)
+        call()
+        asked = [x for x in log() if x.startswith(("pool", "default"))]
+        assert asked and all(x.startswith("pool %d " % device) for x in asked), asked
+""")
