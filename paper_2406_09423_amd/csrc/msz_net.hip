@@ -15,6 +15,7 @@
 // 16-byte read of 8 consecutive channels of one shifted vertex from the LDS
 // input tile; a lane's result is 4 consecutive output channels of one vertex,
 // written as one 8-byte store.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -463,7 +464,7 @@ __global__ void __launch_bounds__(1024) k_reduce_dw(const float* __restrict__ pa
 // Channels 8..11 gather over the neighbour slots: neighbour j = i + off[s]
 // points back at i through the opposite slot s ^ 1.
 //
-// A block owns 32 x 8 columns and walks kFeatZ planes of z.  Each plane, with
+// A block owns FX x FY columns and walks kFeatZ planes of z.  Each plane, with
 // a one-vertex halo, is staged in LDS once: (f, fhat) and the target masks of
 // every vertex, both zero outside the grid (a zero adds nothing to a box sum
 // and targets nothing).  A thread reads its 3 x 3 neighbourhood and carries
@@ -473,7 +474,12 @@ __global__ void __launch_bounds__(1024) k_reduce_dw(const float* __restrict__ pa
 // reciprocals are correctly rounded and no divisor's significand is all ones).
 // Moves 42 bytes per vertex: 213 us for 256^3 (3.3 TB/s), where one thread
 // per column, loading its 36 values per vertex itself, took 788.
-constexpr int kFeatX = 32, kFeatY = 8, kFeatZ = 16, kFeatHX = kFeatX + 2, kFeatHY = kFeatY + 2;
+constexpr int kFeatZ = 16;
+template <int FX, int FY>
+struct FeatTile {
+    static constexpr int X = FX, Y = FY, HX = FX + 2, HY = FY + 2;
+    static_assert(FX * FY == 256, "a thread per column");
+};
 
 // Target masks of vertex j from its directions in f and fhat: bit d of a is
 // set when j's descents differ and f's is slot d, bit d of b when its ascents
@@ -505,17 +511,20 @@ __device__ __forceinline__ double quotient(double x, double d, double r) {
     return q + q == q ? q : __fma_rn(__fma_rn(-q, d, x), r, q);
 }
 
+template <int FX, int FY>
 __global__ void __launch_bounds__(256) k_features(const float* __restrict__ f, const float* __restrict__ fhat,
                                                   const uint8_t* __restrict__ dirs_f,
-                                                  const uint8_t* __restrict__ dirs_h, Grid gr, float xi, float xi_ch,
-                                                  uint16_t* __restrict__ feat) {
-    constexpr int NP = kFeatHX * kFeatHY, PER = (NP + 255) / 256;
+                                                  const uint8_t* __restrict__ dirs_h, Grid gr, int ntiles, float xi,
+                                                  float xi_ch, uint16_t* __restrict__ feat) {
+    using T = FeatTile<FX, FY>;
+    constexpr int NP = T::HX * T::HY, PER = (NP + 255) / 256;
     __shared__ float2 sv[2][NP];
     __shared__ uint2 st[2][NP];
-    const int tx_n = (gr.nx + kFeatX - 1) / kFeatX, ty_n = (gr.ny + kFeatY - 1) / kFeatY;
-    const int t = blockIdx.x;
-    const int X0 = (t % tx_n) * kFeatX, Y0 = ((t / tx_n) % ty_n) * kFeatY, Z0 = (t / (tx_n * ty_n)) * kFeatZ;
-    const int lx = threadIdx.x % kFeatX, ly = threadIdx.x / kFeatX;
+    const int tx_n = (gr.nx + T::X - 1) / T::X, ty_n = (gr.ny + T::Y - 1) / T::Y;
+    const int t = blockIdx.y * gridDim.x + blockIdx.x;
+    if (t >= ntiles) return;
+    const int X0 = (t % tx_n) * T::X, Y0 = ((t / tx_n) % ty_n) * T::Y, Z0 = (t / (tx_n * ty_n)) * kFeatZ;
+    const int lx = threadIdx.x % T::X, ly = threadIdx.x / T::X;
     const int x = X0 + lx, y = Y0 + ly;
     const bool in_xy = x < gr.nx && y < gr.ny;
     const int z_end = min(Z0 + kFeatZ, gr.nz);  // planes [Z0, z_end) are written
@@ -523,15 +532,21 @@ __global__ void __launch_bounds__(256) k_features(const float* __restrict__ f, c
     const double xid = xi, rxi = 1.0 / xid;
     const unsigned one = bf16_bits(1.0f);
 
-    // plane z into registers (unconditional loads; zeros outside the grid)
+    // plane z into registers (unconditional loads; zeros outside the grid,
+    // two planes of the three of a 2D field)
     float2 rv[PER];
     uint2 rt[PER];
     auto load = [&](int z) {
+        if (z < 0 || z >= gr.nz) {
+#pragma unroll
+            for (int k = 0; k < PER; ++k) rv[k] = make_float2(0.0f, 0.0f), rt[k] = make_uint2(0u, 0u);
+            return;
+        }
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             const int e = min(static_cast<int>(threadIdx.x) + 256 * k, NP - 1);
-            const int xx = X0 + e % kFeatHX - 1, yy = Y0 + e / kFeatHX - 1;
-            const bool ok = xx >= 0 && xx < gr.nx && yy >= 0 && yy < gr.ny && z >= 0 && z < gr.nz;
+            const int xx = X0 + e % T::HX - 1, yy = Y0 + e / T::HX - 1;
+            const bool ok = xx >= 0 && xx < gr.nx && yy >= 0 && yy < gr.ny;
             const long j = ok ? xx + static_cast<long>(gr.nx) * yy + static_cast<long>(gr.nxy) * z : 0;
             const float fj = f[j], hj = fhat[j];
             const TargetMask m = target_mask(dirs_f[j], dirs_h[j]);
@@ -562,19 +577,19 @@ __global__ void __launch_bounds__(256) k_features(const float* __restrict__ f, c
     for (int z = Z0 - 1; z <= z_end; ++z) {  // plane z is in LDS; vertex z - 1 is written
         const int slot = (z - Z0 + 1) & 1;
         if (z < z_end) load(z + 1);
-        const float2* pv = sv[slot] + (lx + 1) + kFeatHX * (ly + 1);
-        const uint2* pt = st[slot] + (lx + 1) + kFeatHX * (ly + 1);
+        const float2* pv = sv[slot] + (lx + 1) + T::HX * (ly + 1);
+        const uint2* pt = st[slot] + (lx + 1) + T::HX * (ly + 1);
         double sf = 0.0, sh = 0.0;
 #pragma unroll
         for (int dy = -1; dy <= 1; ++dy)
 #pragma unroll
             for (int dx = -1; dx <= 1; ++dx) {
-                const float2 v = pv[dx + kFeatHX * dy];
+                const float2 v = pv[dx + T::HX * dy];
                 sf += v.x;
                 sh += v.y;
             }
-        const uint2 c = pt[0], px = pt[1], mx = pt[-1], py = pt[kFeatHX], my = pt[-kFeatHX], pxy = pt[kFeatHX + 1],
-                    mxy = pt[-kFeatHX - 1];
+        const uint2 c = pt[0], px = pt[1], mx = pt[-1], py = pt[T::HX], my = pt[-T::HX], pxy = pt[T::HX + 1],
+                    mxy = pt[-T::HX - 1];
         uint2 t_up = make_uint2(0u, 0u), t_in = t_up, t_next = t_up;
         add_target(t_up, c, 6);  // this plane's vertices seen from the plane below it
         add_target(t_up, px, 8);
@@ -734,6 +749,33 @@ static void launch_conv_t(const uint16_t* in, const Grid& gr, const WeightView& 
     }
 }
 
+template <int FX, int FY>
+static void launch_features_t(const float* f, const float* fhat, const uint8_t* df, const uint8_t* dh, const Grid& gr,
+                              float xi, float xi_ch, uint16_t* feat, hipStream_t s) {
+    using T = FeatTile<FX, FY>;
+    // a tile per block (at most one per vertex), in rows of 2^20 blocks: a
+    // grid's row has fewer than 2^32 threads
+    const int nt = ((gr.nx + T::X - 1) / T::X) * ((gr.ny + T::Y - 1) / T::Y) * ((gr.nz + kFeatZ - 1) / kFeatZ);
+    const int row = std::min(nt, 1 << 20);
+    hipLaunchKernelGGL((k_features<FX, FY>), dim3(row, (nt + row - 1) / row), dim3(256), 0, s, f, fhat, df, dh, gr, nt,
+                       xi, xi_ch, feat);
+}
+
+// Tiles of 32 x 8 columns, but of another shape in fields of so few columns or
+// rows that most of such a tile would lie outside them.  Whole calls with
+// 32 x 8 tiles and with these: nx = 1 (1000003 rows) 739 and 230 us; nx = 3
+// (300001 rows) 282 and 137; nx = 16 (100 planes of 3000 rows) 308 and 297,
+// where nx = 20 takes 292 and 299; ny = 1 (nx = 1000003) 231 and 125; ny = 4
+// (nx = 300001) 113 and 95, where ny = 5 takes the same.
+static void launch_features(const float* f, const float* fhat, const uint8_t* df, const uint8_t* dh, const Grid& gr,
+                            float xi, float xi_ch, uint16_t* feat, hipStream_t s) {
+    if (gr.nx == 1) launch_features_t<1, 256>(f, fhat, df, dh, gr, xi, xi_ch, feat, s);
+    else if (gr.ny == 1) launch_features_t<256, 1>(f, fhat, df, dh, gr, xi, xi_ch, feat, s);
+    else if (gr.nx <= 16) launch_features_t<4, 64>(f, fhat, df, dh, gr, xi, xi_ch, feat, s);
+    else if (gr.ny <= 4) launch_features_t<128, 2>(f, fhat, df, dh, gr, xi, xi_ch, feat, s);
+    else launch_features_t<32, 8>(f, fhat, df, dh, gr, xi, xi_ch, feat, s);
+}
+
 // Blocks (and partial sums) of a weight gradient: tiles of 16 x 8 x 4 vertices
 // (2D: 16 x 16), so that three blocks' tiles with their halos share a
 // compute unit's LDS and one block stages while another computes.
@@ -862,8 +904,7 @@ int features_impl(const float* f, const float* fhat, const Grid& gr, float xi, u
     const float xi_ch = static_cast<float>(std::log10(static_cast<double>(xi) / range) / 4.0 + 1.0);
     launch_dirs(f, gr, df, nullptr, s);
     launch_dirs(fhat, gr, dh, nullptr, s);
-    const int nt = ((gr.nx + kFeatX - 1) / kFeatX) * ((gr.ny + kFeatY - 1) / kFeatY) * ((gr.nz + kFeatZ - 1) / kFeatZ);
-    hipLaunchKernelGGL(k_features, dim3(nt), dim3(256), 0, s, f, fhat, df, dh, gr, xi, xi_ch, feat);
+    launch_features(f, fhat, df, dh, gr, xi, xi_ch, feat, s);
     return hipGetLastError() == hipSuccess ? MSZ_OK : MSZ_EDEVICE;
 }
 

@@ -1,6 +1,6 @@
 """The host side of the library on a stand-in for the HIP runtime
-(fake_hip.cpp), without a GPU: where the scratch of a call comes from, and what
-a call does when memory is short."""
+(fake_hip.cpp), without a GPU: where the scratch of a call comes from, what a
+call does when memory is short, and that its grids can be launched."""
 import os
 import subprocess
 import sys
@@ -88,4 +88,14 @@ for stream, device in ((STREAM, 3), (None, 1)):
         call()
         asked = [x for x in log() if x.startswith(("pool", "default"))]
         assert asked and all(x.startswith("pool %d " % device) for x in asked), asked
+""")
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(1, 1, 2 ** 28), (1, 2 ** 27, 1), (2 ** 27, 1, 1), (4096, 4096, 8)])
+def test_feature_grids_can_be_launched(fake, nx, ny, nz):
+    """Fewer than 2^32 threads, also where a field is one vertex wide."""
+    run(fake, f"""
+fake.fake_pattern(1)  # a value range of 1
+rc = L.msz_net_features(f, f, msz.Dims(3, {nx}, {ny}, {nz}), ctypes.c_float(0.1), array(16), None, 0, None)
+assert rc == msz.OK, (rc, log())
 """)
