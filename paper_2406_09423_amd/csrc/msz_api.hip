@@ -152,32 +152,32 @@ Layout layout_for(const Grid& gr) {
     const int64_t n = gr.n;
     Layout l{};
     size_t o = 0;
-    auto take = [&](size_t bytes) {
+    auto take = [&](size_t bytes, size_t align) {
         const size_t r = o;
-        o += align256(bytes);
+        o = (o + bytes + align - 1) / align * align;
         return r;
     };
-    l.L = take(n * 4);
-    l.g = take(n * 4);
-    l.dirs_f = take(n);
-    l.dirs_g = take(n);
-    l.marks = take((n + 15) & ~int64_t(15));
-    l.cases = take((n + 15) & ~int64_t(15));
-    l.dirty = take((n + 15) & ~int64_t(15));
-    l.chunk_dirty = take(((n + kEngChunk - 1) / kEngChunk) * 4);
-    l.chunk_cnt = take(((n + kEngChunk - 1) / kEngChunk) * 8);
-    l.chunk_unk = take(((n + kEngChunk - 1) / kEngChunk) * 4);
-    l.sparse = take(sizeof(SparseBuf));
-    l.tile_dirty = take(label_tile_count(gr));
-    l.Mf = take(n * 4);
-    l.mf = take(n * 4);
-    l.qu = take(n * 2);
-    l.qd = take(n * 2);
+    const size_t chunks = (n + kEngChunk - 1) / kEngChunk, flags = (n + 15) & ~int64_t(15);
+    l.L = take(n * 4, 256);
+    l.g = take(n * 4, 256);
+    l.dirs_f = take(n, 256);
+    l.dirs_g = take(n, 256);
+    l.marks = take(flags, 256);
+    l.cases = take(flags, 256);
+    l.dirty = take(flags, 256);
+    l.Mf = take(n * 4, 256);
+    l.mf = take(n * 4, 256);
+    l.qu = take(n * 2, 16);
+    l.qd = take(n * 2, 16);
+    l.chunk_dirty = take(chunks * 4, 16);
+    l.chunk_cnt = take(chunks * 8, 16);
+    l.chunk_unk = take(chunks * 4, 16);
+    l.tile_dirty = take(label_tile_count(gr), 16);
+    l.sparse = take(sizeof(SparseBuf), 16);
     // The size asked of callers, and with it the limit of msz_fix_noalloc, is
-    // that of four int32 pointer arrays (29 bytes per vertex); fields of a few
-    // hundred vertices need a little more.
-    const size_t chunks = (n + kEngChunk - 1) / kEngChunk, flags = align256((n + 15) & ~int64_t(15));
-    l.total = std::max(o, 6 * align256(n * 4) + 2 * align256(n) + 3 * flags + 2 * align256(chunks * 4) +
+    // that of four int32 pointer arrays (29 bytes per vertex), each array on a
+    // 256-byte boundary; the arrays above fit it, the last ones packed closer.
+    l.total = std::max(o, 6 * align256(n * 4) + 2 * align256(n) + 3 * align256(flags) + 2 * align256(chunks * 4) +
                               align256(chunks * 8) + align256(label_tile_count(gr)));
     return l;
 }

@@ -776,18 +776,16 @@ static void launch_features(const float* f, const float* fhat, const uint8_t* df
     else launch_features_t<32, 8>(f, fhat, df, dh, gr, xi, xi_ch, feat, s);
 }
 
-// Blocks (and partial sums) of a weight gradient: tiles of 16 x 8 x 4 vertices
-// (2D: 16 x 16), so that three blocks' tiles with their halos share a
-// compute unit's LDS and one block stages while another computes.
-static int dw_blocks(const Grid& gr) {
-    const int nt = gr.nz == 1 ? tiles_of(gr, 16, 1) : tiles_of(gr, 8, 4);
-    return nt < kDwBlocks ? nt : kDwBlocks;
-}
+// Tiles of a weight gradient: 16 x 8 x 4 vertices (2D: 16 x 16), so that three
+// blocks' tiles with their halos share a compute unit's LDS and one block
+// stages while another computes.
+static int dw_tiles(const Grid& gr) { return gr.nz == 1 ? tiles_of(gr, 16, 1) : tiles_of(gr, 8, 4); }
 
-// The gradient of one layer's weights (n_out output channels stored) and bias.
-static void launch_dw(const uint16_t* in, const uint16_t* dz, const Grid& gr, float* part, int n_out, float* gW,
-                      float* gb, hipStream_t s) {
-    const int nb = dw_blocks(gr);
+// The gradient of one layer's weights (n_out output channels stored) and bias,
+// by at most max_blocks blocks (and partial sums).
+static void launch_dw(const uint16_t* in, const uint16_t* dz, const Grid& gr, float* part, int max_blocks, int n_out,
+                      float* gW, float* gb, hipStream_t s) {
+    const int nb = std::min(dw_tiles(gr), std::min(kDwBlocks, max_blocks));
     if (gr.nz == 1) hipLaunchKernelGGL((k_conv_dw<16, 1>), dim3(nb), dim3(256), 0, s, in, dz, gr, part);
     else hipLaunchKernelGGL((k_conv_dw<8, 4>), dim3(nb), dim3(256), 0, s, in, dz, gr, part);
     hipLaunchKernelGGL(k_reduce_dw, dim3((kDwSums + 63) / 64), dim3(1024), 0, s, part, nb, n_out, gW, gb);
@@ -805,7 +803,8 @@ bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // Net workspace of one field.
 struct NetLayout {
-    size_t dirs_f, dirs_h, feat, a1, a2, p, dz_a, dz_b, part, minmax, g0, total;
+    size_t dirs_f, dirs_h, a1, a2, p, dz_a, dz_b, feat, minmax, g0, total;
+    int max_parts;  // partial sums of a weight gradient, from feat on
 };
 
 NetLayout net_layout(const Grid& gr) {
@@ -819,13 +818,18 @@ NetLayout net_layout(const Grid& gr) {
     };
     l.dirs_f = take(n + 16);
     l.dirs_h = take(n + 16);
-    l.feat = take(n * 32);
     l.a1 = take(n * 32);
     l.a2 = take(n * 32);
     l.p = take(n * 4);
     l.dz_a = take(n * 32);
     l.dz_b = take(n * 32);
-    l.part = take(static_cast<size_t>(dw_blocks(gr)) * kDwSums * 4);
+    // The partial sums of a gradient, which is given its features, lie over
+    // the features and a part of its own: a partial for each tile of the
+    // convolutions, half as many as the weight gradient has tiles.
+    l.feat = take(n * 32);
+    (void)take(static_cast<size_t>(std::min(kDwBlocks, gr.nz == 1 ? tiles_of(gr, 32, 1) : tiles_of(gr, 8, 8))) *
+               kDwSums * 4);
+    l.max_parts = static_cast<int>(std::min<size_t>(kDwBlocks, (o - l.feat) / (kDwSums * 4)));
     l.minmax = take(kConvBlocks * 2 * 4);
     l.g0 = take(n * 4);
     l.total = o;
@@ -983,19 +987,19 @@ int msz_net_gradients(const float* params, const uint16_t* feat, const float* ta
     float* p = reinterpret_cast<float*>(w + l.p);
     uint16_t* dza = reinterpret_cast<uint16_t*>(w + l.dz_a);
     uint16_t* dzb = reinterpret_cast<uint16_t*>(w + l.dz_b);
-    float* part = reinterpret_cast<float*>(w + l.part);
+    float* part = reinterpret_cast<float*>(w + l.feat);
     float* lp = reinterpret_cast<float*>(w + l.minmax);
     net_forward(params, feat, gr, a1, a2, p, s);
     const int nb = blocks_n(gr.n);
     hipLaunchKernelGGL(k_mse, dim3(nb), dim3(256), 0, s, p, target, gr.n, edit_weight, dza, lp);
     // layer 2
-    launch_dw(a2, dza, gr, part, 1, grad_out + kOffW2, grad_out + kOffB2, s);
+    launch_dw(a2, dza, gr, part, l.max_parts, 1, grad_out + kOffW2, grad_out + kOffB2, s);
     launch_conv_t<kConvBackData>(dza, gr, layer_back_view(params, 2), a2, dzb, s);
     // layer 1
-    launch_dw(a1, dzb, gr, part, 16, grad_out + kOffW1, grad_out + kOffB1, s);
+    launch_dw(a1, dzb, gr, part, l.max_parts, 16, grad_out + kOffW1, grad_out + kOffB1, s);
     launch_conv_t<kConvBackData>(dzb, gr, layer_back_view(params, 1), a1, dza, s);
     // layer 0
-    launch_dw(feat, dza, gr, part, 16, grad_out + kOffW0, grad_out + kOffB0, s);
+    launch_dw(feat, dza, gr, part, l.max_parts, 16, grad_out + kOffW0, grad_out + kOffB0, s);
     if (hipGetLastError() != hipSuccess) return MSZ_EDEVICE;
     std::vector<float> host(nb);
     if (hipMemcpyAsync(host.data(), lp, nb * sizeof(float), hipMemcpyDeviceToHost, s) != hipSuccess ||
