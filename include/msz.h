@@ -29,7 +29,7 @@
  *    device clears a done word in pinned host memory.
  *  - Memory: when no workspace is given, the library takes scratch for the
  *    call, ordered on the stream, from a memory pool of its own, which keeps
- *    at most 256 MB per device between calls.  It also keeps one control block
+ *    at most 512 MB per device between calls.  It also keeps one control block
  *    (about 9 MB: field table, step states, round counters, statistics) with
  *    up to three cached graphs, and 512 bytes of pinned, device-mapped host
  *    memory (the done word and the final statistics of one-field runs) per

@@ -60,7 +60,7 @@ bool make_grid(const msz_dims& d, Grid& gr) {
 // gives back what is above at the next wait, all of it when an allocation
 // fails; the runtime orders its memory by stream, so calls of several threads
 // and streams may share it.
-constexpr uint64_t kPoolKeep = 256u << 20;
+constexpr uint64_t kPoolKeep = 512u << 20;
 constexpr int kMaxDevices = 64;
 
 // The device of a stream (as an allocation on the stream takes it); -1 if
@@ -1140,34 +1140,19 @@ int msz_labels(const float* field, msz_dims d, int32_t* max_label, int32_t* min_
     unsigned* hc = host_counters();
     if (!hc) return MSZ_EDEVICE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const size_t c0 = align256(kCntBlockWords * sizeof(unsigned)), nb = align256(gr.n), nq = align256(size_t(gr.n) * 2);
-    // Straight from the tile codes; where memory for these is short or a chain
-    // is too long, through compressed pointers in the output arrays.
-    for (bool wide = false;; wide = true) {
-        Scratch ws;
-        if (int rc = ws.get(nullptr, 0, c0 + nb + (wide ? 0 : 2 * nq), s)) {
-            if (wide) return rc;
-            continue;
-        }
-        char* p = static_cast<char*>(ws.p);
-        unsigned* cnt = reinterpret_cast<unsigned*>(p);
-        uint8_t* dirs = reinterpret_cast<uint8_t*>(p + c0);
-        uint16_t* q_up = reinterpret_cast<uint16_t*>(p + c0 + nb);
-        uint16_t* q_dn = reinterpret_cast<uint16_t*>(p + c0 + nb + nq);
-        if (clear_counters(cnt, s)) return MSZ_EDEVICE;
-        launch_dirs(field, gr, dirs, cnt, s);
-        if (wide) {
-            launch_label_forests(dirs, gr, max_label, min_label, cnt, s);
-            launch_label_final(max_label, min_label, gr, max_label, min_label, cnt, s);
-        } else {
-            launch_label_codes(dirs, gr, q_up, q_dn, s);
-            launch_label_direct(q_up, q_dn, gr, max_label, min_label, cnt, s);
-        }
-        if (int rc = read_counters(cnt, hc, s)) return rc;
-        if (hc[kCntErr] & kErrWalk) return MSZ_EDEVICE;
-        if (hc[kCntErr] & kErrNonFinite) return MSZ_ENONFINITE;
-        if (!(hc[kCntErr] & kErrLong)) return MSZ_OK;
-    }
+    // through compressed pointers in the output arrays
+    const size_t c0 = align256(kCntBlockWords * sizeof(unsigned));
+    Scratch ws;
+    if (int rc = ws.get(nullptr, 0, c0 + align256(gr.n), s)) return rc;
+    unsigned* cnt = static_cast<unsigned*>(ws.p);
+    uint8_t* dirs = static_cast<uint8_t*>(ws.p) + c0;
+    if (clear_counters(cnt, s)) return MSZ_EDEVICE;
+    launch_dirs(field, gr, dirs, cnt, s);
+    launch_label_forests(dirs, gr, max_label, min_label, cnt, s);
+    launch_label_final(max_label, min_label, gr, max_label, min_label, cnt, s);
+    if (int rc = read_counters(cnt, hc, s)) return rc;
+    if (hc[kCntErr] & kErrWalk) return MSZ_EDEVICE;
+    return hc[kCntErr] & kErrNonFinite ? MSZ_ENONFINITE : MSZ_OK;
 }
 
 int msz_count_false(const float* f, const float* g, msz_dims d, msz_false_counts* out, void* stream) {
@@ -1178,37 +1163,37 @@ int msz_count_false(const float* f, const float* g, msz_dims d, msz_false_counts
     if (!hc) return MSZ_EDEVICE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const size_t c0 = align256(kCntBlockWords * sizeof(unsigned));
-    const size_t nb = align256(gr.n);
-    for (bool wide = false;; wide = true) {  // as in msz_labels
-        const size_t nq = align256(size_t(gr.n) * (wide ? 4 : 2));
-        Scratch ws;
-        if (int rc = ws.get(nullptr, 0, c0 + 2 * nb + 4 * nq, s)) return rc;
-        char* p = static_cast<char*>(ws.p);
-        unsigned* cnt = reinterpret_cast<unsigned*>(p);
-        uint8_t* df = reinterpret_cast<uint8_t*>(p + c0);
-        uint8_t* dg = df + nb;
-        char* q[4];  // f's ascents and descents, g's
-        for (int k = 0; k < 4; ++k) q[k] = p + c0 + 2 * nb + k * nq;
+    const size_t nb = align256(gr.n), nq = align256(size_t(gr.n) * 2);
+    Scratch ws, more;
+    if (int rc = ws.get(nullptr, 0, c0 + 2 * nb + 4 * nq, s)) return rc;
+    char* p = static_cast<char*>(ws.p);
+    unsigned* cnt = reinterpret_cast<unsigned*>(p);
+    uint8_t* df = reinterpret_cast<uint8_t*>(p + c0);
+    uint8_t* dg = df + nb;
+    char* q = p + c0 + 2 * nb;
+    uint16_t* c[4];  // f's ascents and descents, g's
+    for (int k = 0; k < 4; ++k) c[k] = reinterpret_cast<uint16_t*>(q + k * nq);
+    if (clear_counters(cnt, s)) return MSZ_EDEVICE;
+    launch_dirs(f, gr, df, cnt, s);
+    launch_dirs(g, gr, dg, cnt, s);
+    launch_label_codes(df, gr, c[0], c[1], cnt, s);
+    launch_label_codes(dg, gr, c[2], c[3], cnt, s);
+    launch_compare_direct(df, dg, c[0], c[1], c[2], c[3], gr, cnt, s);
+    if (int rc = read_counters(cnt, hc, s)) return rc;
+    if (hc[kCntErr] & kErrWalk) return MSZ_EDEVICE;
+    if (hc[kCntErr] & kErrNonFinite) return MSZ_ENONFINITE;
+    if (hc[kCntErr] & kErrLong) {
+        // through compressed pointers; f's lie over the codes
+        if (int rc = more.get(nullptr, 0, 4 * nq, s)) return rc;
+        int* w[4];
+        for (int k = 0; k < 4; ++k)
+            w[k] = reinterpret_cast<int*>((k < 2 ? q : static_cast<char*>(more.p)) + (k & 1) * 2 * nq);
         if (clear_counters(cnt, s)) return MSZ_EDEVICE;
-        launch_dirs(f, gr, df, cnt, s);
-        launch_dirs(g, gr, dg, cnt, s);
-        if (wide) {
-            int* w[4];
-            for (int k = 0; k < 4; ++k) w[k] = reinterpret_cast<int*>(q[k]);
-            launch_label_forests(df, gr, w[0], w[1], cnt, s);
-            launch_label_forests(dg, gr, w[2], w[3], cnt, s);
-            launch_compare(df, dg, w[0], w[1], w[2], w[3], gr.n, cnt, s);
-        } else {
-            uint16_t* c[4];
-            for (int k = 0; k < 4; ++k) c[k] = reinterpret_cast<uint16_t*>(q[k]);
-            launch_label_codes(df, gr, c[0], c[1], s);
-            launch_label_codes(dg, gr, c[2], c[3], s);
-            launch_compare_direct(df, dg, c[0], c[1], c[2], c[3], gr, cnt, s);
-        }
+        launch_label_forests(df, gr, w[0], w[1], cnt, s);
+        launch_label_forests(dg, gr, w[2], w[3], cnt, s);
+        launch_compare(df, dg, w[0], w[1], w[2], w[3], gr.n, cnt, s);
         if (int rc = read_counters(cnt, hc, s)) return rc;
         if (hc[kCntErr] & kErrWalk) return MSZ_EDEVICE;
-        if (hc[kCntErr] & kErrNonFinite) return MSZ_ENONFINITE;
-        if (!(hc[kCntErr] & kErrLong)) break;
     }
     out->fp_max = hc[kCntCase + 0];
     out->fp_min = hc[kCntCase + 1];

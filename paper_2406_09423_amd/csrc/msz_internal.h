@@ -26,6 +26,7 @@ enum : int {
     kCntInexact = 10,
     kCntWrongMax = 11,
     kCntWrongMin = 12,
+    kCntExits = 13,    // vertices whose line leaves its label tile (both families)
     kCntSlots = 16
 };
 enum : unsigned { kErrNonFinite = 1u, kErrBound = 2u, kErrWarmNonFinite = 4u, kErrWarmBound = 8u, kErrWalk = 16u, kErrLong = 32u };
@@ -142,14 +143,14 @@ struct Scratch {
 
 // cnt: where a non-finite value is reported (NULL: not checked)
 void launch_dirs(const float* h, const Grid& gr, uint8_t* dirs_out, unsigned* cnt, hipStream_t s);
-// Labels and their comparison straight from tile codes; kErrLong is reported
-// where a chain is too long for that.
-void launch_label_codes(const uint8_t* dirs, const Grid& gr, uint16_t* q_up, uint16_t* q_dn, hipStream_t s);
-void launch_label_direct(const uint16_t* q_up, const uint16_t* q_dn, const Grid& gr, int* M, int* m, unsigned* cnt,
-                         hipStream_t s);
+// The comparison of two label fields straight from tile codes.  Where many lines
+// leave their tiles or a chain of exits is too long for that, kErrLong is
+// reported and the counts are not valid.
+void launch_label_codes(const uint8_t* dirs, const Grid& gr, uint16_t* q_up, uint16_t* q_dn, unsigned* cnt,
+                        hipStream_t s);
 void launch_compare_direct(const uint8_t* dirs_f, const uint8_t* dirs_g, const uint16_t* qfu, const uint16_t* qfd,
                            const uint16_t* qgu, const uint16_t* qgd, const Grid& gr, unsigned* cnt, hipStream_t s);
-// The same through compressed pointers, for any chains.
+// Labels and their comparison through compressed pointers, for any chains.
 void launch_label_forests(const uint8_t* dirs, const Grid& gr, int* q_up, int* q_dn, unsigned* cnt,
                           hipStream_t s);
 void launch_label_final(const int* q_up, const int* q_dn, const Grid& gr, int* M, int* m, unsigned* cnt,

@@ -70,6 +70,16 @@ __device__ __forceinline__ unsigned wave_sum(unsigned v) {
     return v;
 }
 
+// Words that blocks of one kernel hand to each other: device-scope accesses,
+// of which every XCD sees one value.
+__device__ __forceinline__ int ld_dev(const int* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned ld_dev(const unsigned* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_dev(int* p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
 // Inclusive prefix sum over a wave in the VALU (shifts within the rows of 16
 // lanes, then the row totals broadcast onward), without the LDS round trip
 // per step of a lane shuffle.
@@ -732,13 +742,13 @@ __device__ __forceinline__ void target_edit(bool preempt, uint8_t* __restrict__ 
 // id) or the first vertex e outside the tile on its integral line (stored as
 // -e-1).  Such exit targets lie on the face layer of their own tile.  A label
 // is then the end of a short chain of exits (on the fields here a tile exit
-// leads on through another tile a quarter of the time): follow_root walks it.
+// leads on through another tile a quarter of the time): follow_roots walks it.
 // The correction loop follows the chains where it needs labels (a few
-// gathers per hundred vertices), and so do msz_labels and msz_count_false.
-// Where a chain is too long for that (k_label_direct), these compress the exit
-// targets' pointers to their roots first (each thread walks its own chain,
-// writing back every step; any value read is an ancestor, so no barrier is
-// needed and each walk strictly advances).
+// gathers per hundred vertices), and so does msz_count_false on rough fields
+// (k_compare_direct).  msz_labels, and msz_count_false on smooth fields, whose
+// chains are long, compress the exit targets' pointers to their roots first
+// (each thread walks its own chain, writing back every step; any value read is
+// an ancestor, so no barrier is needed and each walk strictly advances).
 
 // Label tiles of 4096 vertices, wide in x: a tile row fills whole 128-byte
 // lines of the label passes' int32 arrays and halves of their 16-bit ones
@@ -888,20 +898,21 @@ __device__ __forceinline__ void follow_roots(const int* q_up, const int* q_dn, i
     }
 }
 
-// The same over arrays of TileCodes, with at most CAP gathers per chain (err
+// The same over arrays of TileCodes, with at most cap gathers per chain (err
 // is set in bad when a chain is longer): chain k in q_up, or in q_dn when dn[k];
 // from S on, in a second pair of forests, r_up and r_dn.  (The forest is
 // chosen at each load: a pointer per chain would cost two registers each.)
-template <int NDIM, int K, int S, int CAP = kMaxChain>
+template <int NDIM, int K, int S>
 __device__ __forceinline__ void follow_codes(const Grid& gr, const uint16_t* q_up, const uint16_t* q_dn,
                                              const uint16_t* r_up, const uint16_t* r_dn, const bool (&dn)[K],
-                                             int (&y)[K], unsigned& bad, unsigned& hops, unsigned err = kErrWalk) {
+                                             int (&y)[K], unsigned& bad, unsigned& hops, int cap = kMaxChain,
+                                             unsigned err = kErrWalk) {
     for (int pass = 0;; ++pass) {
         bool any = false;
 #pragma unroll
         for (int k = 0; k < K; ++k) any |= y[k] < 0;
         if (!any) return;
-        if (pass == CAP) {
+        if (pass == cap) {
             bad |= err;
 #pragma unroll
             for (int k = 0; k < K; ++k) y[k] = max(y[k], 0);
@@ -922,7 +933,8 @@ __device__ __forceinline__ void follow_codes(const Grid& gr, const uint16_t* q_u
 // One label tile; su, sd: LDS arrays of the tile's vertex count; tab: the
 // block's slot table (fill_slot_steps).  The caller separates consecutive
 // tiles of one block with a barrier.  Out: uint16_t stores TileCodes, int
-// the pointers as ids (a root as itself, an exit e as -e-1).
+// the pointers as ids (a root as itself, an exit e as -e-1).  exits receives
+// the number of exits among the thread's TileCodes.
 //
 // Thread t owns the 4-vertex row groups starting at l = 4 t + 1024 k and
 // keeps their pointers in registers; the LDS copy is what other threads read.
@@ -936,7 +948,7 @@ __device__ __forceinline__ void follow_codes(const Grid& gr, const uint16_t* q_u
 template <int NDIM, typename Out>
 __device__ __forceinline__ void label_tile_body(const uint8_t* __restrict__ dirs, const Grid& gr, int tile,
                                                 Out* __restrict__ q_up, Out* __restrict__ q_dn, uint16_t* su,
-                                                uint16_t* sd, const SlotStep* tab) {
+                                                uint16_t* sd, const SlotStep* tab, unsigned& exits) {
     using T = LabelTile<NDIM>;
     using P = TilePos<NDIM>;
     using C = TileCode<NDIM>;
@@ -1032,15 +1044,18 @@ __device__ __forceinline__ void label_tile_body(const uint8_t* __restrict__ dirs
     const unsigned corner = C::corner(gr, X0, Y0, Z0);
     auto store4 = [&](Out* q, const int (&p)[4]) {
         if constexpr (sizeof(Out) == 2) {
-            *reinterpret_cast<Shorts4*>(q) = Shorts4{static_cast<unsigned>(p[0]) | (static_cast<unsigned>(p[1]) << 16),
-                                                     static_cast<unsigned>(p[2]) | (static_cast<unsigned>(p[3]) << 16)};
+            const Shorts4 v{static_cast<unsigned>(p[0]) | (static_cast<unsigned>(p[1]) << 16),
+                            static_cast<unsigned>(p[2]) | (static_cast<unsigned>(p[3]) << 16)};
+            constexpr unsigned kExits = C::kExit | (C::kExit << 16);
+            exits += __popc(v.x & kExits) + __popc(v.y & kExits);
+            *reinterpret_cast<Shorts4*>(q) = v;
         } else {
             store_ints4(q, C::target(gr, corner, p[0]), C::target(gr, corner, p[1]), C::target(gr, corner, p[2]),
                         C::target(gr, corner, p[3]));
         }
     };
     auto store1 = [&](Out* q, int p) {
-        if constexpr (sizeof(Out) == 2) *q = static_cast<uint16_t>(p);
+        if constexpr (sizeof(Out) == 2) *q = static_cast<uint16_t>(p), exits += (p & C::kExit) != 0u;
         else *q = C::target(gr, corner, p);
     };
 #pragma unroll
@@ -1064,16 +1079,23 @@ __device__ __forceinline__ void label_tile_body(const uint8_t* __restrict__ dirs
     }
 }
 
+// (TileCodes: also counts the exits, for k_compare_direct)
 template <int NDIM, typename Out>
 __global__ void __launch_bounds__(256) k_label_tile(const uint8_t* __restrict__ dirs, Grid gr,
-                                                    Out* __restrict__ q_up, Out* __restrict__ q_dn) {
+                                                    Out* __restrict__ q_up, Out* __restrict__ q_dn,
+                                                    unsigned* __restrict__ cnt) {
     constexpr int NT = LabelTile<NDIM>::X * LabelTile<NDIM>::Y * LabelTile<NDIM>::Z;
     __shared__ __align__(16) uint16_t su[NT];
     __shared__ __align__(16) uint16_t sd[NT];
     __shared__ __align__(16) SlotStep tab[16];
     fill_slot_steps<NDIM>(tab);
     __syncthreads();
-    label_tile_body<NDIM>(dirs, gr, xcd_logical_block(blockIdx.x, gridDim.x), q_up, q_dn, su, sd, tab);
+    unsigned exits[1] = {0u};
+    label_tile_body<NDIM>(dirs, gr, xcd_logical_block(blockIdx.x, gridDim.x), q_up, q_dn, su, sd, tab, exits[0]);
+    if constexpr (sizeof(Out) == 2) {
+        const int idx[1] = {kCntExits};
+        block_add<1>(exits, cnt, idx);
+    }
 }
 
 // Number of face-layer vertices of a full label tile.
@@ -1283,61 +1305,6 @@ __global__ void __launch_bounds__(256) k_label_final(const int* q_up, const int*
     unsigned bad = 0, hops = 0;
     for (int tile = range.first; tile < range.hi; tile += range.stride)
         bad |= label_final_tile<NDIM>(q_up, q_dn, gr, tile, M, m, hops);
-    if (bad) atomicOr(cnt + kCntErr, bad);
-}
-
-// Labels straight from the tile codes: every vertex follows its own chain.
-// The chains of measured fields cross 0.3 tiles on average and at most 9; a
-// chain of more than kDirectHops (a line that winds through the whole grid, of
-// which there may be one per vertex) sets kErrLong, and the caller then takes
-// the route through compressed pointers, which halves such chains instead of
-// walking each.  Against that route (ids out, three compressions, final
-// labels) the two int32 forests are not stored and read back four times:
-// labels of a 256^3 field 267 -> 227 us, the comparison of two 3600 x 2400
-// fields 195 -> 167 us (calls timed whole, with the value check in the
-// direction pass instead of a pass of its own).
-constexpr int kDirectHops = 64;
-template <int NDIM>
-__global__ void __launch_bounds__(256) k_label_direct(const uint16_t* __restrict__ q_up,
-                                                      const uint16_t* __restrict__ q_dn, Grid gr,
-                                                      int* __restrict__ M, int* __restrict__ m,
-                                                      unsigned* __restrict__ cnt) {
-    using C = TileCode<NDIM>;
-    const ItemRange range = xcd_items(label_tiles_of(gr));
-    unsigned bad = 0, hops = 0;
-    for (int tile = range.first; tile < range.hi; tile += range.stride) {
-        const int3 o = tile_origin<NDIM>(gr, tile);
-        const unsigned corner = C::corner(gr, o.x, o.y, o.z);
-        TileGroup<NDIM> tg[4];
-        Shorts4 u[4], d[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            tg[k] = tile_group<NDIM>(gr, tile, k);
-            u[k] = load_codes4(q_up, tg[k].i0, tg[k].count);
-            d[k] = load_codes4(q_dn, tg[k].i0, tg[k].count);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const unsigned cu[4] = {u[k].x & 0xFFFFu, u[k].x >> 16, u[k].y & 0xFFFFu, u[k].y >> 16};
-            const unsigned cd[4] = {d[k].x & 0xFFFFu, d[k].x >> 16, d[k].y & 0xFFFFu, d[k].y >> 16};
-            const bool dn[8] = {false, true, false, true, false, true, false, true};
-            int y[8];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                y[2 * j] = j < tg[k].count ? C::target(gr, corner, cu[j]) : 0;
-                y[2 * j + 1] = j < tg[k].count ? C::target(gr, corner, cd[j]) : 0;
-            }
-            follow_codes<NDIM, 8, 8, kDirectHops>(gr, q_up, q_dn, nullptr, nullptr, dn, y, bad, hops, kErrLong);
-            if (tg[k].vec) {
-                store_ints4(M + tg[k].i0, y[0], y[2], y[4], y[6]);
-                store_ints4(m + tg[k].i0, y[1], y[3], y[5], y[7]);
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (j < tg[k].count) M[tg[k].i0 + j] = y[2 * j], m[tg[k].i0 + j] = y[2 * j + 1];
-            }
-        }
-    }
     if (bad) atomicOr(cnt + kCntErr, bad);
 }
 
@@ -1638,13 +1605,47 @@ __global__ void __launch_bounds__(256) k_compare(const uint8_t* __restrict__ dir
     block_add<7>(c, cnt, idx);
 }
 
-// The same from tile codes (see k_label_direct).  A vertex whose codes in g and
-// f agree and end in the tile needs no walk.  An item is a tile, or a quarter
-// of one (a row group per thread) where the tiles are fewer than the grid's
-// blocks: the walks of a block's groups one after the other then are the
-// kernel's time.  Whole calls: 40x50x60 127 us with tiles, 97 with quarters,
-// 100x110x120 145 and 125, 3600x2400 (2175 tiles) 174 and 175, 512^3 2.70 and
-// 2.78 ms.
+// The same from tile codes: every vertex follows its own chains of exits, if
+// its codes in g and f differ or leave the tile.  Against the route through
+// compressed pointers, half the scratch, and four int32 forests are not stored
+// and read back four times: the comparison of two 3600x2400 fields 195 -> 167
+// us (calls timed whole, with the value check in the direction pass instead of
+// a pass of its own).  But a walk is a chain of dependent gathers, which the
+// other route shortens once per tile face for all vertices behind it, so that
+// smooth fields, whose lines run through many tiles, are left to it (kErrLong):
+// at once when more than a share of the pointers leave their tiles, and else,
+// for fields smooth in a part, by all blocks as soon as one chain is longer
+// than a limit.  Random fields with a spectrum k^-3 (2D) and k^-11/3 (3D) have
+// shares of 0.07 and 0.32 and chains of at most 9.  Whole calls by this kernel
+// and by the other route (which then costs what this one has done so far):
+// 3600x2400, share 0.07 187 and 262 us, 0.3 302 and 282, 0.5 426 and 290,
+// eight wide bumps (0.99) 1174 and 324; 256^3, share 0.5 585 and 632, 0.72 825
+// and 704, eight bumps 2981 and 779, a tenth of the field smooth 1069 and 679.
+// In fields of fewer than 1024 tiles the walks take less than the other
+// route's launches and its wait unless nearly all lines are long: 1200x1800
+// (570 tiles), a quarter smooth, 157 and 242, a ramp 282 and 209; 2000x2500
+// (1580 tiles), 0.4 of it smooth, 363 and 228.
+// An item is a tile, or a quarter of one (a row group per thread) where the
+// tiles are fewer than the grid's blocks: the walks of a block's groups one
+// after the other then are the kernel's time.  Whole calls: 40x50x60 127 us
+// with tiles, 97 with quarters, 100x110x120 145 and 125, 3600x2400 (2175
+// tiles) 174 and 175, 512^3 2.70 and 2.78 ms.
+struct DirectLimits {
+    int hops;     // longest chain that is walked
+    float share;  // largest share of exits among the pointers
+};
+template <int NDIM>
+__device__ __forceinline__ DirectLimits direct_limits(const Grid& gr) {
+    if (label_tiles_of(gr) < 1024) return {64, 0.9f};
+    return {16, NDIM == 3 ? 0.5f : 0.3f};
+}
+// Whether more than `share` of the 4 n pointers are exits.
+__device__ __forceinline__ bool many_exits(const unsigned* cnt, int n, float share) {
+    static_assert(kSlots == 64, "a slot per lane");
+    // in units of 64, so that the sum of the slots stays below 2^32
+    const unsigned exits = wave_sum(cnt[(threadIdx.x & 63) * kSlotStride + kCntExits] >> 6);
+    return 16.0f * static_cast<float>(exits) > share * static_cast<float>(n);
+}
 static_assert(LabelTile<2>::X * LabelTile<2>::Y == 4096, "four row groups per thread");
 template <int NDIM, int PARTS>
 __global__ void __launch_bounds__(256) k_compare_direct(const uint8_t* __restrict__ dirs_f,
@@ -1655,15 +1656,21 @@ __global__ void __launch_bounds__(256) k_compare_direct(const uint8_t* __restric
                                                         const uint16_t* __restrict__ qgd, Grid gr,
                                                         unsigned* __restrict__ cnt) {
     using C = TileCode<NDIM>;
+    const DirectLimits limits = direct_limits<NDIM>(gr);
+    if (many_exits(cnt, gr.n, limits.share)) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(cnt + kCntErr, kErrLong);
+        return;
+    }
     const ItemRange range = xcd_items(PARTS * label_tiles_of(gr));
     unsigned c[7] = {0, 0, 0, 0, 0, 0, 0}, cases[4] = {0, 0, 0, 0};
     unsigned bad = 0, hops = 0;
-    for (int item = range.first; item < range.hi; item += range.stride) {
+    bool stop = false;  // a chain is too long, here or in another block: the counts are not used
+    for (int item = range.first; item < range.hi && !stop; item += range.stride) {
         const int tile = item / PARTS;
         const int3 o = tile_origin<NDIM>(gr, tile);
         const unsigned corner = C::corner(gr, o.x, o.y, o.z);
 #pragma unroll 2
-        for (int part = 0; part < 4 / PARTS; ++part) {
+        for (int part = 0; part < 4 / PARTS && !stop; ++part) {
             const int k = PARTS == 4 ? item & 3 : part;
             const TileGroup<NDIM> t = tile_group<NDIM>(gr, tile, k);
             unsigned df = 0u, dg = 0u;
@@ -1678,6 +1685,7 @@ __global__ void __launch_bounds__(256) k_compare_direct(const uint8_t* __restric
             }
             const Shorts4 fu = load_codes4(qfu, t.i0, t.count), fd = load_codes4(qfd, t.i0, t.count);
             const Shorts4 gu = load_codes4(qgu, t.i0, t.count), gd = load_codes4(qgd, t.i0, t.count);
+            stop = (ld_dev(cnt + kCntErr) & kErrLong) != 0u;
             (void)cases4(df, dg, cases);
             const unsigned a[4] = {gu.x, gu.y, gd.x, gd.y}, b[4] = {fu.x, fu.y, fd.x, fd.y};
             // chains of g in 0..7 (ascents of the four vertices, then descents), of f in 8..15
@@ -1691,7 +1699,11 @@ __global__ void __launch_bounds__(256) k_compare_direct(const uint8_t* __restric
                 y[e] = same ? 0 : C::target(gr, corner, cg);
                 y[8 + e] = same ? 0 : C::target(gr, corner, cf);
             }
-            follow_codes<NDIM, 16, 8, kDirectHops>(gr, qgu, qgd, qfu, qfd, dn, y, bad, hops, kErrLong);
+            if (!stop) follow_codes<NDIM, 16, 8>(gr, qgu, qgd, qfu, qfd, dn, y, bad, hops, limits.hops, kErrLong);
+            if (bad) {
+                atomicOr(cnt + kCntErr, bad);
+                stop = true;
+            }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const bool wM = y[j] != y[8 + j], wm = y[4 + j] != y[12 + j];
@@ -1705,7 +1717,6 @@ __global__ void __launch_bounds__(256) k_compare_direct(const uint8_t* __restric
     for (int t = 0; t < 4; ++t) c[t] = cases[t];
     const int idx[7] = {kCntCase + 0, kCntCase + 1, kCntCase + 2, kCntCase + 3,
                         kCntWrongMax, kCntWrongMin, kCntWrong};
-    if (bad) atomicOr(cnt + kCntErr, bad);
     block_add<7>(c, cnt, idx);
 }
 
@@ -1814,21 +1825,16 @@ void launch_dirs(const float* h, const Grid& gr, uint8_t* dirs_out, unsigned* cn
 }
 
 template <typename Out>
-static void launch_label_tile(const uint8_t* dirs, const Grid& gr, Out* q_up, Out* q_dn, hipStream_t s) {
+static void launch_label_tile(const uint8_t* dirs, const Grid& gr, Out* q_up, Out* q_dn, unsigned* cnt,
+                              hipStream_t s) {
     const int nb = label_tiles_of(gr);
-    if (gr.ndim == 2) hipLaunchKernelGGL((k_label_tile<2, Out>), dim3(nb), dim3(256), 0, s, dirs, gr, q_up, q_dn);
-    else hipLaunchKernelGGL((k_label_tile<3, Out>), dim3(nb), dim3(256), 0, s, dirs, gr, q_up, q_dn);
+    if (gr.ndim == 2) hipLaunchKernelGGL((k_label_tile<2, Out>), dim3(nb), dim3(256), 0, s, dirs, gr, q_up, q_dn, cnt);
+    else hipLaunchKernelGGL((k_label_tile<3, Out>), dim3(nb), dim3(256), 0, s, dirs, gr, q_up, q_dn, cnt);
 }
 
-void launch_label_codes(const uint8_t* dirs, const Grid& gr, uint16_t* q_up, uint16_t* q_dn, hipStream_t s) {
-    launch_label_tile(dirs, gr, q_up, q_dn, s);
-}
-
-void launch_label_direct(const uint16_t* q_up, const uint16_t* q_dn, const Grid& gr, int* M, int* m, unsigned* cnt,
-                         hipStream_t s) {
-    const int nt = label_tiles_of(gr), nb = nt < kDirsBlocks ? nt : kDirsBlocks;
-    if (gr.ndim == 2) hipLaunchKernelGGL(k_label_direct<2>, dim3(nb), dim3(256), 0, s, q_up, q_dn, gr, M, m, cnt);
-    else hipLaunchKernelGGL(k_label_direct<3>, dim3(nb), dim3(256), 0, s, q_up, q_dn, gr, M, m, cnt);
+void launch_label_codes(const uint8_t* dirs, const Grid& gr, uint16_t* q_up, uint16_t* q_dn, unsigned* cnt,
+                        hipStream_t s) {
+    launch_label_tile(dirs, gr, q_up, q_dn, cnt, s);
 }
 
 template <int PARTS>
@@ -1857,7 +1863,7 @@ void launch_label_compress(const Grid& gr, int* q_up, int* q_dn, unsigned* cnt, 
 
 void launch_label_forests(const uint8_t* dirs, const Grid& gr, int* q_up, int* q_dn, unsigned* cnt,
                           hipStream_t s) {
-    launch_label_tile(dirs, gr, q_up, q_dn, s);
+    launch_label_tile(dirs, gr, q_up, q_dn, cnt, s);
     launch_label_compress(gr, q_up, q_dn, cnt, s);
 }
 
@@ -2237,14 +2243,6 @@ __device__ __forceinline__ void refresh_list(const EngField& F, int np, bool sum
 // completed: a device-scope fence, which on MI355X writes back the L2 of the
 // XCD, is never needed.  Everything else a step writes is read by later
 // steps, after the kernel boundary.
-__device__ __forceinline__ int ld_dev(const int* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned ld_dev(const unsigned* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_dev(int* p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
 // True in every thread of the block that draws ticket n - 1 of *ticket.
 __device__ __forceinline__ bool draw_last(int* ticket, int n, int* s_flag) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores and atomics have completed
@@ -2568,11 +2566,12 @@ __device__ __forceinline__ void eng_run_range(const EngField& F, const EngState&
             fill_slot_steps<NDIM>(s_tab);
             __syncthreads();
             for (int item = lo; item < hi; ++item) {
+                unsigned exits = 0;  // not used
                 if constexpr (SINGLE) {
-                    label_tile_body<NDIM>(F.dirs_f, gr, item, F.Mf, F.mf, su, sd, s_tab);
+                    label_tile_body<NDIM>(F.dirs_f, gr, item, F.Mf, F.mf, su, sd, s_tab, exits);
                 } else {
                     label_tile_body<NDIM>(F.dirs_f, gr, item, reinterpret_cast<uint16_t*>(F.Mf),
-                                          reinterpret_cast<uint16_t*>(F.mf), su, sd, s_tab);
+                                          reinterpret_cast<uint16_t*>(F.mf), su, sd, s_tab, exits);
                 }
                 __syncthreads();
                 if (lead) acct += (SINGLE ? 9 : 5) * tile_vertices<NDIM>(gr, item);
@@ -2585,7 +2584,8 @@ __device__ __forceinline__ void eng_run_range(const EngField& F, const EngState&
             __syncthreads();
             for (int item = lo; item < hi; ++item) {
                 if (!F.tile_dirty[item]) continue;
-                label_tile_body<NDIM>(F.dirs_g, gr, item, F.qu, F.qd, su, sd, s_tab);
+                unsigned exits = 0;  // not used
+                label_tile_body<NDIM>(F.dirs_g, gr, item, F.qu, F.qd, su, sd, s_tab, exits);
                 __syncthreads();
                 if (threadIdx.x == 0) {
                     F.tile_dirty[item] = 0;

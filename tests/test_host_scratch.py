@@ -49,13 +49,10 @@ def run(fake, code):
 
 
 def test_labels_with_little_memory(fake):
-    """The scratch of the first route (5 bytes per vertex) does not fit, that of
-    the second (one byte) does: the labels are computed."""
+    """Labels take one byte of scratch per vertex."""
     run(fake, """
-fake.fake_set(3 * n, 0, 0)
+fake.fake_set(2 * n, 0, 0)
 assert L.msz_labels(f, d, M, m, None) == msz.OK
-asked = [x for x in log() if x.startswith(("pool", "default"))]
-assert [x.endswith("fails") for x in asked] == [True, True, False], asked
 assert fake.fake_live() == 1  # the pinned counters
 """)
 
