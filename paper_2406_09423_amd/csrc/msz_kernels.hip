@@ -1356,39 +1356,102 @@ __device__ __forceinline__ int f_pointer(const Grid& gr, const void* a, int i, u
     else return TileCode<NDIM>::target(gr, corner, static_cast<const uint16_t*>(a)[i]);
 }
 
-// Mislabelled vertices of one tile (the start field's count): every vertex's
-// labels in g and f are resolved.  bytes receives the algorithmic bytes.
-template <int NDIM, bool FLABELS>
-__device__ __forceinline__ void count_wrong_tile(const Forests& fo, const Grid& gr, int tile, unsigned& wrong,
-                                                 unsigned& bad, unsigned& hops, unsigned long long& bytes) {
+// The labels of a thread's vertices of a tile (vertex j of row group k: entry
+// 4 k + j) in the forest of the TileCodes q: stored in lab, or, with COMPARE,
+// compared with it (bit e of differ is set where entry e is another).  Lines
+// that leave the tile at the same vertex share a label, so each such vertex,
+// not each line, is followed: T.at holds its pointer, then its root, at its
+// position.  By all threads of the block, with a barrier before the next use
+// of T; outside the grid the entries of any two forests are alike.
+template <int NDIM>
+struct ExitTable {
+    static constexpr int BOX = TileCode<NDIM>::HXY * (NDIM == 3 ? LabelTile<NDIM>::Z + 2 : 1);
+    int at[BOX];
+    unsigned short list[BOX - 4096];  // positions past the tile that a line leaves at
+    int count;
+};
+template <int NDIM, bool COMPARE>
+__device__ __forceinline__ void tile_labels(const uint16_t* q, const Grid& gr, int tile, unsigned corner,
+                                            ExitTable<NDIM>& T, int (&lab)[16], unsigned& differ, unsigned& bad,
+                                            unsigned& hops) {
     using C = TileCode<NDIM>;
-    const int3 o = tile_origin<NDIM>(gr, tile);
-    const unsigned corner = C::corner(gr, o.x, o.y, o.z);
-#pragma unroll 1
+    constexpr int K = 4;
+    for (int p = threadIdx.x; p < T.BOX; p += 256) T.at[p] = 0;
+    if (threadIdx.x == 0) T.count = 0;
+    Shorts4 c[4];
+    auto code = [&](int e) { return ((e & 2 ? c[e >> 2].y : c[e >> 2].x) >> (16 * (e & 1))) & 0xFFFFu; };
+#pragma unroll
     for (int k = 0; k < 4; ++k) {
         const TileGroup<NDIM> t = tile_group<NDIM>(gr, tile, k);
+        c[k] = load_codes4(q, t.i0, t.count);
+    }
+    __syncthreads();
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            int y[4] = {0, 0, 0, 0};  // g's ascent and descent, f's
-            if (j < t.count) {
-                const int i = t.i0 + j;
-                y[0] = C::target(gr, corner, fo.q_up[i]), y[1] = C::target(gr, corner, fo.q_dn[i]);
-                y[2] = f_pointer<NDIM, FLABELS>(gr, fo.Mf, i, corner), y[3] = f_pointer<NDIM, FLABELS>(gr, fo.mf, i, corner);
-                bytes += FLABELS ? 12 : 8;
+    for (int e = 0; e < 16; ++e) {
+        if (code(e) & C::kExit) T.at[code(e) & C::kPos] = C::target(gr, corner, code(e));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // (the codes stay packed: kept unpacked, they took the batch step kernels
+    // past the 128 registers of four waves)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) asm("" : "+v"(c[k].x), "+v"(c[k].y));
+    __syncthreads();
+    for (int p = threadIdx.x; p < T.BOX; p += 256)
+        if (T.at[p] < 0) T.list[atomicAdd(&T.count, 1)] = static_cast<unsigned short>(p);
+    __syncthreads();
+    const int n = T.count;
+    const bool dn[K] = {};
+    for (int i0 = threadIdx.x; i0 < n; i0 += 256 * K) {
+        int y[K];
+#pragma unroll
+        for (int e = 0; e < K; ++e) y[e] = i0 + 256 * e < n ? T.at[T.list[i0 + 256 * e]] : 0;
+        follow_codes<NDIM, K, K>(gr, q, q, nullptr, nullptr, dn, y, bad, hops);
+#pragma unroll
+        for (int e = 0; e < K; ++e)
+            if (i0 + 256 * e < n) T.at[T.list[i0 + 256 * e]] = y[e];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const int l = code(e) & C::kExit ? T.at[code(e) & C::kPos] : C::target(gr, corner, code(e));
+        if constexpr (COMPARE) differ |= l != lab[e] ? 1u << e : 0u;
+        else lab[e] = l;
+        if (e % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// Mislabelled vertices of one tile (the start field's count): every vertex's
+// labels in g and f are resolved.  The
+// count adds to a correction of a 256^3 ramp, whose lines run through the whole
+// grid, 0.43 ms (1.86 with every vertex following its own chain, 0.81 over
+// arrays of ids), of a random 256^3 field 0.18 (0.20, 0.17), of a 3600x2400
+// ramp 0.22 (1.91, 1.08).
+template <int NDIM, bool FLABELS>
+__device__ __forceinline__ void count_wrong_tile(const Forests& fo, const Grid& gr, int tile, ExitTable<NDIM>& T,
+                                                 unsigned& wrong, unsigned& bad, unsigned& hops) {
+    const int3 o = tile_origin<NDIM>(gr, tile);
+    const unsigned corner = TileCode<NDIM>::corner(gr, o.x, o.y, o.z);
+    unsigned differ = 0u;  // bit e: vertex e's label of either kind
+#pragma unroll 1
+    for (int w = 0; w < 2; ++w) {
+        int lab[16];
+        tile_labels<NDIM, false>(w ? fo.q_dn : fo.q_up, gr, tile, corner, T, lab, differ, bad, hops);
+        const void* f = w ? fo.mf : fo.Mf;
+        __syncthreads();
+        if constexpr (FLABELS) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const TileGroup<NDIM> t = tile_group<NDIM>(gr, tile, k);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (j < t.count && static_cast<const int*>(f)[t.i0 + j] != lab[4 * k + j]) differ |= 1u << (4 * k + j);
             }
-            if constexpr (FLABELS) {
-                const bool dn[2] = {false, true};
-                int yg[2] = {y[0], y[1]};
-                follow_codes<NDIM, 2, 2>(gr, fo.q_up, fo.q_dn, nullptr, nullptr, dn, yg, bad, hops);
-                y[0] = yg[0], y[1] = yg[1];
-            } else {
-                const bool dn[4] = {false, true, false, true};
-                follow_codes<NDIM, 4, 2>(gr, fo.q_up, fo.q_dn, static_cast<const uint16_t*>(fo.Mf),
-                                         static_cast<const uint16_t*>(fo.mf), dn, y, bad, hops);
-            }
-            wrong += y[0] != y[2] || y[1] != y[3];
+        } else {
+            tile_labels<NDIM, true>(static_cast<const uint16_t*>(f), gr, tile, corner, T, lab, differ, bad, hops);
+            __syncthreads();
         }
     }
+    wrong += __popc(differ);
 }
 
 // Global id of the vertex with tile-local index l (l = x + X (y + Y z) in the
@@ -2748,11 +2811,14 @@ __device__ __forceinline__ void eng_run_range(const EngField& F, const EngState&
             for (int item = lo; item < hi; ++item) {
                 // the start field's count needs every mislabelled vertex;
                 // the loop's rounds need only the troublemakers
-                if (st.init)
-                    count_wrong_tile<NDIM, SINGLE>(fo, gr, item, wrong, bad, hops, acct);
-                else
+                if (st.init) {
+                    static_assert(sizeof(ExitTable<NDIM>) <= kEngSmemBytes, "the table of exits fits");
+                    count_wrong_tile<NDIM, SINGLE>(fo, gr, item, *reinterpret_cast<ExitTable<NDIM>*>(smem), wrong, bad, hops);
+                    if (lead) acct += (SINGLE ? 12 : 8) * tile_vertices<NDIM>(gr, item);
+                } else {
                     detect_r_tile_sparse<NDIM, SINGLE>(F.dirs_f, F.dirs_g, fo, gr, item, item + 1, hi, words, tl,
                                                        cand_up, cand_dn, &s_cand, cases, changed, bad, hops, acct);
+                }
                 if (lead) acct += 2 * tile_vertices<NDIM>(gr, item);
                 __syncthreads();  // every wave's additions to the list are in s_targets
                 // past half the list: edit what it holds and empty it

@@ -35,6 +35,17 @@ def _bumps(shape, smooth, seed):
     return f
 
 
+def _seconds(call):
+    call()
+    times = []
+    for _ in range(9):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        call()
+        times.append(time.perf_counter() - t)
+    return sorted(times)[4]
+
+
 # 1088 and 1280 label tiles, and 99 and 60
 @pytest.mark.parametrize("shape", [(2048, 2176), (64, 128, 640), (350, 1100), (40, 31, 150)])
 @pytest.mark.parametrize("smooth", [1.0, 0.6, 0.15])
@@ -50,6 +61,32 @@ def test_smooth_and_half_smooth_fields(msz, shape, smooth):
 
 
 @pytest.mark.parametrize("shape", [(2400, 3600), (256, 256, 256)])
+def test_count_of_smooth_start_fields(msz, shape):
+    """Counting the mislabelled vertices of the start field adds less to the
+    correction of a ramp than one and a half times what it takes without
+    (following every vertex's chain added two to three and a half times)."""
+    f = sum(torch.linspace(0, k + 1.0, s, device="cuda").reshape([-1 if a == k else 1 for a in range(len(shape))])
+            for k, s in enumerate(shape)).contiguous()
+    ws = torch.empty(msz.workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    plain, counted = (_seconds(lambda: msz.fix(f, f, 0.1, workspace=ws, count_init=c)) for c in (False, True))
+    assert counted < 2.5 * plain
+
+
+@pytest.mark.parametrize("shape", [(350, 1100), (40, 31, 150)])
+@pytest.mark.parametrize("smooth", [1.0, 0.5])
+def test_mislabelled_vertices_of_smooth_start_fields(msz, shape, smooth):
+    f = _bumps(shape, smooth, 9)
+    fh = (f - np.random.default_rng(10).uniform(0, 1e-3, shape)).astype(np.float32)
+    want = oracle.fix(f, fh, 2e-3, max_rounds=1)
+    fd, fhd = torch.from_numpy(f).cuda(), torch.from_numpy(fh).cuda()
+    runs = [msz.fix(fd, fhd, 2e-3, max_rounds=1, count_init=True)]
+    runs += msz.fix_batch([(fd, fhd, 2e-3)] * 2, max_rounds=1, count_init=True)[1]
+    for rc, d, g, st in runs:
+        assert rc == want[0] and st == want[3]
+        assert np.array_equal(g.cpu().numpy(), want[2])
+
+
+@pytest.mark.parametrize("shape", [(2400, 3600), (256, 256, 256)])
 def test_smooth_fields_take_little_longer(msz, shape):
     """A ramp's lines run through the whole grid; its labels and counts take
     less than three times those of a rough field (walking every line took seven
@@ -59,15 +96,5 @@ def test_smooth_fields_take_little_longer(msz, shape):
     ramp = sum(torch.linspace(0, k + 1.0, s, device="cuda").reshape([-1 if a == k else 1 for a in range(len(shape))])
                for k, s in enumerate(shape)).contiguous()
 
-    def seconds(call):
-        call()
-        times = []
-        for _ in range(9):
-            torch.cuda.synchronize()
-            t = time.perf_counter()
-            call()
-            times.append(time.perf_counter() - t)
-        return sorted(times)[4]
-
     for call in (lambda h: msz.labels(h), lambda h: msz.count_false(h, 2 * h)):
-        assert seconds(lambda: call(ramp)) < 3 * seconds(lambda: call(rough))
+        assert _seconds(lambda: call(ramp)) < 3 * _seconds(lambda: call(rough))
