@@ -347,8 +347,8 @@ size_t msz_edits_bound(int64_t n);
  * (DEVICE, 16-byte aligned, capacity bytes).  *out_bytes (HOST) receives the
  * encoded size; MSZ_EINVAL if it exceeds capacity (msz_edits_bound(n) always
  * suffices) or if the stream would pass 2^32 words (more than about 1.4e9
- * edits).  stats (HOST) may be NULL.  Takes its scratch (about 8 bytes per
- * edit) from the library's pool and synchronises before returning. */
+ * edits).  stats (HOST) may be NULL.  Takes its scratch (at most about 8 bytes
+ * per entry) from the library's pool and synchronises before returning. */
 int msz_encode_edits(const float* edits, int64_t n, void* out, size_t capacity, size_t* out_bytes,
                      msz_edit_stats* stats, void* stream);
 

@@ -15,6 +15,7 @@ std::map<void*, size_t> live;
 std::string text;
 size_t largest = ~size_t(0);  // a larger request of device memory fails
 int current = 0, of_stream = 0;
+unsigned word = 0;     // what copies of four bytes to the host bring
 bool pattern = false;  // copies to the host bring 0, 1, 0, 1, ... as floats
 hipError_t last = hipSuccess;
 
@@ -45,6 +46,7 @@ void fake_set(size_t largest_request, int current_device, int device_of_streams)
     of_stream = device_of_streams;
     text.clear();
 }
+void fake_word(unsigned w) { word = w; }
 void fake_pattern(int on) { pattern = on != 0; }
 const char* fake_log() { return text.c_str(); }
 size_t fake_live() { return live.size(); }
@@ -77,6 +79,7 @@ hipError_t hipFreeAsync(void* p, hipStream_t) {
 }
 hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKind kind, hipStream_t) {
     std::memcpy(dst, src, bytes);
+    if (kind == hipMemcpyDeviceToHost && bytes == 4) std::memcpy(dst, &word, 4);
     for (size_t i = 0; pattern && kind == hipMemcpyDeviceToHost && i < bytes / 4; ++i)
         static_cast<float*>(dst)[i] = static_cast<float>(i & 1);
     return hipSuccess;

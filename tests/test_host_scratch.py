@@ -96,3 +96,22 @@ fake.fake_pattern(1)  # a value range of 1
 rc = L.msz_net_features(f, f, msz.Dims(3, {nx}, {ny}, {nz}), ctypes.c_float(0.1), array(16), None, 0, None)
 assert rc == msz.OK, (rc, log())
 """)
+
+
+@pytest.mark.parametrize("n,some", [(3600 * 2400, (600000, 700000, 840001, 8000000)), (2 ** 27 + 5, (9000000, 11000001, 16000000)),
+                                    (300 * 200, (4100, 5400, 6100, 8000))])
+def test_new_edits_need_no_new_memory(fake, n, some):
+    """The scratch of an encoding is of the same size for any edits of a field
+    (of a large field, or of few edits, for edits of about the same number), so
+    that the pool has it at hand."""
+    run(fake, f"""
+size = ctypes.c_size_t()
+asked = []
+for m in {some}:
+    fake.fake_set(EVERY, 0, 0)
+    fake.fake_word(m)  # the number of edits, and the words of the stream
+    rc = L.msz_encode_edits(f, {n}, M, ctypes.c_size_t(2 ** 40), ctypes.byref(size), None, None)
+    assert rc == msz.OK, rc
+    asked.append([x for x in log() if x.startswith(("pool", "default"))])
+assert all(a == asked[0] for a in asked), asked
+""")
