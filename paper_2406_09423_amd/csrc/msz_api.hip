@@ -578,10 +578,11 @@ int run_engine(std::vector<EngField>& hf, std::vector<EngStats>& st, bool timing
         const int64_t chunks = (static_cast<int64_t>(tab[0].gr.n) + kEngChunk - 1) / kEngChunk;
         tab[0].sum = chunks >= static_cast<int64_t>(kSelectChunks) * (has3 ? grid3 : grid2) ? 1 : 0;
     }
-    const bool small = single && !timing && small_field(tab[0]);
+    const bool small = single && small_field(tab[0]);
     if (small) grid2 = std::min(grid2, kSmallGrid), grid3 = std::min(grid3, kSmallGrid);
     EngineCtx::Graphs& graphs = E.sets[single ? (small ? 2 : 1) : 0];
-    const int launch_steps = small ? kSmallSteps : kGraphSteps;
+    // (timed runs read back kGraphSteps records per launch)
+    const int launch_steps = small && !timing ? kSmallSteps : kGraphSteps;
     if (int rc = E.graph_for(graphs, nf, n2, timing, grid2, grid3, launch_steps)) {
         E.drop_graph();
         return rc;

@@ -9,9 +9,11 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <vector>
 
 namespace {
 std::map<void*, size_t> live;
+std::vector<void*> pinned;
 std::string text;
 size_t largest = ~size_t(0);  // a larger request of device memory fails
 int current = 0, of_stream = 0;
@@ -69,7 +71,11 @@ hipError_t hipMallocFromPoolAsync(void** p, size_t bytes, hipMemPool_t pool, hip
     return take(p, bytes, "pool " + std::to_string(reinterpret_cast<uintptr_t>(pool) - 1));
 }
 hipError_t hipMallocAsync(void** p, size_t bytes, hipStream_t) { return take(p, bytes, "default"); }
-hipError_t hipHostMalloc(void** p, size_t bytes, unsigned) { return take(p, bytes, "host"); }
+hipError_t hipHostMalloc(void** p, size_t bytes, unsigned) {
+    const hipError_t e = take(p, bytes, "host");
+    if (e == hipSuccess) pinned.push_back(*p);
+    return e;
+}
 hipError_t hipFreeAsync(void* p, hipStream_t) {
     const auto it = live.find(p);
     if (it == live.end()) return result(hipErrorInvalidValue);
@@ -89,6 +95,43 @@ hipError_t hipMemsetAsync(void* dst, int v, size_t bytes, hipStream_t) {
     return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+
+// The rest of what a correction needs.  A graph is its list of launches; once
+// launched, the first word of every pinned allocation is cleared, which ends
+// the loop of a correction (its results are zeros).
+hipError_t hipMalloc(void** p, size_t bytes) { return take(p, bytes, "device"); }
+hipError_t hipFree(void* p) { return hipFreeAsync(p, nullptr); }
+hipError_t hipHostGetDevicePointer(void** dev, void* host, unsigned) { return *dev = host, hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { return *v = 256, hipSuccess; }
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { return *n = 4, hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+    return *s = reinterpret_cast<hipStream_t>(static_cast<uintptr_t>(4096)), hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { return *e = nullptr, hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return *e = nullptr, hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipGraphCreate(hipGraph_t* g, unsigned) {
+    return *g = reinterpret_cast<hipGraph_t>(new std::string), hipSuccess;
+}
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphAddKernelNode(hipGraphNode_t*, hipGraph_t g, const hipGraphNode_t*, size_t,
+                                 const hipKernelNodeParams* p) {
+    *reinterpret_cast<std::string*>(g) += "step " + std::to_string(p->gridDim.x) + "\n";
+    return hipSuccess;
+}
+hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t g, hipGraphNode_t*, char*, size_t) {
+    return *e = reinterpret_cast<hipGraphExec_t>(g), hipSuccess;
+}
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+hipError_t hipGraphLaunch(hipGraphExec_t e, hipStream_t) {
+    text += *reinterpret_cast<std::string*>(e);
+    for (void* p : pinned) std::memset(p, 0, 4);
+    return hipSuccess;
+}
+
 hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t shared, hipStream_t s) {
     pushed_grid = grid, pushed_block = block, pushed_shared = shared, pushed_stream = s;
     return hipSuccess;

@@ -1,6 +1,6 @@
 """The host side of the library on a stand-in for the HIP runtime
 (fake_hip.cpp), without a GPU: where the scratch of a call comes from, what a
-call does when memory is short, and that its grids can be launched."""
+call does when memory is short, and the grids it launches."""
 import os
 import subprocess
 import sys
@@ -114,4 +114,21 @@ for m in {some}:
     assert rc == msz.OK, rc
     asked.append([x for x in log() if x.startswith(("pool", "default"))])
 assert all(a == asked[0] for a in asked), asked
+""")
+
+
+@pytest.mark.parametrize("nx,ny,blocks", [(120, 130, 256), (3600, 2400, 1024)])
+def test_timed_corrections_launch_the_same_grids(fake, nx, ny, blocks):
+    """What a timed run of a field measures is what an untimed one runs: the
+    blocks of its steps do not depend on the timing."""
+    run(fake, f"""
+st = msz.Stats()
+for flags in (0, msz.FLAG_TIMING, 0):
+    fake.fake_set(EVERY, 0, 0)
+    opt = msz.Options()
+    opt.flags = flags
+    rc = L.msz_fix(f, f, msz.Dims(2, {nx}, {ny}, 1), ctypes.c_float(0.5), M, ctypes.byref(opt), ctypes.byref(st), None)
+    assert rc == msz.OK, rc
+    steps = [x for x in log() if x.startswith("step")]
+    assert steps and all(x == "step {blocks}" for x in steps), steps
 """)
