@@ -98,6 +98,13 @@ hipMemPool_t scratch_pool(int dev) {
     return pools[dev];
 }
 
+// The runtime's last error is said by the result; left, it would pass for an
+// error of the next launch.
+static int out_of_memory() {
+    (void)hipGetLastError();
+    return MSZ_ENOMEM;
+}
+
 Scratch::~Scratch() {
     if (owned && p) (void)hipFreeAsync(p, s);
 }
@@ -120,9 +127,8 @@ int Scratch::get(void* user, size_t user_bytes, size_t need, hipStream_t stream)
         (void)hipMemPoolTrimTo(pool, 0);
     }
     if (hipMallocAsync(&p, need, stream) != hipSuccess) {
-        (void)hipGetLastError();  // said by the result; left, it would pass for an error of the next launch
         p = nullptr;
-        return MSZ_ENOMEM;
+        return out_of_memory();
     }
     owned = true;
     return MSZ_OK;
@@ -319,7 +325,7 @@ struct EngineCtx {
         const size_t ot = take(stamp_bytes());
         const size_t oc2 = take(sizeof(unsigned) * kCntBlockWords * kEngMaxFields);
         void* p = nullptr;
-        if (hipMalloc(&p, o) != hipSuccess) return MSZ_ENOMEM;
+        if (hipMalloc(&p, o) != hipSuccess) return out_of_memory();
         ctl_mem = static_cast<char*>(p);
         fields = reinterpret_cast<EngField*>(ctl_mem + of);
         states = reinterpret_cast<EngState*>(ctl_mem + os);
@@ -334,15 +340,15 @@ struct EngineCtx {
         counters = reinterpret_cast<unsigned*>(ctl_mem + oc2);
         if (!host) {
             void* h = nullptr;
-            if (hipHostMalloc(&h, host_bytes(), hipHostMallocDefault) != hipSuccess)
-                return MSZ_ENOMEM;
+            if (hipHostMalloc(&h, host_bytes(), hipHostMallocDefault) != hipSuccess) return out_of_memory();
             host = static_cast<int*>(h);
         }
         if (!hflag) {
             void* h = nullptr;
             void* d = nullptr;
             static_assert((kHostStatsWord + sizeof(EngStats) / 4) * 4 <= 512, "host word block");
-            if (hipHostMalloc(&h, 512, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) return MSZ_ENOMEM;
+            if (hipHostMalloc(&h, 512, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
+                return out_of_memory();
             if (hipHostGetDevicePointer(&d, h, 0) != hipSuccess) return MSZ_EDEVICE;
             hflag = static_cast<int*>(h);
             hflag_dev = static_cast<int*>(d);

@@ -613,7 +613,10 @@ unsigned* enc_host_words() {
     thread_local unsigned* p = nullptr;
     if (!p) {
         void* q = nullptr;
-        if (hipHostMalloc(&q, 4 * (kEncGapSyms + kEncValSyms), hipHostMallocDefault) != hipSuccess) return nullptr;
+        if (hipHostMalloc(&q, 4 * (kEncGapSyms + kEncValSyms), hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();  // said by the result
+            return nullptr;
+        }
         p = static_cast<unsigned*>(q);
     }
     return p;

@@ -60,6 +60,12 @@ assert fake.fake_live() == 1  # the pinned counters
 def test_calls_after_one_without_memory(fake):
     """A call that found no memory says so, and the next one is not affected."""
     run(fake, """
+opt, st = msz.Options(), msz.Stats()
+opt.workspace, opt.workspace_bytes = array(L.msz_workspace_bytes(d)), L.msz_workspace_bytes(d)
+fake.fake_set(100, 0, 0)  # no memory for the control block
+assert L.msz_fix(f, f, d, ctypes.c_float(0.5), M, ctypes.byref(opt), ctypes.byref(st), None) == msz.ENOMEM
+fake.fake_set(EVERY, 0, 0)
+assert L.msz_labels(f, d, M, m, None) == msz.OK
 for call in (lambda: L.msz_count_false(f, f, d, ctypes.byref(counts), None), lambda: L.msz_labels(f, d, M, m, None)):
     fake.fake_set(100, 0, 0)
     assert call() == msz.ENOMEM
