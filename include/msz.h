@@ -28,13 +28,16 @@
  *    graph of 48 steps (30 for a small field alone) is relaunched until the
  *    device clears a done word in pinned host memory.
  *  - Memory: when no workspace is given, the library takes scratch for the
- *    call, ordered on the stream, from a memory pool of its own, which keeps
- *    at most 512 MB per device between calls.  It also keeps one control block
- *    (about 9 MB: field table, step states, round counters, statistics) with
- *    up to three cached graphs, and 512 bytes of pinned, device-mapped host
- *    memory (the done word and the final statistics of one-field runs) per
- *    host thread and device for the life of the process.  msz_fix_noalloc allocates
- *    nothing: it works in a static device array instead (see there).
+ *    call, on the stream's device and ordered on the stream, from a memory pool
+ *    of its own.  Of what a call gives back the pool keeps up to 512 MB per
+ *    device; the rest stays mapped until the next wait for a stream of the
+ *    device (such as the next call's).  The library also keeps, per host thread
+ *    and device, for the life of the process, one control block (about 9 MB:
+ *    field table, step states, round counters, statistics) with up to four
+ *    cached graphs, and pinned host memory (about 60 KB of records and
+ *    counters, and 512 device-mapped bytes: the done word and the final
+ *    statistics of one-field runs).  msz_fix_noalloc allocates nothing: it
+ *    works in a static device array instead (see there).
  *  - Errors: the return code is the only error channel; no global state
  *    besides the pool and control block above.  msz_strerror() names a code.  Inputs
  *    must be finite with magnitude at most 2^100 (so that no edit can

@@ -56,10 +56,10 @@ bool make_grid(const msz_dims& d, Grid& gr) {
 // default pool gives everything back at each wait for the stream, so every
 // call mapped its scratch again: of the 600 us of a msz_count_false of
 // 3600x2400 after a wait, 370 were that, and 2.5 ms of the 3.0 of a
-// msz_encode_edits.  This one keeps at most kPoolKeep bytes between calls and
-// gives back what is above at the next wait, all of it when an allocation
-// fails; the runtime orders its memory by stream, so calls of several threads
-// and streams may share it.
+// msz_encode_edits.  This one keeps at most kPoolKeep bytes past the next wait
+// for a stream, and gives back all of it when an allocation fails; the runtime
+// orders its memory by stream, so calls of several threads and streams may
+// share it.
 constexpr uint64_t kPoolKeep = 512u << 20;
 constexpr int kMaxDevices = 64;
 
@@ -293,7 +293,7 @@ struct EngineCtx {
         for (Graphs& G : sets) G.drop();
     }
     // No destructor work: at process exit the HIP runtime may already be torn
-    // down, and the device memory (about 0.4 MB per host thread) is reclaimed
+    // down, and the device memory (about 9 MB per host thread) is reclaimed
     // with the process.
 
     static size_t host_bytes() { return 256 + stamp_bytes(); }

@@ -2340,11 +2340,14 @@ __device__ __forceinline__ bool draw_last(int* ticket, int n, int* s_flag) {
 // Bound by latency: a round of a few cases takes 3 to 5 us (one gather for
 // the targets, one for the refresh, the LDS atomics of the set and five
 // barriers) where two step kernels take 11 on a 128x128 field and 25 on a
-// 3600x2400 one; 256 more refreshes add about 2.5 us, so rounds beyond a few
-// hundred cases are left to all blocks.  128x128 bumps 0.68 -> 0.43 ms,
-// 3600x2400 1.99 -> 1.82 ms, the 96-field batch 24.9 -> 22.6 ms.  (Flags
-// and claims in memory, as the other rounds use, with a workgroup-scope atomic
-// per neighbour, took 7 us a round.)
+// 3600x2400 one; 256 more refreshes add about 2.5 us, so that a round as large
+// as the set allows takes what two steps of such a field do, and larger ones
+// are left to all blocks.  (A limit of 96 cases instead of 256, 208 in 3D:
+// 110^3 fields 1.56 -> 1.49 ms, 1500x2000 ones 2.31 -> 2.41, all others tried
+// within 8% either way.)  128x128 bumps 0.68 -> 0.43 ms, 3600x2400 1.99 -> 1.82
+// ms, the 96-field batch 24.9 -> 22.6 ms.  (Flags and claims in memory, as the
+// other rounds use, with a workgroup-scope atomic per neighbour, took 7 us a
+// round.)
 constexpr int kSparseList = 512;     // listed cases, and changed vertices of a round
 constexpr int kSparseSlots = 4096;   // hash table
 constexpr int kSparseDirty = 3328;   // vertices in it
