@@ -28,18 +28,18 @@
  *    graph of 48 steps (30 for a small field alone) is relaunched until the
  *    device clears a done word in pinned host memory.
  *  - Memory: when no workspace is given, the library takes scratch for the
- *    call, on the stream's device and ordered on the stream, from a memory pool
- *    of its own.  Of what a call gives back the pool keeps up to 512 MB per
- *    device; the rest stays mapped until the next wait for a stream of the
- *    device (such as the next call's).  The library also keeps, per host thread
- *    and device, for the life of the process, one control block (about 9 MB:
- *    field table, step states, round counters, statistics) with up to four
- *    cached graphs, and pinned host memory (about 60 KB of records and
- *    counters, and 512 device-mapped bytes: the done word and the final
+ *    call on the stream's device.  It keeps at most 512 MB per device of what
+ *    calls give back (after a wait for their stream), for later calls on any
+ *    stream and thread; larger scratch is given back at once, and all that is
+ *    kept when scratch cannot be allocated.  The library also keeps, per host
+ *    thread and device, for the life of the process, one control block (about
+ *    9 MB: field table, step states, round counters, statistics) with up to
+ *    four cached graphs, and pinned host memory (some tens of KB of counters
+ *    and records, and 512 device-mapped bytes: the done word and the final
  *    statistics of one-field runs).  msz_fix_noalloc allocates nothing: it
  *    works in a static device array instead (see there).
  *  - Errors: the return code is the only error channel; no global state
- *    besides the pool and control block above.  msz_strerror() names a code.  Inputs
+ *    besides the kept scratch and control block above.  msz_strerror() names a code.  Inputs
  *    must be finite with magnitude at most 2^100 (so that no edit can
  *    overflow float32).
  *  - Concurrency: calls on different streams with separate workspaces are
@@ -350,8 +350,8 @@ size_t msz_edits_bound(int64_t n);
  * (DEVICE, 16-byte aligned, capacity bytes).  *out_bytes (HOST) receives the
  * encoded size; MSZ_EINVAL if it exceeds capacity (msz_edits_bound(n) always
  * suffices) or if the stream would pass 2^32 words (more than about 1.4e9
- * edits).  stats (HOST) may be NULL.  Takes its scratch (at most about 8 bytes
- * per entry) from the library's pool and synchronises before returning. */
+ * edits).  stats (HOST) may be NULL.  Takes scratch (about 8 bytes per edit) and
+ * synchronises before returning. */
 int msz_encode_edits(const float* edits, int64_t n, void* out, size_t capacity, size_t* out_bytes,
                      msz_edit_stats* stats, void* stream);
 

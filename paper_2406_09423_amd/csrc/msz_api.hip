@@ -18,6 +18,7 @@
 #include <cmath>
 #include <cstring>
 #include <mutex>
+#include <utility>
 #include <vector>
 
 #include "../../include/msz.h"
@@ -52,50 +53,75 @@ bool make_grid(const msz_dims& d, Grid& gr) {
     return true;
 }
 
-// One memory pool per device for the scratch of all calls.  The device's
-// default pool gives everything back at each wait for the stream, so every
-// call mapped its scratch again: of the 600 us of a msz_count_false of
-// 3600x2400 after a wait, 370 were that, and 2.5 ms of the 3.0 of a
-// msz_encode_edits.  This one keeps at most kPoolKeep bytes past the next wait
-// for a stream, and gives back all of it when an allocation fails; the runtime
-// orders its memory by stream, so calls of several threads and streams may
-// share it.
-constexpr uint64_t kPoolKeep = 512u << 20;
 constexpr int kMaxDevices = 64;
 
 // The device of a stream (as an allocation on the stream takes it); -1 if
 // there is none.  The null stream and the two other handles that name no
 // stream object (1 and 2) stand for streams of the current device.
-int device_of(hipStream_t stream) {
+static int device_of(hipStream_t stream) {
     int dev = 0;
     const bool object = reinterpret_cast<uintptr_t>(stream) > 2;
-    if ((object ? hipStreamGetDevice(stream, &dev) : hipGetDevice(&dev)) == hipSuccess) return dev;
+    if ((object ? hipStreamGetDevice(stream, &dev) : hipGetDevice(&dev)) == hipSuccess) return dev < kMaxDevices ? dev : -1;
     (void)hipGetLastError();
     return -1;
 }
 
-hipMemPool_t scratch_pool(int dev) {
-    static std::mutex mu;
-    static hipMemPool_t pools[kMaxDevices] = {};
-    if (dev < 0 || dev >= kMaxDevices) return nullptr;
-    std::lock_guard<std::mutex> lock(mu);
-    if (!pools[dev]) {
-        hipMemPoolProps props{};
-        props.allocType = hipMemAllocationTypePinned;
-        props.handleTypes = hipMemHandleTypeNone;
-        props.location.type = hipMemLocationTypeDevice;
-        props.location.id = dev;
-        hipMemPool_t p = nullptr;
-        uint64_t keep = kPoolKeep;
-        if (hipMemPoolCreate(&p, &props) != hipSuccess ||
-            hipMemPoolSetAttribute(p, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
-            if (p) (void)hipMemPoolDestroy(p);
-            (void)hipGetLastError();  // the call goes on with the default pool
-            return nullptr;
-        }
-        pools[dev] = p;
+// The scratch of past calls, kept for later ones of any stream and thread: at
+// most kScratchKeep bytes per device, all given back when an allocation fails.
+// A call waits for its stream before its scratch comes here, so that a block at
+// hand is free on the device.  The runtime's own pools give memory back at
+// waits and frees (also below their release threshold, all but the block freed
+// last), so that calls mapped their scratch again: 370 of the 600 us of a
+// msz_count_false of 3600x2400 after a wait, 2.5 ms of the 3.0 of a
+// msz_encode_edits, and some 300 us of a call after one with larger scratch.
+constexpr size_t kScratchKeep = size_t(512) << 20;
+
+struct ScratchBlock {
+    void* p;
+    size_t bytes;
+};
+
+class ScratchCache {
+  public:
+    // The smallest block of at least `need` bytes that is not far too large.
+    bool take(int dev, size_t need, ScratchBlock& b) {
+        const size_t most = 8 * std::max(need, size_t(1) << 20);
+        std::lock_guard<std::mutex> lock(mu_);
+        std::vector<ScratchBlock>& v = blocks_[dev];
+        size_t best = v.size();
+        for (size_t k = 0; k < v.size(); ++k)
+            if (v[k].bytes >= need && v[k].bytes <= most && (best == v.size() || v[k].bytes < v[best].bytes)) best = k;
+        if (best == v.size()) return false;
+        b = v[best];
+        v.erase(v.begin() + best);
+        return true;
     }
-    return pools[dev];
+    // Keeps b; the blocks kept longest go where they are too many now (out).
+    void put(int dev, ScratchBlock b, std::vector<ScratchBlock>& out) {
+        std::lock_guard<std::mutex> lock(mu_);
+        std::vector<ScratchBlock>& v = blocks_[dev];
+        v.push_back(b);
+        size_t total = 0;
+        for (const ScratchBlock& x : v) total += x.bytes;
+        for (; total > kScratchKeep; v.erase(v.begin())) {
+            total -= v.front().bytes;
+            out.push_back(v.front());
+        }
+    }
+    std::vector<ScratchBlock> take_all(int dev) {
+        std::lock_guard<std::mutex> lock(mu_);
+        return std::exchange(blocks_[dev], {});
+    }
+
+  private:
+    std::mutex mu_;
+    std::vector<ScratchBlock> blocks_[kMaxDevices];
+};
+
+// Never destroyed: at process exit the runtime may already be torn down.
+static ScratchCache& scratch_cache() {
+    static ScratchCache* c = new ScratchCache;
+    return *c;
 }
 
 // The runtime's last error is said by the result; left, it would pass for an
@@ -106,7 +132,11 @@ static int out_of_memory() {
 }
 
 Scratch::~Scratch() {
-    if (owned && p) (void)hipFreeAsync(p, s);
+    if (!owned || !p) return;
+    std::vector<ScratchBlock> out;
+    if (dev >= 0 && bytes <= kScratchKeep && hipStreamSynchronize(s) == hipSuccess) scratch_cache().put(dev, {p, bytes}, out);
+    else out.push_back({p, bytes});
+    for (const ScratchBlock& b : out) (void)hipFreeAsync(b.p, s);
 }
 
 int Scratch::get(void* user, size_t user_bytes, size_t need, hipStream_t stream) {
@@ -116,20 +146,26 @@ int Scratch::get(void* user, size_t user_bytes, size_t need, hipStream_t stream)
         p = user;
         return MSZ_OK;
     }
-    need = std::max<size_t>(need, 256);
-    hipMemPool_t pool = scratch_pool(device_of(stream));
-    if (pool) {
-        if (hipMallocFromPoolAsync(&p, need, pool, stream) == hipSuccess) {
-            owned = true;
-            return MSZ_OK;
+    dev = device_of(stream);
+    ScratchBlock b{nullptr, need};
+    if (dev < 0 || !scratch_cache().take(dev, need, b)) {
+        // a little more than asked for, so that the block serves similar calls
+        if (need <= kScratchKeep) {
+            size_t step = size_t(256) << 10;
+            while (16 * step <= need) step *= 2;
+            b.bytes = (need + step - 1) / step * step;
         }
-        (void)hipGetLastError();
-        (void)hipMemPoolTrimTo(pool, 0);
+        if (hipMallocAsync(&b.p, b.bytes, stream) != hipSuccess) {
+            (void)hipGetLastError();
+            if (dev >= 0)
+                for (const ScratchBlock& x : scratch_cache().take_all(dev)) (void)hipFreeAsync(x.p, stream);
+            (void)hipStreamSynchronize(stream);
+            b.bytes = std::max<size_t>(need, 256);
+            if (hipMallocAsync(&b.p, b.bytes, stream) != hipSuccess) return out_of_memory();
+        }
     }
-    if (hipMallocAsync(&p, need, stream) != hipSuccess) {
-        p = nullptr;
-        return out_of_memory();
-    }
+    p = b.p;
+    bytes = b.bytes;
     owned = true;
     return MSZ_OK;
 }

@@ -36,8 +36,6 @@ namespace msz {
 constexpr int kEncGapSyms = 32, kEncValSyms = 512, kEncMaxLen = 20;
 constexpr int kEncChunk = 256;         // edits per chunk (one decoding thread each)
 constexpr int kEncBlock = 4096;        // dense entries per compaction block (256 threads x 16)
-constexpr unsigned kEncFew = 1u << 17;    // edits whose scratch (8 bytes each) costs nothing to map
-constexpr int64_t kEncKept = 60 << 20;    // entries whose scratch the pool keeps between calls
 constexpr int kEncHeader = 576;        // header bytes (24 fixed + 544 code lengths, padded)
 constexpr unsigned kEncMagic = 0x455A534Du;  // "MSZE"
 constexpr unsigned kEncVersion = 1u;
@@ -678,15 +676,7 @@ int msz_encode_edits(const float* edits, int64_t n, void* out, size_t capacity, 
         o += (b + 255) & ~size_t(255);
         return r;
     };
-    // The pool hands a kept block out again only for a request of about its
-    // size.  So where the edits take more than its smallest blocks, the second
-    // part is as large as any edits of the field may need, if the pool keeps
-    // such a block, and otherwise sized for the next power of two of edits.
-    // (Sized for the edits themselves, each new set of a 3600x2400 field's
-    // mapped memory: 300 to 640 us a call, where this takes 165 to 220.)
-    size_t room = 1;
-    while (room < m) room *= 2;
-    if ((m > kEncFew && n <= kEncKept) || room > static_cast<size_t>(n)) room = static_cast<size_t>(n);
+    const size_t room = m;
     const size_t o_idx = take(4 * room), o_val = take(4 * room),
                  o_cw = take(4 * (room / kEncChunk + 2)), o_hist = take(4 * (kEncGapSyms + kEncValSyms)),
                  o_tab = take(sizeof(EncTables));

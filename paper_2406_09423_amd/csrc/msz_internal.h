@@ -131,11 +131,13 @@ namespace msz {
 // Validates dims (ndim 2 or 3, nz == 1 in 2D, positive sides, n <= 2^31 - 2^16) and fills gr.
 bool make_grid(const msz_dims& d, Grid& gr);
 
-// Device scratch of one call: the caller's, or taken from the library's pool
-// on the call's stream and given back to it at the end.
+// Device scratch of one call: the caller's, or the library's own, kept for
+// later calls at the end (after a wait for the call's stream).
 struct Scratch {
     void* p = nullptr;
+    size_t bytes = 0;
     hipStream_t s = nullptr;
+    int dev = -1;
     bool owned = false;
     ~Scratch();
     int get(void* user, size_t user_bytes, size_t need, hipStream_t stream);

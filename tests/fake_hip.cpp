@@ -51,7 +51,11 @@ void fake_set(size_t largest_request, int current_device, int device_of_streams)
 void fake_word(unsigned w) { word = w; }
 void fake_pattern(int on) { pattern = on != 0; }
 const char* fake_log() { return text.c_str(); }
-size_t fake_live() { return live.size(); }
+size_t fake_live_bytes() {
+    size_t n = 0;
+    for (const auto& b : live) n += b.second;
+    return n;
+}
 
 hipError_t hipGetDevice(int* dev) { return *dev = current, hipSuccess; }
 hipError_t hipStreamGetDevice(hipStream_t, hipDevice_t* dev) { return *dev = of_stream, hipSuccess; }
@@ -60,17 +64,7 @@ hipError_t hipGetLastError() {
     last = hipSuccess;
     return e;
 }
-hipError_t hipMemPoolCreate(hipMemPool_t* pool, const hipMemPoolProps* props) {
-    *pool = reinterpret_cast<hipMemPool_t>(static_cast<uintptr_t>(1 + props->location.id));
-    return hipSuccess;
-}
-hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void*) { return hipSuccess; }
-hipError_t hipMemPoolDestroy(hipMemPool_t) { return hipSuccess; }
-hipError_t hipMemPoolTrimTo(hipMemPool_t, size_t) { return hipSuccess; }
-hipError_t hipMallocFromPoolAsync(void** p, size_t bytes, hipMemPool_t pool, hipStream_t) {
-    return take(p, bytes, "pool " + std::to_string(reinterpret_cast<uintptr_t>(pool) - 1));
-}
-hipError_t hipMallocAsync(void** p, size_t bytes, hipStream_t) { return take(p, bytes, "default"); }
+hipError_t hipMallocAsync(void** p, size_t bytes, hipStream_t) { return take(p, bytes, "device"); }
 hipError_t hipHostMalloc(void** p, size_t bytes, unsigned) {
     const hipError_t e = take(p, bytes, "host");
     if (e == hipSuccess) pinned.push_back(*p);

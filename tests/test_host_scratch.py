@@ -16,7 +16,7 @@ sys.path.insert(0, sys.argv[2])
 fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)  # ahead of the library's own runtime
 fake.fake_set.argtypes = [ctypes.c_size_t, ctypes.c_int, ctypes.c_int]
 fake.fake_log.restype = ctypes.c_char_p
-fake.fake_live.restype = ctypes.c_size_t
+fake.fake_live_bytes.restype = ctypes.c_size_t
 import paper_2406_09423_amd as msz
 L = msz.lib()
 EVERY = 2 ** 63
@@ -53,7 +53,7 @@ def test_labels_with_little_memory(fake):
     run(fake, """
 fake.fake_set(2 * n, 0, 0)
 assert L.msz_labels(f, d, M, m, None) == msz.OK
-assert fake.fake_live() == 1  # the pinned counters
+assert fake.fake_live_bytes() < 2 << 20
 """)
 
 
@@ -66,31 +66,60 @@ fake.fake_set(100, 0, 0)  # no memory for the control block
 assert L.msz_fix(f, f, d, ctypes.c_float(0.5), M, ctypes.byref(opt), ctypes.byref(st), None) == msz.ENOMEM
 fake.fake_set(EVERY, 0, 0)
 assert L.msz_labels(f, d, M, m, None) == msz.OK
-for call in (lambda: L.msz_count_false(f, f, d, ctypes.byref(counts), None), lambda: L.msz_labels(f, d, M, m, None)):
-    fake.fake_set(100, 0, 0)
-    assert call() == msz.ENOMEM
-    fake.fake_set(EVERY, 0, 0)
-    assert call() == msz.OK
+fake.fake_set(100, 0, 0)  # nor for scratch
+assert L.msz_count_false(f, f, d, ctypes.byref(counts), None) == msz.ENOMEM
+fake.fake_set(EVERY, 0, 0)
+assert L.msz_labels(f, d, M, m, None) == msz.OK
+assert L.msz_count_false(f, f, d, ctypes.byref(counts), None) == msz.OK
 """)
 
 
 def test_scratch_lies_on_the_device_of_the_stream(fake):
-    """A call on a stream of another device than the current one takes its
-    scratch there; on the null stream, from the current device."""
+    """A call takes kept scratch of its stream's device only; on the null
+    stream, of the current device."""
     run(fake, """
 size = ctypes.c_size_t()
 edits, blob = array(4 * n), array(L.msz_edits_bound(n))
 feat, p = array(32 * n), array(4 * n)
 params = array(4 * msz.NET_PARAMS)
-for stream, device in ((STREAM, 3), (None, 1)):
-    for call in (lambda: L.msz_labels(f, d, M, m, stream), lambda: L.msz_count_false(f, f, d, ctypes.byref(counts), stream),
-                 lambda: L.msz_encode_edits(edits, n, blob, L.msz_edits_bound(n), ctypes.byref(size), None, stream),
-                 lambda: L.msz_decode_edits(blob, size.value, edits, n, stream),
-                 lambda: L.msz_net_forward(params, feat, d, p, None, None, None, 0, stream)):
-        fake.fake_set(EVERY, 1, 3)
-        call()
-        asked = [x for x in log() if x.startswith(("pool", "default"))]
-        assert asked and all(x.startswith("pool %d " % device) for x in asked), asked
+for k, call in enumerate([
+        lambda s: L.msz_labels(f, d, M, m, s), lambda s: L.msz_count_false(f, f, d, ctypes.byref(counts), s),
+        lambda s: L.msz_encode_edits(edits, n, blob, L.msz_edits_bound(n), ctypes.byref(size), None, s),
+        lambda s: L.msz_decode_edits(blob, size.value, edits, n, s),
+        lambda s: L.msz_net_forward(params, feat, d, p, None, None, None, 0, s)]):
+    a, b = 2 * k, 2 * k + 1  # devices not used yet
+    asked = []
+    for stream, current, of_stream in ((STREAM, a, b), (STREAM, a, b), (None, a, b), (None, b, a), (STREAM, b, a)):
+        fake.fake_set(EVERY, current, of_stream)
+        call(stream)
+        asked.append(any(x.startswith("device") for x in log()))
+    assert asked == [True, False, True, False, False], asked
+""")
+
+
+def test_scratch_is_kept_and_bounded(fake):
+    """Calls of different sizes in turn take what earlier ones left; what is
+    kept stays below 512 MB, and is given back when memory is short."""
+    run(fake, """
+def call(nx, ny):
+    fake.fake_set(EVERY, 0, 0)
+    assert L.msz_count_false(f, f, msz.Dims(2, nx, ny, 1), ctypes.byref(counts), STREAM) == msz.OK
+    return [x for x in log() if x.startswith("device")]
+sizes = [(3600, 2400), (300, 200), (1800, 1200), (3600, 2390), (320, 190)]
+for nx, ny in sizes:
+    call(nx, ny)
+assert not any(call(nx, ny) for nx, ny in sizes)
+assert fake.fake_live_bytes() < 512 << 20
+for k in range(12):
+    call(5000 + 700 * k, 1000)
+    assert fake.fake_live_bytes() <= (512 << 20) + (1 << 20)
+    call(500, 1000 + 500 * k)
+big = 30000 * 3000  # 900 MB of scratch: not kept
+assert call(30000, 3000) and call(30000, 3000)
+assert fake.fake_live_bytes() <= (512 << 20) + (1 << 20)
+fake.fake_set(30 << 20, 0, 0)  # a request above 30 MB fails: everything kept is given back
+assert L.msz_count_false(f, f, msz.Dims(2, 30000, 3000, 1), ctypes.byref(counts), STREAM) == msz.ENOMEM
+assert fake.fake_live_bytes() <= 1 << 20
 """)
 
 
@@ -104,22 +133,19 @@ assert rc == msz.OK, (rc, log())
 """)
 
 
-@pytest.mark.parametrize("n,some", [(3600 * 2400, (600000, 700000, 840001, 8000000)), (2 ** 27 + 5, (9000000, 11000001, 16000000)),
-                                    (300 * 200, (4100, 5400, 6100, 8000))])
+@pytest.mark.parametrize("n,some", [(3600 * 2400, (600000, 700000, 640001, 1, 690000)),
+                                    (2 ** 27 + 5, (9000000, 11000001, 10500000)), (300 * 200, (4100, 8000, 60000))])
 def test_new_edits_need_no_new_memory(fake, n, some):
-    """The scratch of an encoding is of the same size for any edits of a field
-    (of a large field, or of few edits, for edits of about the same number), so
-    that the pool has it at hand."""
+    """Encoding edits of about as many as before takes no new memory."""
     run(fake, f"""
 size = ctypes.c_size_t()
 asked = []
-for m in {some}:
+for k, m in enumerate((max({some}),) + {some}):
     fake.fake_set(EVERY, 0, 0)
     fake.fake_word(m)  # the number of edits, and the words of the stream
     rc = L.msz_encode_edits(f, {n}, M, ctypes.c_size_t(2 ** 40), ctypes.byref(size), None, None)
     assert rc == msz.OK, rc
-    asked.append([x for x in log() if x.startswith(("pool", "default"))])
-assert all(a == asked[0] for a in asked), asked
+    assert k == 0 or not [x for x in log() if x.startswith("device")], (m, log())
 """)
 
 
