@@ -273,8 +273,13 @@ constexpr int kGraphSteps = kEngTimeSlots;  // steps per graph launch (even: par
 // step's decision: 177x95x48 takes 0.437 ms where 1024 blocks take 0.516, 512
 // 0.460 and 128 0.541 (a 128x128 field takes the same with any number; a
 // 1795x1153 one, 2117 direction items, 1.39 ms with 256 and 1.29 with 1024).
-// Its graphs hold fewer steps: with the sparse rounds such a field is done
-// after about 25, and each idle step costs 1.7 us.
+// Over fields from 64x64 to 900x1100 and 24^3 to 256x40x40 the 256 blocks are
+// up to 22% faster (256x40x40) and at most 8% slower (where the steps below
+// take a second launch).  Its graphs hold fewer steps: with the sparse rounds
+// such a field is done after about 25, and each idle step costs 1.7 us.  Then
+// 30 steps gain 5 to 15% on 48 (64x64 189 and 218 us); a field of 31 to 48
+// steps loses 5 to 8% by a second launch (300x300 538 and 506 us, 40^3 599 and
+// 561).
 constexpr int kSmallGrid = 256;
 constexpr int kSmallSteps = 30;
 static_assert(kSmallSteps % 6 == 0, "parities of 2 and 3 continue across graph launches");
