@@ -1687,7 +1687,9 @@ __global__ void __launch_bounds__(256) k_compare(const uint8_t* __restrict__ dir
 // In fields of fewer than 1024 tiles the walks take less than the other
 // route's launches and its wait unless nearly all lines are long: 1200x1800
 // (570 tiles), a quarter smooth, 157 and 242, a ramp 282 and 209; 2000x2500
-// (1580 tiles), 0.4 of it smooth, 363 and 228.
+// (1580 tiles), 0.4 of it smooth, 363 and 228; and below 320 tiles then too:
+// a 300x300 field of four bumps 84 and 112, a 96^3 ramp (288 tiles) 162 and
+// 250, where 1000x1400 (352) takes 189 and 190.
 // An item is a tile, or a quarter of one (a row group per thread) where the
 // tiles are fewer than the grid's blocks: the walks of a block's groups one
 // after the other then are the kernel's time.  Whole calls: 40x50x60 127 us
@@ -1699,7 +1701,8 @@ struct DirectLimits {
 };
 template <int NDIM>
 __device__ __forceinline__ DirectLimits direct_limits(const Grid& gr) {
-    if (label_tiles_of(gr) < 1024) return {64, 0.9f};
+    const int tiles = label_tiles_of(gr);
+    if (tiles < 1024) return {64, tiles < 320 ? 2.0f : 0.9f};
     return {16, NDIM == 3 ? 0.5f : 0.3f};
 }
 // Whether more than `share` of the 4 n pointers are exits.

@@ -46,8 +46,8 @@ def _seconds(call):
     return sorted(times)[4]
 
 
-# 1088 and 1280 label tiles, and 99 and 60
-@pytest.mark.parametrize("shape", [(2048, 2176), (64, 128, 640), (350, 1100), (40, 31, 150)])
+# 1088, 1280 and 1008 label tiles, and 99 and 60
+@pytest.mark.parametrize("shape", [(2048, 2176), (64, 128, 640), (2000, 2048), (350, 1100), (40, 31, 150)])
 @pytest.mark.parametrize("smooth", [1.0, 0.6, 0.15])
 def test_smooth_and_half_smooth_fields(msz, shape, smooth):
     f = _bumps(shape, smooth, 7)
